@@ -185,6 +185,7 @@ int capture_fused(opara_dag *g, opara_exec **out) {
   for (int32_t v = 0; v < n; ++v) indeg[v] = g->pred_off[v + 1] - g->pred_off[v];
   uint32_t max_lds = 0;
   int32_t placed = 0;
+  std::vector<KernelPlan> plan(g->plan);           // a wave's contractions get their tile shapes together
   while (placed < n) {
     wave.clear();
     for (int32_t i = 0; i < n; ++i) {
@@ -197,8 +198,14 @@ int capture_fused(opara_dag *g, opara_exec **out) {
       ++placed;
       for (int32_t j = g->succ_off[v]; j < g->succ_off[v + 1]; ++j) --indeg[g->succ[j]];
     }
-    // Operators that can share a group kernel: a 256-thread body, one element type.  The rest
-    // (none with the present kernel set) and waves of one run as ordinary kernel nodes.
+    if (wave.size() > 1) {
+      std::vector<KernelPlan *> open[2];             // by element type
+      for (int32_t v : wave)
+        if (tile_choice_open(plan[v].kernel)) open[kernel_is_f16(plan[v].kernel)].push_back(&plan[v]);
+      for (auto &o : open)
+        if (!o.empty()) choose_tiles(o.data(), (int)o.size());
+    }
+    // Operators of one element type share group kernels; waves of one run as ordinary kernel nodes.
     std::vector<int32_t> members;
     auto flush = [&]() {
       if (members.empty()) return;
@@ -214,7 +221,7 @@ int capture_fused(opara_dag *g, opara_exec **out) {
         for (int j = 0; j < kGroupMaxOps; ++j) node.ga.block_end[j] = INT32_MAX;
         int64_t end = 0;
         for (size_t i = 0; i < members.size(); ++i) {
-          const KernelPlan &p = g->plan_group[members[i]];
+          const KernelPlan &p = plan[members[i]];
           node.flavor = std::max(node.flavor, group_flavor(p.kernel));
           node.f16 = kernel_is_f16(p.kernel);
           const int64_t tiles = (int64_t)p.gx * p.gy * p.gz;
@@ -248,16 +255,16 @@ int capture_fused(opara_dag *g, opara_exec **out) {
       std::vector<int32_t> by_flavor[3];
       bool groupable = wave.size() > 1;
       for (int32_t v : wave) {
-        const KernelPlan &p = g->plan_group[v];
+        const KernelPlan &p = plan[v];
         const int f = group_flavor(p.kernel);
-        groupable = groupable && f >= 0 && kernel_is_f16(p.kernel) == kernel_is_f16(g->plan_group[wave[0]].kernel) &&
+        groupable = groupable && f >= 0 && kernel_is_f16(p.kernel) == kernel_is_f16(plan[wave[0]].kernel) &&
                     (int64_t)p.gx * p.gy * p.gz < (1 << 24);
         if (f >= 0) by_flavor[f].push_back(v);
       }
       int64_t below[3] = {0, 0, 0};                    // workgroups of all members lighter than flavour f
       for (int f = 1; f < 3; ++f) {
         below[f] = below[f - 1];
-        for (int32_t v : by_flavor[f - 1]) below[f] += (int64_t)g->plan_group[v].gx * g->plan_group[v].gy * g->plan_group[v].gz;
+        for (int32_t v : by_flavor[f - 1]) below[f] += (int64_t)plan[v].gx * plan[v].gy * plan[v].gz;
       }
       const bool cut2 = !by_flavor[2].empty() && below[2] > kFusedSplitLightBlocks;                       // heavy | rest
       const bool cut1 = !by_flavor[1].empty() && !by_flavor[0].empty() && below[1] > kFusedSplitLightBlocks &&
@@ -265,7 +272,7 @@ int capture_fused(opara_dag *g, opara_exec **out) {
       if (groupable && (cut1 || cut2)) {
         for (int f = 2; f >= 0; --f) {
           for (int32_t v : by_flavor[f]) {
-            const int64_t tiles = (int64_t)g->plan_group[v].gx * g->plan_group[v].gy * g->plan_group[v].gz;
+            const int64_t tiles = (int64_t)plan[v].gx * plan[v].gy * plan[v].gz;
             if (members.size() == (size_t)kGroupMaxOps || blocks + tiles > (1 << 24)) { flush(); blocks = 0; }
             members.push_back(v);
             blocks += tiles + kGroupAlign;
@@ -277,7 +284,7 @@ int capture_fused(opara_dag *g, opara_exec **out) {
       }
     }
     for (int32_t v : wave) {
-      const KernelPlan &p = g->plan_group[v];
+      const KernelPlan &p = plan[v];
       bool light = true;
       const int64_t tiles = (int64_t)p.gx * p.gy * p.gz;
       const bool fits = group_kernel_ok(p.kernel, &light) && wave.size() > 1 && tiles < (1 << 24);
@@ -289,7 +296,7 @@ int capture_fused(opara_dag *g, opara_exec **out) {
         continue;
       }
       if (!members.empty() && (members.size() == (size_t)kGroupMaxOps || blocks + tiles > (1 << 24) ||
-                               kernel_is_f16(p.kernel) != kernel_is_f16(g->plan_group[members[0]].kernel))) {
+                               kernel_is_f16(p.kernel) != kernel_is_f16(plan[members[0]].kernel))) {
         flush();
         blocks = 0;
       }
@@ -670,7 +677,7 @@ int build_persist_image(const opara_dag *g, int32_t n_workgroups, const char *wh
     const int64_t chunk = (t + wgs - 1) / wgs;                  // 1 unless the operator has more tiles than workgroups
     const int64_t items = (t + chunk - 1) / chunk;
     total += (items + kPersistItemAlign - 1) / kPersistItemAlign * kPersistItemAlign;
-    rec[i].kernel = kid + (g->ops[v].op_type == OPARA_BGEMM ? kPersistActivationB : 0);
+    rec[i].kernel = kid;
     rec[i].gx = (int32_t)p.gx; rec[i].gy = (int32_t)p.gy; rec[i].gz = (int32_t)p.gz;
     rec[i].args = p.args;
     const int32_t np = g->pred_off[v + 1] - g->pred_off[v];
@@ -835,7 +842,7 @@ int64_t chain_blocks_of(const KernelPlan &p) {
 extern "C" int opara_chained_workspace_bytes(const opara_dag *g, uint64_t *bytes) {
   if (!g || !bytes) { set_error("opara_chained_workspace_bytes: null pointer"); return OPARA_EINVAL; }
   int64_t total = 0;
-  for (int32_t v = 0; v < g->n; ++v) total += chain_blocks_of(g->plan_group[v]);
+  for (int32_t v = 0; v < g->n; ++v) total += chain_blocks_of(g->plan[v]);
   *bytes = chain_layout(g->n, total).bytes;
   return OPARA_OK;
 }
@@ -849,7 +856,7 @@ extern "C" int opara_capture_chained(opara_dag *g, void *workspace, uint64_t wor
   const int32_t np_ops = n - prefix;
   if (n > 65535) { set_error("opara_capture_chained: more than 65535 operators"); return OPARA_EUNSUPPORTED; }
   int64_t total = 0;
-  for (int32_t i = 0; i < np_ops; ++i) total += chain_blocks_of(g->plan_group[g->order[prefix + i]]);
+  for (int32_t i = 0; i < np_ops; ++i) total += chain_blocks_of(g->plan[g->order[prefix + i]]);
   if (total > (int64_t)1 << 30) { set_error("opara_capture_chained: %lld workgroups in one launch", (long long)total); return OPARA_EUNSUPPORTED; }
   const ChainLayout lay = chain_layout(n, total);
   const PersistLayout play = persist_layout(n);
@@ -872,7 +879,7 @@ extern "C" int opara_capture_chained(opara_dag *g, void *workspace, uint64_t wor
   int64_t at = 0;
   for (int32_t i = 0; i < np_ops; ++i) {
     const int32_t v = g->order[prefix + i];
-    const KernelPlan &p = g->plan_group[v];
+    const KernelPlan &p = g->plan[v];
     bool light = true;
     if (!chain_kernel_ok(p.kernel, &light)) { set_error("opara_capture_chained: operator %d has no 256-thread kernel", v); return OPARA_EUNSUPPORTED; }
     if (i == 0) f16 = kernel_is_f16(p.kernel);
@@ -882,7 +889,7 @@ extern "C" int opara_capture_chained(opara_dag *g, void *workspace, uint64_t wor
     pos_of[v] = i;
     const int64_t tiles = (int64_t)p.gx * p.gy * p.gz, blocks = chain_blocks_of(p);
     ChainRec &r = rec[i];
-    r.kernel = p.kernel + (g->ops[v].op_type == OPARA_BGEMM ? kPersistActivationB : 0);
+    r.kernel = p.kernel;
     r.gx = (int32_t)p.gx; r.gy = (int32_t)p.gy; r.gz = (int32_t)p.gz;
     r.begin = (int32_t)at;
     r.tiles = (int32_t)tiles;

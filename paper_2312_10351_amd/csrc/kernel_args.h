@@ -26,6 +26,8 @@ struct IgemmArgs {
   int32_t b_kmajor;             // second operand stored [K][N]
   int32_t relu;
   float alpha;
+  uint32_t div_HoWo, div_Wo, div_Cin, div_kw;   // min(2^32 / d, 2^32 - 1): see fast_div
+  uint32_t x_bytes, w_bytes;    // what the operands span (one batch element), 0 if kOperandMaxBytes or more
 };
 
 struct PoolArgs {
@@ -66,20 +68,22 @@ struct ConcatArgs {
 // X(name, ArgsType).  Order defines kernel ids.
 #define OPARA_KERNEL_LIST(X)            \
   X(igemm_f16_t128x64, IgemmArgs)       \
+  X(igemm_f16_tile64x64, IgemmArgs)     \
+  X(igemm_f16_tile128x128, IgemmArgs)   \
   X(igemm_f16_t64x64, IgemmArgs)        \
   X(igemm_f16_direct4, IgemmArgs)       \
-  X(igemm_f16_direct8, IgemmArgs)       \
   X(igemm_f16_quad4, IgemmArgs)         \
-  X(igemm_f16_quad8, IgemmArgs)         \
   X(igemm_f16_quad64x4, IgemmArgs)      \
+  X(igemm_f16_quad64x64, IgemmArgs)     \
   X(igemm_f16_t64x64_scalar, IgemmArgs) \
   X(igemm_f32_t128x64, IgemmArgs)       \
+  X(igemm_f32_tile64x64, IgemmArgs)     \
+  X(igemm_f32_tile128x128, IgemmArgs)   \
   X(igemm_f32_t64x64, IgemmArgs)        \
   X(igemm_f32_direct4, IgemmArgs)       \
-  X(igemm_f32_direct8, IgemmArgs)       \
   X(igemm_f32_quad4, IgemmArgs)         \
-  X(igemm_f32_quad8, IgemmArgs)         \
   X(igemm_f32_quad64x4, IgemmArgs)      \
+  X(igemm_f32_quad64x64, IgemmArgs)     \
   X(igemm_f32_t64x64_scalar, IgemmArgs) \
   X(gemv_f16, IgemmArgs)                \
   X(gemv_f32, IgemmArgs)                \
@@ -163,19 +167,20 @@ struct GroupArgs {
   KernelArgs args[kGroupMaxOps];
 };
 
+// Operands of the LDS-fed contractions are addressed through 32-bit buffer offsets; this
+// offset is past the end of every operand they accept, and stays so with a row of K added.
+constexpr uint32_t kOperandMaxBytes = 0xc0000000u;
+
 // Tile geometry of the implicit-GEMM kernels (output columns x rows per workgroup).
-struct IgemmTile { int bn, bm, threads; };
-constexpr IgemmTile kTile128x64{128, 64, 256};   // 128 output columns x 64 rows
-constexpr double kTiledMinFlops = 6.0e9;          // lighter contractions use the latency-oriented kernels
-constexpr double kTiledMinFlopsPersistent = 2.0e9;   // inside the persistent kernel (four wavefronts per tile whatever K is)
+struct IgemmTile { int bn, bm; };
+constexpr IgemmTile kTile128x64{128, 64};
+constexpr double kTiledMinFlopsPersistent = 2.0e9;   // persistent kernel: lighter contractions use 32 x 32 tiles
 constexpr int kTiledMinTiles = 80;               // ... and so do contractions with fewer 128x64 tiles
-constexpr IgemmTile kTile64{64, 64, 256};
-constexpr int64_t kQuadMinRowBytes = 1024;   // rows of K at least this long take the quad-coalesced variant
-constexpr int kQuad64MinTiles = 128;             // GEMM-shaped operands with at least this many 64 x 64 tiles take them
-constexpr double kQuad64MaxFlops = 4.0e10;       // ... up to this weight (measured up to 1.7e10)
-constexpr int kQuadFourWaveTiles = 128;          // from this many 32 x 32 tiles on, four wavefronts per tile whatever K is
-constexpr int kDirectTile = 32;       // output tile edge of the latency-oriented kernels
-constexpr int kSmallTile = 16;        // ... of their small-tile forms, for operators with few 32 x 32 tiles
+constexpr IgemmTile kTile64{64, 64};
+constexpr int64_t kQuadMinRowBytes = 512;    // shorter rows of K stay on the fragment-loading kernels
+constexpr int64_t kDirectMaxTiles32 = 2048;  // ... unless there are so many tiles that bytes count, not latency
+constexpr int kDirectTile = 32;       // output tile edge of the fragment-loading kernels
+constexpr int kSmallTile = 16;        // ... of their small-tile form, for operators with few 32 x 32 tiles
 constexpr int kSmallTileMaxTiles32 = 100;   // at most this many 32 x 32 tiles: take 16 x 16 ones (four times as many workgroups)
 
 constexpr int kRowGroupWave = 64;     // threads cooperating on one row (wave variant)

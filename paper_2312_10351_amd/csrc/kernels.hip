@@ -30,43 +30,18 @@ __device__ __forceinline__ Blk launch_blk() {
 template <typename T> struct Vec16;
 template <> struct Vec16<half_t> { typedef half8 type; typedef half4 quad; static constexpr int N = 8; };
 template <> struct Vec16<float> { typedef floatx4 type; typedef floatx4 quad; static constexpr int N = 4; };
+template <typename T> struct VecRun { static constexpr int N = 16 / (4 * sizeof(T)); };   // runs of four elements in 16 bytes
 
 // Access policy of a body.  Ordinary launches use plain loads and stores: kernel
-// boundaries make results visible.  Inside the persistent executor an operator's inputs
-// were written by other workgroups of the same launch, possibly on another XCD with its
-// own L2; there every access to an activation is an agent-scope (device-coherent) access,
+// boundaries make results visible.  Inside the persistent and chained executors an
+// operator's inputs were written by other workgroups of the same launch, possibly on another
+// XCD with its own L2; there results are stored with agent-scope (device-coherent) accesses,
 // which the hardware completes at the point all XCDs share, so that a completion counter
-// published after a wait for the stores is all the synchronisation a consumer needs: no
-// cache write-back or invalidate.  Weights are never written and stay plain (L2-cached).
-constexpr int kCohAct = 1;     // first operand, residual inputs, row/element inputs, outputs
-constexpr int kCohW = 2;       // second operand too (batched GEMM of two activations)
-constexpr int kCohStore = 4;   // outputs only: loads stay plain and follow a cache invalidate
+// published after a wait for the stores is all the synchronisation a consumer needs: no cache
+// write-back.  Loads stay plain and follow a cache invalidate.
+constexpr int kCohStore = 1;
 
-template <bool COH, typename V, typename P>
-__device__ __forceinline__ V ldg(const P *p) {
-  if constexpr (!COH) {
-    return *(const V *)p;
-  } else {
-    V v;
-    if constexpr (sizeof(V) == 16) {
-      uint64_t q[2];
-      q[0] = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      q[1] = __hip_atomic_load((const uint64_t *)p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_memcpy(&v, q, 16);
-    } else if constexpr (sizeof(V) == 8) {
-      const uint64_t q = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_memcpy(&v, &q, 8);
-    } else if constexpr (sizeof(V) == 4) {
-      const uint32_t q = __hip_atomic_load((const uint32_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_memcpy(&v, &q, 4);
-    } else {
-      static_assert(sizeof(V) == 2, "access width");
-      const uint16_t q = __hip_atomic_load((const uint16_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_memcpy(&v, &q, 2);
-    }
-    return v;
-  }
-}
+template <typename V, typename P> __device__ __forceinline__ V ldg(const P *p) { return *(const V *)p; }
 
 template <bool COH, typename V, typename P>
 __device__ __forceinline__ void stg(P *p, const V &v) {
@@ -121,6 +96,26 @@ template <> __device__ __forceinline__ floatx4 mma16<float>(floatx4 a, floatx4 b
   return c;
 }
 
+// acc[i][j] += a[i] . b[j] over one 16-byte chunk per lane.  In fp32 the chunk takes four matrix
+// instructions; they go round the accumulators, so that no two in a row depend on each other.
+template <typename T, int NI, int NJ>
+__device__ __forceinline__ void mma_block(const typename Vec16<T>::type (&a)[NI], const typename Vec16<T>::type (&b)[NJ],
+                                          floatx4 (&acc)[NI][NJ]) {
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = mma16<T>(a[i], b[j], acc[i][j]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+  }
+}
+
 // Thread index as a body sees it.  Inside the persistent kernel (COH != 0) the LDS-staged
 // 64 x 64 contraction takes it through a statement the optimiser cannot see through: what it
 // derives from it then stays inside the body instead of becoming an invariant of the
@@ -154,7 +149,7 @@ __device__ __forceinline__ void igemm_body(const AR &a, const Blk &b, unsigned c
   const int t = body_thread<COH>(), lane = t & 63, wave = t >> 6;
   const int wn0 = (wave % WN) * (BN / WN), wm0 = (wave / WN) * (BM / WM);
   const int m0 = b.x * BM, n0 = b.y * BN;
-  constexpr bool CA = (COH & kCohAct) != 0, CW = (COH & kCohW) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const T *__restrict__ x = (const T *)a.x + (int64_t)b.z * a.a_bs;
   const T *__restrict__ w = (const T *)a.w + (int64_t)b.z * a.b_bs;
   T *__restrict__ y = (T *)a.y + (int64_t)b.z * a.y_bs;
@@ -198,11 +193,11 @@ __device__ __forceinline__ void igemm_body(const AR &a, const Blk &b, unsigned c
       if (VEC) {
         if (m < a.M && kbase < a.K) {
           if (!a.gather) {
-            v = ldg<CA, V>(x + (int64_t)m * a.lda + kbase);
+            v = ldg<V>(x + (int64_t)m * a.lda + kbase);
           } else {
             const int ih = ih0[i] + g_r, iw = iw0[i] + g_s;
             if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W)
-              v = ldg<CA, V>(ximg[i] + ((int64_t)ih * a.W + iw) * a.Cin + g_ci);
+              v = ldg<V>(ximg[i] + ((int64_t)ih * a.W + iw) * a.Cin + g_ci);
           }
         }
       } else {
@@ -212,12 +207,12 @@ __device__ __forceinline__ void igemm_body(const AR &a, const Blk &b, unsigned c
             const int k = kbase + e;
             if (k < a.K) {
               if (!a.gather) {
-                v[e] = ldg<CA, T>(x + (int64_t)m * a.lda + k);
+                v[e] = ldg<T>(x + (int64_t)m * a.lda + k);
               } else {
                 const int ci = k % a.Cin, rs = k / a.Cin;
                 const int ih = ih0[i] + rs / a.kw, iw = iw0[i] + rs % a.kw;
                 if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W)
-                  v[e] = ldg<CA, T>(ximg[i] + ((int64_t)ih * a.W + iw) * a.Cin + ci);
+                  v[e] = ldg<T>(ximg[i] + ((int64_t)ih * a.W + iw) * a.Cin + ci);
               }
             }
           }
@@ -232,11 +227,11 @@ __device__ __forceinline__ void igemm_body(const AR &a, const Blk &b, unsigned c
       if (!a.b_kmajor) {
         const int n = n0 + row0 + i * RSTEP;
         if (VEC) {
-          if (n < a.N && kbase < a.K) v = ldg<CW, V>(w + (int64_t)n * a.ldb + kbase);
+          if (n < a.N && kbase < a.K) v = ldg<V>(w + (int64_t)n * a.ldb + kbase);
         } else if (n < a.N) {
 #pragma unroll
           for (int e = 0; e < VE; ++e)
-            if (kbase + e < a.K) v[e] = ldg<CW, T>(w + (int64_t)n * a.ldb + kbase + e);
+            if (kbase + e < a.K) v[e] = ldg<T>(w + (int64_t)n * a.ldb + kbase + e);
         }
       } else {
         // operand stored [K][N]: a chunk runs along N at one K position
@@ -245,11 +240,11 @@ __device__ __forceinline__ void igemm_body(const AR &a, const Blk &b, unsigned c
         const int k = kt * BKE + krow, n = n0 + nch * VE;
         if (k < a.K) {
           if (VEC) {
-            if (n < a.N) v = ldg<CW, V>(w + (int64_t)k * a.ldb + n);
+            if (n < a.N) v = ldg<V>(w + (int64_t)k * a.ldb + n);
           } else {
 #pragma unroll
             for (int e = 0; e < VE; ++e)
-              if (n + e < a.N) v[e] = ldg<CW, T>(w + (int64_t)k * a.ldb + n + e);
+              if (n + e < a.N) v[e] = ldg<T>(w + (int64_t)k * a.ldb + n + e);
           }
         }
       }
@@ -328,7 +323,7 @@ __device__ __forceinline__ void igemm_body(const AR &a, const Blk &b, unsigned c
         float r = acc[i][j][e] * a.alpha;
         if (n + e < a.N) {
           if (a.bias) r += a.bias[n + e];
-          for (int q = 0; q < a.n_extra; ++q) r += (float)ldg<CA, T>((const T *)a.extra[q] + (int64_t)m * a.N + n + e);
+          for (int q = 0; q < a.n_extra; ++q) r += (float)ldg<T>((const T *)a.extra[q] + (int64_t)m * a.N + n + e);
         }
         if (a.relu) r = fmaxf(r, 0.f);
         v[e] = r;
@@ -373,188 +368,6 @@ __device__ __forceinline__ void kpos_advance(KPos &p, int delta, int Cin, int kw
 }
 
 // ---------------------------------------------------------------------------------
-// Throughput-oriented tiled implicit GEMM: BN x BM tile, four wavefronts, K stages of
-// 128 bytes per row, LDS double buffer with a 144-byte row pitch, and global loads
-// running DEPTH-1 stages ahead in DEPTH rotating register sets (at one workgroup per
-// compute unit the loop is bound by memory latency, so the bytes in flight set the
-// speed).  Vector loads only, second operand stored [N][K].
-// ---------------------------------------------------------------------------------
-template <typename T, int BN, int BM, int WN, int WM, int DEPTH, int COH, typename AR>
-__device__ __forceinline__ void igemm_pipe_body(const AR &a, const Blk &b, unsigned char *lds) {
-  typedef typename Vec16<T>::type V;
-  typedef typename Vec16<T>::quad Q;
-  constexpr int VE = Vec16<T>::N;
-  constexpr int KCH = 8;                   // 16-byte chunks per row and stage
-  constexpr int BKE = KCH * VE;
-  constexpr int NT = WN * WM * 64;
-  constexpr int ROWB = KCH * 16 + 16;
-  constexpr int CHW = BN * KCH / NT, CHX = BM * KCH / NT;
-  constexpr int FN = BN / WN / 16, FM = BM / WM / 16;
-  constexpr int RSTEP = NT / KCH;
-  static_assert((BN * KCH) % NT == 0 && (BM * KCH) % NT == 0, "tile/threads mismatch");
-  unsigned char (*smem)[(BN + BM) * ROWB] = (unsigned char (*)[(BN + BM) * ROWB])lds;   // [2][...]
-
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wn0 = (wave % WN) * (BN / WN), wm0 = (wave / WN) * (BM / WM);
-  int tile_x, tile_y;
-  xcd_tile(b, tile_x, tile_y);
-  const int m0 = tile_x * BM, n0 = tile_y * BN;
-  constexpr bool CA = (COH & kCohAct) != 0, CW = (COH & kCohW) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
-  const T *__restrict__ x = (const T *)a.x + (int64_t)b.z * a.a_bs;
-  const T *__restrict__ w = (const T *)a.w + (int64_t)b.z * a.b_bs;
-  T *__restrict__ y = (T *)a.y + (int64_t)b.z * a.y_bs;
-  const int kc = t % KCH, row0 = t / KCH;
-
-  // Per-thread rows, clamped into range: every global load below is unconditional and
-  // reads a valid address; out-of-range rows, K tails and padding taps are zeroed when
-  // the registers are written to LDS.  (A load guarded by a branch makes the compiler
-  // wait for it right inside the branch, which serialises the whole prefetch.)
-  int ih0[CHX], iw0[CHX];
-  const T *xrow[CHX], *ximg[CHX];
-  const T *wrow[CHW];
-  unsigned rowmask = 0;                       // bit i: pixel row i valid, bit 8+i: weight row i valid
-#pragma unroll
-  for (int i = 0; i < CHX; ++i) {
-    const int m = m0 + row0 + i * RSTEP;
-    const bool ok = m < a.M;
-    const int mm = ok ? m : 0;
-    rowmask |= (unsigned)ok << i;
-    xrow[i] = x + (int64_t)mm * a.lda;
-    const int img = mm / a.HoWo, pix = mm - img * a.HoWo;   // used only when gathering
-    const int oh = pix / a.Wo, ow = pix - oh * a.Wo;
-    ih0[i] = oh * a.sh - a.ph;
-    iw0[i] = ow * a.sw - a.pw;
-    ximg[i] = x + (int64_t)img * a.img_stride;
-  }
-#pragma unroll
-  for (int i = 0; i < CHW; ++i) {
-    const int n = n0 + row0 + i * RSTEP;
-    const bool ok = n < a.N;
-    rowmask |= (unsigned)ok << (8 + i);
-    wrow[i] = w + (int64_t)(ok ? n : 0) * a.ldb;
-  }
-  KPos pos = {0, 0, 0};
-  if (a.gather) {
-    const int k = kc * VE;
-    pos.ci = k % a.Cin;
-    const int rs = k / a.Cin;
-    pos.s = rs % a.kw;
-    pos.r = rs / a.kw;
-  }
-  const V vzero = {};
-
-  // Stages must be requested in increasing order.  Returns the validity mask of the set.
-  auto load_global = [&](int kt, V *wr, V *xr) -> unsigned {
-    const int kbase = kt * BKE + kc * VE;
-    const bool kok = kbase < a.K;
-    const int ks = kok ? kbase : 0;
-    unsigned mask = kok ? rowmask : 0u;
-    if (!a.gather) {
-#pragma unroll
-      for (int i = 0; i < CHX; ++i) xr[i] = ldg<CA, V>(xrow[i] + ks);
-    } else {
-#pragma unroll
-      for (int i = 0; i < CHX; ++i) {
-        const int ih = ih0[i] + pos.r, iw = iw0[i] + pos.s;
-        const bool inb = kok && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-        const int64_t off = inb ? ((int64_t)ih * a.W + iw) * a.Cin + pos.ci : 0;
-        if (!inb) mask &= ~(1u << i);
-        xr[i] = ldg<CA, V>(ximg[i] + off);
-      }
-      kpos_advance(pos, BKE, a.Cin, a.kw);
-    }
-#pragma unroll
-    for (int i = 0; i < CHW; ++i) wr[i] = ldg<CW, V>(wrow[i] + ks);
-    return mask;
-  };
-  auto store_lds = [&](int buf, const V *wr, const V *xr, unsigned mask) {
-    unsigned char *Wb = smem[buf];
-    unsigned char *Xb = Wb + BN * ROWB;
-#pragma unroll
-    for (int i = 0; i < CHX; ++i)
-      *(V *)(Xb + (row0 + i * RSTEP) * ROWB + kc * 16) = ((mask >> i) & 1u) ? xr[i] : vzero;
-#pragma unroll
-    for (int i = 0; i < CHW; ++i)
-      *(V *)(Wb + (row0 + i * RSTEP) * ROWB + kc * 16) = ((mask >> (8 + i)) & 1u) ? wr[i] : vzero;
-  };
-
-  floatx4 acc[FN][FM];
-#pragma unroll
-  for (int i = 0; i < FN; ++i)
-#pragma unroll
-    for (int j = 0; j < FM; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int buf) {
-    const unsigned char *Wb = smem[buf];
-    const unsigned char *Xb = Wb + BN * ROWB;
-#pragma unroll
-    for (int ks = 0; ks < KCH / 4; ++ks) {
-      V af[FN], bf[FM];
-#pragma unroll
-      for (int i = 0; i < FN; ++i)
-        af[i] = *(const V *)(Wb + (wn0 + i * 16 + (lane & 15)) * ROWB + ks * 64 + (lane >> 4) * 16);
-#pragma unroll
-      for (int j = 0; j < FM; ++j)
-        bf[j] = *(const V *)(Xb + (wm0 + j * 16 + (lane & 15)) * ROWB + ks * 64 + (lane >> 4) * 16);
-#pragma unroll
-      for (int i = 0; i < FN; ++i)
-#pragma unroll
-        for (int j = 0; j < FM; ++j) acc[i][j] = mma16<T>(af[i], bf[j], acc[i][j]);
-    }
-  };
-
-  // DEPTH register sets rotate through the stages: set j carries the stages congruent to
-  // j; a set is refilled right after its previous stage went to LDS, so every load has
-  // DEPTH-1 stage computations to land.  Stages past the end of K are masked to zero.
-  const int nst = (a.K + BKE - 1) / BKE;
-  V wS[DEPTH][CHW], xS[DEPTH][CHX];
-  unsigned mS[DEPTH];
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d) mS[d] = load_global(d, wS[d], xS[d]);
-  store_lds(0, wS[0], xS[0], mS[0]);
-  __syncthreads();
-#pragma nounroll
-  for (int s = 0; s < nst; s += DEPTH) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {          // LDS buffer d&1 holds stage s+d
-      mS[d] = load_global(s + d + DEPTH, wS[d], xS[d]);
-      compute(d & 1);
-      store_lds((d + 1) & 1, wS[(d + 1) % DEPTH], xS[(d + 1) % DEPTH], mS[(d + 1) % DEPTH]);
-      __syncthreads();
-    }
-  }
-
-#pragma unroll
-  for (int i = 0; i < FN; ++i) {
-    const int n = n0 + wn0 + i * 16 + (lane >> 4) * 4;
-#pragma unroll
-    for (int j = 0; j < FM; ++j) {
-      const int m = m0 + wm0 + j * 16 + (lane & 15);
-      if (m >= a.M || n >= a.N) continue;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float r = acc[i][j][e] * a.alpha;
-        if (n + e < a.N) {
-          if (a.bias) r += a.bias[n + e];
-          for (int q = 0; q < a.n_extra; ++q) r += (float)ldg<CA, T>((const T *)a.extra[q] + (int64_t)m * a.N + n + e);
-        }
-        if (a.relu) r = fmaxf(r, 0.f);
-        v[e] = r;
-      }
-      T *dst = y + (int64_t)m * a.ldy + n;
-      if (n + 3 < a.N && ((uintptr_t)dst & (4 * sizeof(T) - 1)) == 0) {
-        Q q4 = {(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
-        stg<CS, Q>(dst, q4);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n + e < a.N) stg<CS, T>(dst + e, (T)v[e]);
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------
 // Latency-oriented implicit GEMM for small problems (batch-1 convolutions, skinny
 // GEMMs): a workgroup owns a 32 x 32 output tile and its WAVES wavefronts split K
 // between them.  Every lane fetches its MFMA fragments straight from global memory
@@ -577,7 +390,7 @@ __device__ __forceinline__ void igemm_direct_body(const AR &a, const Blk &b, uns
   int tile_x, tile_y;
   xcd_tile(b, tile_x, tile_y);
   const int m0 = tile_x * (16 * NJ), n0 = tile_y * (16 * NI);
-  constexpr bool CA = (COH & kCohAct) != 0, CW = (COH & kCohW) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const T *__restrict__ x = (const T *)a.x + (int64_t)b.z * a.a_bs;
   const T *__restrict__ w = (const T *)a.w + (int64_t)b.z * a.b_bs;
   T *__restrict__ y = (T *)a.y + (int64_t)b.z * a.y_bs;
@@ -641,11 +454,11 @@ __device__ __forceinline__ void igemm_direct_body(const AR &a, const Blk &b, uns
     for (int q = 0; q < a.n_extra; ++q) {
       const T *ex = (const T *)a.extra[q] + (int64_t)m * a.N + n;
       if (full && ((uintptr_t)ex & (4 * sizeof(T) - 1)) == 0) {
-        const Q v = ldg<CA, Q>(ex);
+        const Q v = ldg<Q>(ex);
 #pragma unroll
         for (int e = 0; e < 4; ++e) badd[e] += (float)v[e];
       } else {
-        for (int e = 0; e < 4; ++e) if (n + e < a.N) badd[e] += (float)ldg<CA, T>(ex + e);
+        for (int e = 0; e < 4; ++e) if (n + e < a.N) badd[e] += (float)ldg<T>(ex + e);
       }
     }
 
@@ -665,17 +478,17 @@ __device__ __forceinline__ void igemm_direct_body(const AR &a, const Blk &b, uns
         kok[u][c] = k < a.K;
         const int ks = kok[u][c] ? k : 0;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) wa[u][i][c] = ldg<CW, V>(wrow[i] + ks);
+        for (int i = 0; i < NI; ++i) wa[u][i][c] = ldg<V>(wrow[i] + ks);
         if (!a.gather) {
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) xb[u][j][c] = ldg<CA, V>(xrow[j] + ks);
+          for (int j = 0; j < NJ; ++j) xb[u][j][c] = ldg<V>(xrow[j] + ks);
         } else {
 #pragma unroll
           for (int j = 0; j < NJ; ++j) {
             const int ih = ih0[j] + pc.r, iw = iw0[j] + pc.s;
             inb[u][j][c] = kok[u][c] && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
             const int64_t off = inb[u][j][c] ? ((int64_t)ih * a.W + iw) * a.Cin + pc.ci : 0;
-            xb[u][j][c] = ldg<CA, V>(ximg[j] + off);
+            xb[u][j][c] = ldg<V>(ximg[j] + off);
           }
           if (c == 0) kpos_advance(pc, VE, a.Cin, a.kw);
         }
@@ -740,401 +553,408 @@ __device__ __forceinline__ void igemm_direct_body(const AR &a, const Blk &b, uns
 }
 
 // ---------------------------------------------------------------------------------
-// Quad transposition.  The texture path serves a 16-byte-per-lane load at full rate only
-// when four adjacent lanes read 64 contiguous bytes; lanes that each touch a different
-// line are served one lane at a time (measured on gfx950: 14 against 43 bytes per clock
-// and compute unit).  An MFMA operand wants adjacent lanes on different rows.  So a lane
-// group of four loads four rows, 64 contiguous bytes of one row per instruction, and this
-// 4 x 4 exchange inside the group (two butterfly stages of cross-lane moves) hands every
-// lane the four pieces of its own row: afterwards register t of lane i holds what
-// register i of lane t held.  All cross-lane moves are unconditional; only the selects
-// depend on the lane.
+// Operand staging of the two LDS-fed contractions below.
+//
+// Both walk K in steps of 128 bytes per row and move operand rows from global memory
+// straight into workgroup memory (buffer_load_dwordx4 ... lds: no vector registers, no second
+// instruction for the LDS write, many loads in flight per wavefront).  One instruction of a
+// wavefront fills 1 KB: lane l writes 16 bytes at base + 16 * l, so it covers eight rows and
+// lane l holds slot l % 8 of row l / 8.  The destination is fixed by the hardware, the source
+// is free: a lane fetches the 16-byte chunk (slot ^ f(row)), which keeps eight adjacent lanes
+// on one 128-byte line of memory and spreads the fragment reads of the matrix instructions
+// (sixteen rows, one chunk each) over all banks.
+//
+// The buffer form checks every lane's offset against the operand's size and delivers zeros
+// past it: padding taps, chunks past the end of K and rows past the end of the operand are
+// given an offset no operand reaches (the host keeps operands below it) and cost no traffic.
+// Offsets are 32-bit; the K position of a GEMM-shaped operand is the scalar offset, so a
+// step takes no vector arithmetic at all, and a gathered row takes seven instructions.
 // ---------------------------------------------------------------------------------
-template <int CTRL> __device__ __forceinline__ uint32_t quad_move(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
-}
-template <int T> __device__ __forceinline__ int quad_broadcast(int v) {
-  return __builtin_amdgcn_mov_dpp(v, T * 0x55, 0xf, 0xf, true);
-}
-template <typename V> __device__ __forceinline__ void quad_transpose(V (&r)[4], bool odd, bool hi) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  static_assert(sizeof(V) == 16, "fragment size");
-  u32x4 u[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) u[t] = __builtin_bit_cast(u32x4, r[t]);
-#pragma unroll
-  for (int p = 0; p < 2; ++p)              // lane bit 0 <-> register bit 0
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const uint32_t a0 = u[2 * p][d], b0 = u[2 * p + 1][d];
-      const uint32_t pa = quad_move<0xB1>(a0), pb = quad_move<0xB1>(b0);   // lanes [1,0,3,2]
-      u[2 * p][d] = odd ? pb : a0;
-      u[2 * p + 1][d] = odd ? b0 : pa;
-    }
-#pragma unroll
-  for (int p = 0; p < 2; ++p)              // lane bit 1 <-> register bit 1
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const uint32_t a0 = u[p][d], b0 = u[p + 2][d];
-      const uint32_t pa = quad_move<0x4E>(a0), pb = quad_move<0x4E>(b0);   // lanes [2,3,0,1]
-      u[p][d] = hi ? pb : a0;
-      u[p + 2][d] = hi ? b0 : pa;
-    }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) r[t] = __builtin_bit_cast(V, u[t]);
-}
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// ---------------------------------------------------------------------------------
-// Latency-oriented implicit GEMM for small problems (batch-1 convolutions, skinny
-// GEMMs): a workgroup owns a 32 x 32 output tile and its WAVES wavefronts split K
-// between them in steps of 256 bytes per row.  Operands come straight from global
-// memory, no LDS and no barrier inside the K loop: in one load instruction a group of
-// four lanes reads 64 contiguous bytes of one row (see quad_transpose), the next step's
-// loads are in flight while the current one is transposed and multiplied.  Partial tiles
-// meet in LDS once, at the end, where 256 threads apply the epilogue and write 8/16-byte
-// pieces of output rows.
-// ---------------------------------------------------------------------------------
-template <typename T, int WAVES, int COH, int NI, int NJ, typename AR>
-__device__ __forceinline__ void igemm_quad_body(const AR &a, const Blk &b, unsigned char *lds) {
-  typedef typename Vec16<T>::type V;
+__device__ __forceinline__ i32x4 buffer_of(const void *base, uint32_t bytes) {
+  const uint64_t p = (uint64_t)(uintptr_t)base;
+  return i32x4{__builtin_amdgcn_readfirstlane((int)(uint32_t)p), __builtin_amdgcn_readfirstlane((int)((p >> 32) & 0xffffu)),
+               __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};    // raw buffer, 32-bit data format
+}
+// Volatile statements keep their order among each other; what reads or writes the destination
+// is kept apart from the load by the waits below, which clobber memory.
+__device__ __forceinline__ void lds_load16(i32x4 buf, uint32_t offset, uint32_t soffset, uint32_t lds_base) {
+  // m0 holds the wavefront's LDS address; one wait state between its write and the load.
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               : : "v"(offset), "s"(buf), "s"(soffset), "s"(lds_base) : "m0");
+}
+template <int N> __device__ __forceinline__ void wait_loads() {        // all but the N youngest vector loads
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_loads_and_meet() {   // ... then the workgroup's barrier
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const unsigned char *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)p;
+}
+// floor(n / d) with m = min(2^32 / d, 2^32 - 1): the product underestimates by at most one.
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t m) {
+  const uint32_t q = __umulhi(n, m);
+  return n - q * d >= d ? q + 1 : q;
+}
+// Bytes of one wavefront's ring in igemm_split_body: S steps, or its partial tile.
+constexpr int split_ring_bytes(int ni, int nj, int s) {
+  const int ring = s * (ni + nj) * 16 * 128, part = nj * 16 * (ni * 16 + 4) * 4;
+  return ring > part ? ring : part;
+}
+constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
+
+// LW / LX: rows of the two operands this lane fetches per K step (one load instruction each).
+// Steps must be requested in increasing order from kt0 on.
+template <typename T, int LW, int LX> struct Stager {
+  static constexpr int VE = Vec16<T>::N, BKE = 8 * VE, ES = (int)sizeof(T);
+  i32x4 wbuf, xbuf;
+  uint32_t wo[LW], xo[LX];                // byte offset of this lane's chunk in K step 0 (gather: of tap 0, 0)
+  int ih0[LX], iw0[LX];                   // gather: input position of tap 0, 0
+  int kw0, kx0;                           // element offset of this lane's chunk inside a K step
+  int ci, s, r;                           // gather: channel and tap of this lane's chunk in the next step
+  int dci, ds, dr;                        // ... and how a step moves them
+  int K, gather, H, W, Cin, kh, kw;       // the operator's, read once
+
+  // Row i of an operand is group first + i * step of eight rows, row lane / 8 inside it.
+  template <typename AR>
+  __device__ __forceinline__ void init(const AR &a, const T *w, const T *x, int n0, int m0, int kt0, int first, int step,
+                                       int lane, int wslot, int xslot) {
+    const int l8 = lane >> 3;
+    K = a.K; gather = a.gather; H = a.H; W = a.W; Cin = a.Cin; kh = a.kh; kw = a.kw;
+    kw0 = wslot * VE;
+    kx0 = xslot * VE;
+    wbuf = buffer_of(w, a.w_bytes);
+    xbuf = buffer_of(x, a.x_bytes);
+#pragma unroll
+    for (int i = 0; i < LW; ++i) {
+      const int n = n0 + (first + i * step) * 8 + l8;
+      wo[i] = n < a.N ? ((uint32_t)n * (uint32_t)a.ldb + (uint32_t)kw0) * ES : kOperandMaxBytes;
+    }
+    if (!a.gather) {
+#pragma unroll
+      for (int i = 0; i < LX; ++i) {
+        const int m = m0 + (first + i * step) * 8 + l8;
+        xo[i] = m < a.M ? ((uint32_t)m * (uint32_t)a.lda + (uint32_t)kx0) * ES : kOperandMaxBytes;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < LX; ++i) {
+        const int m = m0 + (first + i * step) * 8 + l8;
+        const int img = (int)fast_div(m, a.HoWo, a.div_HoWo), pix = m - img * a.HoWo;
+        const int oh = (int)fast_div(pix, a.Wo, a.div_Wo), ow = pix - oh * a.Wo;
+        ih0[i] = m < a.M ? oh * a.sh - a.ph : -(1 << 28);          // no tap of a row past the end is inside
+        iw0[i] = ow * a.sw - a.pw;
+        xo[i] = ((uint32_t)img * (uint32_t)a.img_stride + (uint32_t)(((oh * a.sh - a.ph) * a.W + iw0[i]) * a.Cin)) * ES;
+      }
+      const int k = kt0 * BKE + kx0;
+      const int rs = (int)fast_div(k, a.Cin, a.div_Cin);
+      ci = k - rs * a.Cin;
+      r = (int)fast_div(rs, a.kw, a.div_kw);
+      s = rs - r * a.kw;
+      const int drs = (int)fast_div(BKE, a.Cin, a.div_Cin);
+      dci = BKE - drs * a.Cin;
+      dr = (int)fast_div(drs, a.kw, a.div_kw);
+      ds = drs - dr * a.kw;
+    }
+  }
+  // Requests K step kt: operand rows to wl + i * pitch and xl + i * pitch.
+  __device__ __forceinline__ void issue(int kt, uint32_t wl, uint32_t xl, uint32_t pitch) {
+    const uint32_t kb = (uint32_t)kt * 128u;
+    const bool wok = kt * BKE + kw0 < K;
+#pragma unroll
+    for (int i = 0; i < LW; ++i) lds_load16(wbuf, wok ? wo[i] : kOperandMaxBytes, kb, wl + i * pitch);
+    if (gather) {
+      const uint32_t tap = (__umul24(__umul24(r, W) + s, Cin) + ci) * ES;
+      const bool ok = r < kh;
+#pragma unroll
+      for (int i = 0; i < LX; ++i) {
+        const bool in = ok && (unsigned)(ih0[i] + r) < (unsigned)H && (unsigned)(iw0[i] + s) < (unsigned)W;
+        lds_load16(xbuf, in ? xo[i] + tap : kOperandMaxBytes, 0, xl + i * pitch);
+      }
+      ci += dci; s += ds; r += dr;
+      const bool wrap = ci >= Cin;
+      ci -= wrap ? Cin : 0;
+      s += wrap ? 1 : 0;
+      const bool row = s >= kw;
+      s -= row ? kw : 0;
+      r += row ? 1 : 0;
+    } else {
+      const bool xok = kt * BKE + kx0 < K;
+#pragma unroll
+      for (int i = 0; i < LX; ++i) lds_load16(xbuf, xok ? xo[i] : kOperandMaxBytes, kb, xl + i * pitch);
+    }
+  }
+};
+
+// Epilogue of one run of four output channels: scale, bias, residual inputs, ReLU.  Global
+// memory takes vectors at element alignment.
+template <typename T> struct Run4;
+template <> struct Run4<half_t> { typedef _Float16 type __attribute__((ext_vector_type(4), aligned(2))); };
+template <> struct Run4<float> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+
+template <typename T, typename AR>
+__device__ __forceinline__ floatx4 finish4(const AR &a, floatx4 v, floatx4 bias, int m, int n) {
+  typedef typename Run4<T>::type R;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = v[e] * a.alpha + bias[e];
+  for (int q = 0; q < a.n_extra; ++q) {
+    const T *ex = (const T *)a.extra[q] + (int64_t)m * a.N + n;
+    if (n + 3 < a.N) {
+      const R r = *(const R *)ex;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += (float)r[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) if (n + e < a.N) v[e] += (float)ex[e];
+    }
+  }
+  if (a.relu) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+  }
+  return v;
+}
+// Four biases from channel n on; zeros past the last channel and for an operator without bias
+// (no branch: a load behind one is waited for at the end of the branch).
+struct BiasRow {
+  __amdgpu_buffer_rsrc_t buf;
+  template <typename AR> __device__ __forceinline__ BiasRow(const AR &a)
+      : buf(__builtin_amdgcn_make_buffer_rsrc((void *)a.bias, 0, a.bias ? a.N * 4 : 0, 0x00020000)) {}
+  __device__ __forceinline__ floatx4 at(int n) const {
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(buf, n * 4, 0, 0));
+  }
+};
+template <typename T, bool CS, typename AR>
+__device__ __forceinline__ void store4(const AR &a, T *dst, floatx4 v, int n) {
   typedef typename Vec16<T>::quad Q;
-  constexpr int VE = Vec16<T>::N;
-  constexpr int DS = 16 * VE;              // K elements per step: 4 lane groups x 4 pieces of 16 bytes
-  constexpr int PITCH = 36;                // floats per pixel row of a partial tile in LDS
-  float (*part)[32][PITCH] = (float (*)[32][PITCH])lds;                                // [WAVES][32][PITCH]
+  typedef typename Run4<T>::type R;
+  const bool full = n + 3 < a.N && (!CS || ((uintptr_t)dst & (4 * sizeof(T) - 1)) == 0);   // coherent stores need alignment
+  if (full) {
+    if constexpr (CS) stg<CS, Q>(dst, Q{(T)v[0], (T)v[1], (T)v[2], (T)v[3]});
+    else *(R *)dst = R{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < a.N) stg<CS, T>(dst + e, (T)v[e]);
+  }
+}
 
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int grp = lane >> 4, r16 = lane & 15, qd = (lane >> 2) & 3, pc = lane & 3;
-  const bool odd = (lane & 1) != 0, hi = (lane & 2) != 0;
+// ---------------------------------------------------------------------------------
+// Throughput-oriented contraction: BN columns x BM rows per workgroup of WN x WM
+// wavefronts, a ring of S stages in workgroup memory, S - 1 stages requested ahead, one
+// barrier per stage.
+// What bounds it: per 128-byte stage of a 128 x 128 tile the matrix cores need 515 clocks,
+// the fragment reads of four 64 x 64 wavefronts 512 clocks of LDS bandwidth and the loads
+// 512 clocks at 64 bytes per clock; one workgroup alone does these in turn (1,500 clocks
+// measured), two per compute unit overlap them.  Hence two stages (64 KB) and two workgroups
+// per CU for the large tile, smaller tiles where there are too few large ones to give every
+// CU two (see choose_tiles in plan.cpp).  Measured, fp16, eight 384 x 2496 x 3904 products in
+// one launch: 960 TFLOP/s with 128 x 128 tiles, 731 with 64 x 128, 638 with 64 x 64; one
+// 512 x 4096 x 4096 product 25.0 us (64 x 64, 687 TFLOP/s; the register-staged kernels that
+// stood here: 42.8 us); convolution 3 x 3, 32 -> 64 channels, 16 images of 147 x 147: 152 -> 39 us.
+// The rows of the weight operand are dealt to the fragments so that a lane's accumulators
+// are 4 * FN consecutive channels of one row (wide stores, whole lines per wavefront).
+// ---------------------------------------------------------------------------------
+template <typename T, int BN, int BM, int WN, int WM, int S, int COH, typename AR>
+__device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsigned char *lds) {
+  typedef typename Vec16<T>::type V;
+  constexpr int NW = WN * WM, STAGE = (BN + BM) * 128;
+  constexpr int FN = BN / WN / 16, FM = BM / WM / 16;
+  constexpr int LW = BN / 8 / NW, LX = BM / 8 / NW, L = LW + LX;
+  constexpr int FB = 2 + log2_of(FN);      // row bit that tells apart rows whose low two bits repeat in a fragment
+  static_assert(NW == 4 && BN % 32 == 0 && BM % 32 == 0 && (FN == 2 || FN == 4), "tile / wavefront mismatch");
+  constexpr bool CS = COH != 0;
+
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int grp = lane >> 4, r16 = lane & 15;
+  const int wn0 = (wave % WN) * (BN / WN), wm0 = (wave / WN) * (BM / WM);
   int tile_x, tile_y;
   xcd_tile(b, tile_x, tile_y);
-  const int m0 = tile_x * (16 * NJ), n0 = tile_y * (16 * NI);
-  constexpr bool CA = (COH & kCohAct) != 0, CW = (COH & kCohW) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  const int m0 = tile_x * BM, n0 = tile_y * BN;
   const T *__restrict__ x = (const T *)a.x + (int64_t)b.z * a.a_bs;
   const T *__restrict__ w = (const T *)a.w + (int64_t)b.z * a.b_bs;
   T *__restrict__ y = (T *)a.y + (int64_t)b.z * a.y_bs;
 
-  const int nds = (a.K + DS - 1) / DS;
-  const int per_wave = (nds + WAVES - 1) / WAVES;
-  const int ds_begin = wave * per_wave;
-  const int ds_end = min(nds, ds_begin + per_wave);
-  // Only the last step of K can be partial; it runs apart from the pipelined steps.
-  const bool owns_tail = a.K % DS != 0 && ds_begin < nds && ds_end == nds;
-  const int main_end = owns_tail ? ds_end - 1 : ds_end;
-  const int kc = (grp * 4 + pc) * VE;      // this lane's 16-byte piece inside a step
+  // Slot of chunk c of a row: c ^ fw(row) for the weights, c ^ (row & 7) for the other operand.
+  auto fw = [](int row) { return (row & 3) | (((row >> FB) & 1) << 2); };
+  Stager<T, LW, LX> st;
+  st.init(a, w, x, n0, m0, 0, wave, NW, lane, (lane & 7) ^ fw(wave * 8 + (lane >> 3)), (lane & 7) ^ (lane >> 3));
+  const uint32_t base = lds_address(lds) + wave * 1024;
+  auto issue = [&](int kt, int slot) {
+    st.issue(kt, base + slot * STAGE, base + slot * STAGE + BN * 128, NW * 1024);
+  };
 
-  // Register t of block i loads row 16*i + 4*qd + t (clamped into range; results of
-  // clamped rows are never stored).  Offsets are elements from the operand's base and fit
-  // 32 bits (the host selects this kernel only for operands below 2^31 elements).
-  int woff[NI][4], xoff[NJ][4], ihq[NJ][4], iwq[NJ][4];
+  floatx4 acc[FN][FM];
 #pragma unroll
-  for (int i = 0; i < NI; ++i)
+  for (int i = 0; i < FN; ++i)
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) woff[i][tt] = min(n0 + i * 16 + qd * 4 + tt, a.N - 1) * (int)a.ldb + kc;
+    for (int j = 0; j < FM; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int nst = (a.K + Stager<T, LW, LX>::BKE - 1) / Stager<T, LW, LX>::BKE;
 #pragma unroll
-  for (int j = 0; j < NJ; ++j)
+  for (int s = 0; s < S - 1; ++s)
+    if (s < nst) issue(s, s);
+  const int nrun = n0 + wn0 + grp * 4 * FN;            // this lane's first output channel
+  const BiasRow bias(a);
+  floatx4 bv[FN];
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) xoff[j][tt] = min(m0 + j * 16 + qd * 4 + tt, a.M - 1) * (int)a.lda + kc;
-  KPos pos = {0, 0, 0};
-  if (a.gather) {
-    // Pixel geometry of this lane's own row, then of the group's four rows by broadcast.
+  for (int i = 0; i < FN; ++i) bv[i] = bias.at(nrun + i * 4);
+
+  const int wrow = wn0 + (r16 >> 2) * (4 * FN) + (r16 & 3);
+  int slot = 0, ahead = S - 1;
+#pragma nounroll
+  for (int kt = 0; kt < nst; ++kt) {
+    // Stage kt has arrived once at most the S - 2 younger ones are in flight; behind the
+    // barrier everybody's part of it has, and nobody reads the slot that is refilled next.
+    if (kt + S - 2 < nst) wait_loads_and_meet<(S - 2) * L>();
+    else wait_loads_and_meet<0>();
+    if (kt + S - 1 < nst) issue(kt + S - 1, ahead);
+    const unsigned char *Wb = lds + slot * STAGE, *Xb = Wb + BN * 128;
+    V af[2][FN], bf[2][FM];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int m = min(m0 + j * 16 + r16, a.M - 1);
-      const int img = m / a.HoWo, pix = m - img * a.HoWo;
-      const int oh = pix / a.Wo, ow = pix - oh * a.Wo;
-      const int ih0 = oh * a.sh - a.ph, iw0 = ow * a.sw - a.pw, im0 = img * (int)a.img_stride;
-      ihq[j][0] = quad_broadcast<0>(ih0); ihq[j][1] = quad_broadcast<1>(ih0);
-      ihq[j][2] = quad_broadcast<2>(ih0); ihq[j][3] = quad_broadcast<3>(ih0);
-      iwq[j][0] = quad_broadcast<0>(iw0); iwq[j][1] = quad_broadcast<1>(iw0);
-      iwq[j][2] = quad_broadcast<2>(iw0); iwq[j][3] = quad_broadcast<3>(iw0);
-      xoff[j][0] = quad_broadcast<0>(im0); xoff[j][1] = quad_broadcast<1>(im0);
-      xoff[j][2] = quad_broadcast<2>(im0); xoff[j][3] = quad_broadcast<3>(im0);
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int i = 0; i < FN; ++i) {
+        const int row = wrow + i * 4;
+        af[ks][i] = *(const V *)(Wb + row * 128 + (((ks * 4 + grp) ^ fw(row)) * 16));
+      }
+#pragma unroll
+      for (int j = 0; j < FM; ++j) {
+        const int row = wm0 + j * 16 + r16;
+        bf[ks][j] = *(const V *)(Xb + row * 128 + (((ks * 4 + grp) ^ (row & 7)) * 16));
+      }
     }
-    if (ds_begin < ds_end) {
-      const int k = ds_begin * DS + kc;
-      pos.ci = k % a.Cin;
-      const int rs = k / a.Cin;
-      pos.s = rs % a.kw;
-      pos.r = rs / a.kw;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) mma_block<T>(af[ks], bf[ks], acc);
+    slot = slot == S - 1 ? 0 : slot + 1;
+    ahead = ahead == S - 1 ? 0 : ahead + 1;
+  }
+
+  typedef V VU __attribute__((aligned(sizeof(T))));
+#pragma unroll
+  for (int j = 0; j < FM; ++j) {
+    const int m = m0 + wm0 + j * 16 + r16;
+    if (m >= a.M) continue;
+    T *dst = y + (int64_t)m * a.ldy + nrun;
+#pragma unroll
+    for (int i = 0; i < FN; i += VecRun<T>::N) {
+      const int n = nrun + i * 4;
+      if (n >= a.N) break;
+      if constexpr (VecRun<T>::N == 2) {               // eight halves: one 16-byte store
+        const floatx4 lo = finish4<T>(a, acc[i][j], bv[i], m, n);
+        const floatx4 hi = finish4<T>(a, acc[i + 1][j], bv[i + 1], m, n + 4);
+        if (n + 7 < a.N) {
+          V o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { o[e] = (T)lo[e]; o[4 + e] = (T)hi[e]; }
+          if constexpr (CS) stg<CS, V>(dst + i * 4, o);
+          else *(VU *)(dst + i * 4) = o;
+        } else {
+          store4<T, CS>(a, dst + i * 4, lo, n);
+          store4<T, CS>(a, dst + i * 4 + 4, hi, n + 4);
+        }
+      } else {
+        store4<T, CS>(a, dst + i * 4, finish4<T>(a, acc[i][j], bv[i], m, n), n);
+      }
     }
   }
+}
+
+// ---------------------------------------------------------------------------------
+// Latency-oriented contraction (batch-1 convolutions, skinny GEMMs): one 16 NI columns x
+// 16 NJ rows tile per workgroup, K shared out between its four wavefronts in whole 128-byte
+// steps.  Every wavefront stages its own steps in its own ring of S slots and waits for its
+// own loads only: no barrier until the partial tiles meet, each in its wavefront's ring.
+// What bounds it: with few tiles the load rate of one compute unit, which is why a small
+// problem takes small tiles on many CUs; with many, the bytes (a 32 x 32 tile moves twice
+// the operand bytes per multiply-add of a 64 x 64 one).  Measured, isolated fp16 products
+// (us; register-staged kernels that stood here before -> now, with the tile taken):
+// 128 x 768 x 3072 7.5 -> 5.3 (32 x 32), 512 x 768 x 3072 13.8 -> 7.9 (64 x 32),
+// 256 x 2048 x 2048 13.5 -> 6.8 (64 x 32), 64 x 4096 x 4096 13.6 -> 8.2 (32 x 32),
+// 256 x 4096 x 4096 30.3 -> 15.8 (64 x 64).
+// ---------------------------------------------------------------------------------
+template <typename T, int NI, int NJ, int S, int COH, typename AR>
+__device__ __forceinline__ void igemm_split_body(const AR &a, const Blk &b, unsigned char *lds) {
+  typedef typename Vec16<T>::type V;
+  constexpr int WAVES = 4, BN = 16 * NI, BM = 16 * NJ, STEP = (BN + BM) * 128;
+  constexpr int PITCH = BN + 4;            // floats per row of a partial tile
+  constexpr int RING = split_ring_bytes(NI, NJ, S);
+  constexpr int LW = BN / 8, LX = BM / 8, L = LW + LX;
+  constexpr bool CS = COH != 0;
+
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int grp = lane >> 4, r16 = lane & 15;
+  int tile_x, tile_y;
+  xcd_tile(b, tile_x, tile_y);
+  const int m0 = tile_x * BM, n0 = tile_y * BN;
+  const T *__restrict__ x = (const T *)a.x + (int64_t)b.z * a.a_bs;
+  const T *__restrict__ w = (const T *)a.w + (int64_t)b.z * a.b_bs;
+  T *__restrict__ y = (T *)a.y + (int64_t)b.z * a.y_bs;
+
+  const int nst = (a.K + Stager<T, LW, LX>::BKE - 1) / Stager<T, LW, LX>::BKE;
+  const int k_begin = nst * wave / WAVES, k_end = nst * (wave + 1) / WAVES;
+  Stager<T, LW, LX> st;
+  const int cslot = (lane & 7) ^ (lane >> 3);
+  st.init(a, w, x, n0, m0, k_begin, 0, 1, lane, cslot, cslot);
+  unsigned char *ring = lds + wave * RING;
+  const uint32_t base = lds_address(ring);
+  auto issue = [&](int kt, int slot) { st.issue(kt, base + slot * STEP, base + slot * STEP + BN * 128, 1024); };
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+    if (k_begin + s < k_end) issue(k_begin + s, s);
 
   floatx4 acc[NI][NJ];
 #pragma unroll
   for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const V vzero = {};
-
-  // Epilogue operands of this thread's output piece (bias, residual inputs) are requested
-  // before the K walk, so that their latency is hidden behind it.
-  constexpr int PG = 4 * NI;               // four-channel pieces per tile row
-  const int pm = t / PG, pn = (t % PG) * 4;
-  const int m = m0 + pm, n = n0 + pn;
-  const bool full = n + 3 < a.N;           // whole group of four channels inside the tensor
-  const bool live = t < 16 * NJ * PG && m < a.M && n < a.N;
-  floatx4 badd = {0.f, 0.f, 0.f, 0.f};
-  if (live && a.bias) {
-    if (full && ((uintptr_t)(a.bias + n) & 15) == 0) badd = *(const floatx4 *)(a.bias + n);
-    else
-      for (int e = 0; e < 4; ++e) if (n + e < a.N) badd[e] = a.bias[n + e];
-  }
-  if (live)
-    for (int q = 0; q < a.n_extra; ++q) {
-      const T *ex = (const T *)a.extra[q] + (int64_t)m * a.N + n;
-      if (full && ((uintptr_t)ex & (4 * sizeof(T) - 1)) == 0) {
-        const Q v = ldg<CA, Q>(ex);
+  // Bias of this thread's output pieces, requested before the K walk.
+  constexpr int PG = 4 * NI, PIECES = (BM * PG + 255) / 256;   // four-channel pieces per row, per thread
+  const BiasRow bias(a);
+  floatx4 bv[PIECES];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) badd[e] += (float)v[e];
-      } else {
-        for (int e = 0; e < 4; ++e) if (n + e < a.N) badd[e] += (float)ldg<CA, T>(ex + e);
-      }
-    }
-
-  struct Frag { V w[NI][4], x[NJ][4]; };
-  // Requests one step.  In the partial step a lane whose piece lies past the end of K
-  // requests nothing and contributes zeros; padding taps of a convolution read a valid
-  // address and are zeroed after arrival.
-  auto issue = [&](auto tail_tag, int ds, Frag &f) {
-    constexpr bool TAIL = decltype(tail_tag)::value;
-    const int kb = ds * DS;
-    const bool kok = !TAIL || kb + kc < a.K;
-    unsigned inb = 0xffu;
-    int xo[NJ][4];
-    if (a.gather) {
-      inb = 0;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-          const int ih = ihq[j][tt] + pos.r, iw = iwq[j][tt] + pos.s;
-          const bool in = kok && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-          inb |= in ? 1u << (j * 4 + tt) : 0u;
-          xo[j][tt] = in ? xoff[j][tt] + (ih * a.W + iw) * a.Cin + pos.ci : 0;
-        }
-      kpos_advance(pos, DS, a.Cin, a.kw);
-    } else {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) xo[j][tt] = xoff[j][tt] + kb;
-    }
-    if (kok) {
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) f.w[i][tt] = ldg<CW, V>(w + woff[i][tt] + kb);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) f.x[j][tt] = ldg<CA, V>(x + xo[j][tt]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) f.w[i][tt] = vzero;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) f.x[j][tt] = vzero;
-    }
-    return inb;
-  };
-  auto compute = [&](Frag &f, unsigned inb) {
-    if (a.gather) {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) f.x[j][tt] = ((inb >> (j * 4 + tt)) & 1u) ? f.x[j][tt] : vzero;
-    }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) quad_transpose(f.w[i], odd, hi);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) quad_transpose(f.x[j], odd, hi);
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = mma16<T>(f.w[i][tt], f.x[j][tt], acc[i][j]);
-  };
-  if (ds_begin < main_end) {
-    // Two register sets: the loads of step ds+1 are requested before step ds is
-    // transposed and multiplied.  Inside the loop the request is unconditional (after a
-    // conditional one the compiler waits for everything in flight), and the empty
-    // statement pins the order: nothing else keeps a plain load from sinking to its use.
-    Frag cur, nxt;
-    unsigned inb_cur = issue(std::false_type{}, ds_begin, cur), inb_nxt;
+  for (int p = 0; p < PIECES; ++p) bv[p] = bias.at(n0 + ((t + p * 256) % PG) * 4);
+  int slot = 0;
 #pragma nounroll
-    for (int ds = ds_begin + 1; ds < main_end; ++ds) {
-      inb_nxt = issue(std::false_type{}, ds, nxt);
-      asm volatile("" ::: "memory");
-      compute(cur, inb_cur);
-      cur = nxt;
-      inb_cur = inb_nxt;
+  for (int kt = k_begin; kt < k_end; ++kt) {
+    if (kt + S - 1 < k_end) wait_loads<(S - 1) * L>();
+    else wait_loads<0>();
+    const unsigned char *Wb = ring + slot * STEP, *Xb = Wb + BN * 128;
+    V af[2][NI], bf[2][NJ];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int c = ((ks * 4 + grp) ^ (r16 & 7)) * 16;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) af[ks][i] = *(const V *)(Wb + (i * 16 + r16) * 128 + c);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) bf[ks][j] = *(const V *)(Xb + (j * 16 + r16) * 128 + c);
     }
-    compute(cur, inb_cur);
-  }
-  if (owns_tail) {
-    Frag f;
-    const unsigned inb = issue(std::true_type{}, main_end, f);
-    compute(f, inb);
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");     // the slot has been read: it may be refilled
+    if (kt + S < k_end) issue(kt + S, slot);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) mma_block<T>(af[ks], bf[ks], acc);
+    slot = slot == S - 1 ? 0 : slot + 1;
   }
 
-  // ---- meet in LDS: lane holds channels n = i*16 + grp*4 + e of pixel m = j*16 + r16
+  // ---- partial tiles meet: lane holds channels n = i*16 + grp*4 + e of row m = j*16 + r16
+  float *part = (float *)ring;
 #pragma unroll
   for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) *(floatx4 *)&part[wave][j * 16 + r16][i * 16 + grp * 4] = acc[i][j];
+    for (int j = 0; j < NJ; ++j) *(floatx4 *)(part + (j * 16 + r16) * PITCH + i * 16 + grp * 4) = acc[i][j];
   __syncthreads();
-  if (t < 16 * NJ * PG) {
-    floatx4 sum = *(const floatx4 *)&part[0][pm][pn];
 #pragma unroll
-    for (int q = 1; q < WAVES; ++q) sum += *(const floatx4 *)&part[q][pm][pn];
-    if (live) {
-      float v[4];
+  for (int p = 0; p < PIECES; ++p) {
+    const int idx = t + p * 256;
+    const int pm = idx / PG, pn = (idx % PG) * 4;
+    const int m = m0 + pm, n = n0 + pn;
+    if (idx >= BM * PG || m >= a.M || n >= a.N) continue;
+    const unsigned char *at = lds + (pm * PITCH + pn) * 4;
+    floatx4 sum = *(const floatx4 *)at;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float r = sum[e] * a.alpha + badd[e];
-        v[e] = a.relu ? fmaxf(r, 0.f) : r;
-      }
-      T *dst = y + (int64_t)m * a.ldy + n;
-      if (full && ((uintptr_t)dst & (4 * sizeof(T) - 1)) == 0) {
-        Q q4 = {(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
-        stg<CS, Q>(dst, q4);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n + e < a.N) stg<CS, T>(dst + e, (T)v[e]);
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------
-// 64 x 64-tile form of the quad-coalesced contraction, for GEMM-shaped operands (no
-// im2col gather) with enough rows to fill such tiles: every wavefront of the workgroup
-// multiplies the whole tile over its share of K, so each 16-byte piece a lane loads feeds
-// four MFMAs instead of two and the loads and exchanges per multiply-add halve.  The
-// fragments of one step take 128 registers, the accumulators 64: one register set, no
-// prefetch across steps (two four-wavefront workgroups per CU overlap instead; one
-// eight-wavefront workgroup per CU was slower on every shape measured), row offsets
-// recomputed per load.  Partial tiles meet in LDS; each thread finishes four 4-channel pieces.
-// ---------------------------------------------------------------------------------
-template <typename T, int WAVES, int COH, typename AR>
-__device__ __forceinline__ void igemm_quad64_body(const AR &a, const Blk &b, unsigned char *lds) {
-  typedef typename Vec16<T>::type V;
-  typedef typename Vec16<T>::quad Q;
-  constexpr int VE = Vec16<T>::N;
-  constexpr int DS = 16 * VE;              // K elements per step
-  constexpr int PITCH = 68;                // floats per row of a partial tile in LDS
-  float (*part)[64][PITCH] = (float (*)[64][PITCH])lds;                                // [WAVES][64][PITCH]
-
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int grp = lane >> 4, r16 = lane & 15, qd = (lane >> 2) & 3, pc = lane & 3;
-  const bool odd = (lane & 1) != 0, hi = (lane & 2) != 0;
-  int tile_x, tile_y;
-  xcd_tile(b, tile_x, tile_y);
-  const int m0 = tile_x * 64, n0 = tile_y * 64;
-  constexpr bool CA = (COH & kCohAct) != 0, CW = (COH & kCohW) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
-  const T *__restrict__ x = (const T *)a.x + (int64_t)b.z * a.a_bs;
-  const T *__restrict__ w = (const T *)a.w + (int64_t)b.z * a.b_bs;
-  T *__restrict__ y = (T *)a.y + (int64_t)b.z * a.y_bs;
-
-  const int nds = (a.K + DS - 1) / DS;
-  const int per_wave = (nds + WAVES - 1) / WAVES;
-  const int ds_begin = wave * per_wave;
-  const int ds_end = min(nds, ds_begin + per_wave);
-  const bool owns_tail = a.K % DS != 0 && ds_begin < nds && ds_end == nds;
-  const int main_end = owns_tail ? ds_end - 1 : ds_end;
-  const int kc = (grp * 4 + pc) * VE;      // this lane's 16-byte piece inside a step
-  const int lda = (int)a.lda, ldb = (int)a.ldb;
-  const int nq = n0 + qd * 4, mq = m0 + qd * 4;
-
-  floatx4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const V vzero = {};
-
-  struct Frag { V w[4][4], x[4][4]; };
-  // Register tt of block i holds row 16*i + 4*qd + tt (clamped into range; results of
-  // clamped rows are never stored), offsets in elements (below 2^31 by the host's choice).
-  auto step = [&](auto tail_tag, int ds) {
-    constexpr bool TAIL = decltype(tail_tag)::value;
-    const int kb = ds * DS + kc;
-    const bool kok = !TAIL || kb < a.K;
-    Frag f;
-    if (kok) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) f.w[i][tt] = ldg<CW, V>(w + (min(nq + i * 16 + tt, a.N - 1) * ldb + kb));
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) f.x[j][tt] = ldg<CA, V>(x + (min(mq + j * 16 + tt, a.M - 1) * lda + kb));
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) { f.w[i][tt] = vzero; f.x[i][tt] = vzero; }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      quad_transpose(f.w[i], odd, hi);
-      quad_transpose(f.x[i], odd, hi);
-    }
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mma16<T>(f.w[i][tt], f.x[j][tt], acc[i][j]);
-  };
-#pragma nounroll
-  for (int ds = ds_begin; ds < main_end; ++ds) step(std::false_type{}, ds);
-  if (owns_tail) step(std::true_type{}, main_end);
-
-  // ---- meet in LDS: lane holds channels n = i*16 + grp*4 + e of row m = j*16 + r16
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) *(floatx4 *)&part[wave][j * 16 + r16][i * 16 + grp * 4] = acc[i][j];
-  __syncthreads();
-  if (t < 256) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const int idx = t + p * 256;
-      const int pm = idx >> 4, pn = (idx & 15) * 4;
-      const int m = m0 + pm, n = n0 + pn;
-      if (m >= a.M || n >= a.N) continue;
-      const bool full = n + 3 < a.N;
-      floatx4 sum = *(const floatx4 *)&part[0][pm][pn];
-#pragma unroll
-      for (int q = 1; q < WAVES; ++q) sum += *(const floatx4 *)&part[q][pm][pn];
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float r = sum[e] * a.alpha;
-        if (n + e < a.N) {
-          if (a.bias) r += a.bias[n + e];
-          for (int q = 0; q < a.n_extra; ++q) r += (float)ldg<CA, T>((const T *)a.extra[q] + (int64_t)m * a.N + n + e);
-        }
-        v[e] = a.relu ? fmaxf(r, 0.f) : r;
-      }
-      T *dst = y + (int64_t)m * a.ldy + n;
-      if (full && ((uintptr_t)dst & (4 * sizeof(T) - 1)) == 0) {
-        Q q4 = {(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
-        stg<CS, Q>(dst, q4);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n + e < a.N) stg<CS, T>(dst + e, (T)v[e]);
-      }
-    }
+    for (int q = 1; q < WAVES; ++q) sum += *(const floatx4 *)(at + q * RING);
+    store4<T, CS>(a, y + (int64_t)m * a.ldy + n, finish4<T>(a, sum, bv[p], m, n), n);
   }
 }
 
@@ -1147,16 +967,16 @@ __device__ __forceinline__ void gemv_body(const AR &a, const Blk &b, unsigned ch
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = b.x * 4 + wave;
   if (n >= a.N) return;
-  constexpr bool CA = (COH & kCohAct) != 0, CW = (COH & kCohW) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const T *__restrict__ x = (const T *)a.x;
   const T *__restrict__ wr = (const T *)a.w + (int64_t)n * a.ldb;
   float acc[kGemvMaxM] = {0.f, 0.f, 0.f, 0.f};
   for (int k0 = lane * VE; k0 < a.K; k0 += 64 * VE) {
-    const V wv = ldg<CW, V>(wr + k0);
+    const V wv = ldg<V>(wr + k0);
 #pragma unroll
     for (int m = 0; m < kGemvMaxM; ++m) {
       if (m < a.M) {
-        const V xv = ldg<CA, V>(x + (int64_t)m * a.lda + k0);
+        const V xv = ldg<V>(x + (int64_t)m * a.lda + k0);
 #pragma unroll
         for (int e = 0; e < VE; ++e) acc[m] += (float)wv[e] * (float)xv[e];
       }
@@ -1171,7 +991,7 @@ __device__ __forceinline__ void gemv_body(const AR &a, const Blk &b, unsigned ch
     for (int m = 0; m < a.M; ++m) {
       float r = acc[m] * a.alpha;
       if (a.bias) r += a.bias[n];
-      for (int q = 0; q < a.n_extra; ++q) r += (float)ldg<CA, T>((const T *)a.extra[q] + (int64_t)m * a.N + n);
+      for (int q = 0; q < a.n_extra; ++q) r += (float)ldg<T>((const T *)a.extra[q] + (int64_t)m * a.N + n);
       if (a.relu) r = fmaxf(r, 0.f);
       stg<CS, T>(y + (int64_t)m * a.ldy + n, (T)r);
     }
@@ -1183,7 +1003,7 @@ __device__ __forceinline__ void gemv_body(const AR &a, const Blk &b, unsigned ch
 // ---------------------------------------------------------------------------------
 template <typename T, int VE, int COH, typename AR>
 __device__ __forceinline__ void pool_body(const AR &a, const Blk &b, unsigned char *lds) {
-  constexpr bool CA = (COH & kCohAct) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const int cch = a.C / VE;
   const int64_t item = (int64_t)b.x * 256 + threadIdx.x;
   if (item >= (int64_t)a.B * a.Ho * a.Wo * cch) return;
@@ -1199,8 +1019,8 @@ __device__ __forceinline__ void pool_body(const AR &a, const Blk &b, unsigned ch
   auto fetch = [&](int ih, int iw, T *v) {
     const bool ok = (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
     const T *src = x + ((int64_t)(ok ? ih : 0) * a.W + (ok ? iw : 0)) * a.C;
-    if constexpr (VE > 1) *(typename Vec16<T>::type *)v = ldg<CA, typename Vec16<T>::type>(src);
-    else v[0] = ldg<CA, T>(src);
+    if constexpr (VE > 1) *(typename Vec16<T>::type *)v = ldg<typename Vec16<T>::type>(src);
+    else v[0] = ldg<T>(src);
     return ok;
   };
   auto fold = [&](bool ok, const T *v) {
@@ -1245,17 +1065,17 @@ __device__ __forceinline__ void gap_body(const AR &a, const Blk &b, unsigned cha
   float (*part)[64] = (float (*)[64])lds;                                              // [4][64]
   const int cl = threadIdx.x & 63, slice = threadIdx.x >> 6;
   const int c = b.x * 64 + cl;
-  constexpr bool CA = (COH & kCohAct) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const T *__restrict__ x = (const T *)a.x + (int64_t)b.y * a.HW * a.C;
   float s = 0.f;
   if (c < a.C) {
     int p = slice;
     for (; p + 12 < a.HW; p += 16) {
-      const float v0 = (float)ldg<CA, T>(x + (int64_t)p * a.C + c), v1 = (float)ldg<CA, T>(x + (int64_t)(p + 4) * a.C + c);
-      const float v2 = (float)ldg<CA, T>(x + (int64_t)(p + 8) * a.C + c), v3 = (float)ldg<CA, T>(x + (int64_t)(p + 12) * a.C + c);
+      const float v0 = (float)ldg<T>(x + (int64_t)p * a.C + c), v1 = (float)ldg<T>(x + (int64_t)(p + 4) * a.C + c);
+      const float v2 = (float)ldg<T>(x + (int64_t)(p + 8) * a.C + c), v3 = (float)ldg<T>(x + (int64_t)(p + 12) * a.C + c);
       s += (v0 + v1) + (v2 + v3);
     }
-    for (; p < a.HW; p += 4) s += (float)ldg<CA, T>(x + (int64_t)p * a.C + c);
+    for (; p < a.HW; p += 4) s += (float)ldg<T>(x + (int64_t)p * a.C + c);
   }
   part[slice][cl] = s;
   __syncthreads();
@@ -1292,7 +1112,7 @@ __device__ __forceinline__ void row_cached_body(const AR &a, const Blk &b, unsig
   typedef typename Vec16<T>::type V;
   constexpr int VE = Vec16<T>::N;
   float *scratch = (float *)lds;                                                       // [4]
-  constexpr bool CA = (COH & kCohAct) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const int gl = threadIdx.x % G;
   const int row = b.x * (256 / G) + threadIdx.x / G;
   if (G == 64 && row >= a.rows) return;          // whole wavefront leaves together
@@ -1305,7 +1125,7 @@ __device__ __forceinline__ void row_cached_body(const AR &a, const Blk &b, unsig
     for (int e = 0; e < VE; ++e) v[c][e] = 0.f;
     if (col < a.cols) {
       for (int q = 0; q < a.n_in; ++q) {
-        const V t = ldg<CA, V>((const T *)a.in[q] + base + col);
+        const V t = ldg<V>((const T *)a.in[q] + base + col);
 #pragma unroll
         for (int e = 0; e < VE; ++e) v[c][e] += (float)t[e];
       }
@@ -1367,11 +1187,11 @@ __device__ __forceinline__ void row_cached_body(const AR &a, const Blk &b, unsig
 template <typename T, bool IS_LN, int COH, typename AR>
 __device__ __forceinline__ void row_generic_body(const AR &a, const Blk &b, unsigned char *lds) {
   float *scratch = (float *)lds;                                                       // [4]
-  constexpr bool CA = (COH & kCohAct) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const int64_t base = (int64_t)b.x * a.cols;
   auto value = [&](int col) {
     float s = 0.f;
-    for (int q = 0; q < a.n_in; ++q) s += (float)ldg<CA, T>((const T *)a.in[q] + base + col);
+    for (int q = 0; q < a.n_in; ++q) s += (float)ldg<T>((const T *)a.in[q] + base + col);
     return s;
   };
   float p1 = IS_LN ? 0.f : -INFINITY;
@@ -1417,7 +1237,7 @@ template <typename T> __device__ __forceinline__ float elt_apply(int op, float x
 
 template <typename T, int VE, int COH, typename AR>
 __device__ __forceinline__ void elt_body(const AR &a, const Blk &b, unsigned char *lds) {
-  constexpr bool CA = (COH & kCohAct) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const int64_t i = ((int64_t)b.x * 256 + threadIdx.x) * VE;
   if (i >= a.n) return;
   float s[VE];
@@ -1426,8 +1246,8 @@ __device__ __forceinline__ void elt_body(const AR &a, const Blk &b, unsigned cha
   for (int q = 0; q < a.n_in; ++q) {
     T v[VE];
     const T *src = (const T *)a.in[q] + i;
-    if constexpr (VE > 1) *(typename Vec16<T>::type *)v = ldg<CA, typename Vec16<T>::type>(src);
-    else v[0] = ldg<CA, T>(src);
+    if constexpr (VE > 1) *(typename Vec16<T>::type *)v = ldg<typename Vec16<T>::type>(src);
+    else v[0] = ldg<T>(src);
 #pragma unroll
     for (int e = 0; e < VE; ++e) s[e] += (float)v[e];
   }
@@ -1441,7 +1261,7 @@ __device__ __forceinline__ void elt_body(const AR &a, const Blk &b, unsigned cha
 
 template <typename T, int VE, int COH, typename AR>
 __device__ __forceinline__ void concat_body(const AR &a, const Blk &b, unsigned char *lds) {
-  constexpr bool CA = (COH & kCohAct) != 0, CS = (COH & (kCohAct | kCohStore)) != 0;
+  constexpr bool CS = COH != 0;
   const int q = b.y;
   const int cch = a.cols[q] / VE;
   const int64_t item = (int64_t)b.x * 256 + threadIdx.x;
@@ -1450,8 +1270,8 @@ __device__ __forceinline__ void concat_body(const AR &a, const Blk &b, unsigned 
   const int c = (int)(item % cch) * VE;
   const T *src = (const T *)a.in[q] + r * a.cols[q] + c;
   T *dst = (T *)a.y + r * a.out_cols + a.col_off[q] + c;
-  if constexpr (VE > 1) stg<CS, typename Vec16<T>::type>(dst, ldg<CA, typename Vec16<T>::type>(src));
-  else stg<CS, T>(dst, ldg<CA, T>(src));
+  if constexpr (VE > 1) stg<CS, typename Vec16<T>::type>(dst, ldg<typename Vec16<T>::type>(src));
+  else stg<CS, T>(dst, ldg<T>(src));
 }
 
 }  // namespace opara
@@ -1460,9 +1280,9 @@ using namespace opara;
 
 // Workgroup-shared memory each body needs (bytes).
 constexpr int lds_igemm(int bn, int bm) { return 2 * (bn + bm) * 80; }
-constexpr int lds_pipe(int bn, int bm) { return 2 * (bn + bm) * 144; }
+constexpr int lds_tile(int bn, int bm, int stages) { return stages * (bn + bm) * 128; }
+constexpr int lds_split(int ni, int nj, int s) { return 4 * split_ring_bytes(ni, nj, s); }
 constexpr int lds_direct(int waves) { return waves * 32 * 36 * 4; }
-constexpr int lds_quad64(int waves) { return waves * 64 * 68 * 4; }
 constexpr int kLdsGap = 4 * 64 * 4, kLdsRow = 16, kLdsNone = 0;
 
 // Operator timeline (tracing aid, off by default): while a buffer is set, thread 0 of every
@@ -1488,9 +1308,21 @@ __device__ __forceinline__ void op_trace_end(unsigned long long *tr, int tag, un
 __device__ __forceinline__ unsigned launch_lin() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
 __device__ __forceinline__ unsigned launch_total() { return gridDim.x * gridDim.y * gridDim.z; }
 
+// The arguments of a kernel span up to four cache lines, and the compiler reads them where it
+// needs them: one memory round trip after another at the head of every workgroup.  Reading a
+// word of every line first, in one round, lets the later reads hit the scalar cache
+// (isolated 128 x 768 x 768 product: see igemm_split_body).
+template <int BYTES> __device__ __forceinline__ void touch_arguments() {
+  typedef const uint32_t __attribute__((address_space(4))) *CW;
+  const CW w = (CW)__builtin_amdgcn_kernarg_segment_ptr();
+  const uint32_t a = w[0], b = w[(BYTES > 64 ? 64 : 0) / 4], c = w[(BYTES > 128 ? 128 : 0) / 4], d = w[(BYTES - 4) / 4];
+  asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d));
+}
+
 #define KDEF(name, threads, ldsb, Args, call)                                                    \
   extern "C" __global__ void __launch_bounds__(threads) opara_k_##name(Args a, int32_t tag, unsigned long long *trace) {    \
     __shared__ __attribute__((aligned(16))) unsigned char lds[(ldsb) > 0 ? (ldsb) : 16];         \
+    touch_arguments<sizeof(Args) + 16>();                                                        \
     const Blk b = launch_blk();                                                                  \
     const unsigned long long t0 = op_trace_begin();                                              \
     call;                                                                                        \
@@ -1500,27 +1332,30 @@ __device__ __forceinline__ unsigned launch_total() { return gridDim.x * gridDim.
 #define KDEF2(name, threads, waves_per_simd, ldsb, Args, call)                                                \
   extern "C" __global__ void __launch_bounds__(threads, waves_per_simd) opara_k_##name(Args a, int32_t tag, unsigned long long *trace) { \
     __shared__ __attribute__((aligned(16))) unsigned char lds[(ldsb) > 0 ? (ldsb) : 16];                      \
+    touch_arguments<sizeof(Args) + 16>();                                                                     \
     const Blk b = launch_blk();                                                                               \
     const unsigned long long t0 = op_trace_begin();                                                           \
     call;                                                                                                     \
     op_trace_end(trace, tag, t0, launch_lin(), launch_total());                                               \
   }
 
-KDEF2(igemm_f16_t128x64, 256, 2, lds_pipe(128, 64), IgemmArgs, (igemm_pipe_body<half_t, 128, 64, 2, 2, 4, 0>(a, b, lds)))
+KDEF2(igemm_f16_t128x64, 256, 2, lds_tile(128, 64, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 64, 2, 2, 2, 0>(a, b, lds)))
+KDEF2(igemm_f16_tile64x64, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_body<half_t, 64, 64, 2, 2, 3, 0>(a, b, lds)))
+KDEF2(igemm_f16_tile128x128, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 128, 2, 2, 2, 0>(a, b, lds)))
 KDEF(igemm_f16_t64x64, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, 0>(a, b, lds)))
 KDEF(igemm_f16_direct4, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 2, 2>(a, b, lds)))
-KDEF(igemm_f16_direct8, 512, lds_direct(8), IgemmArgs, (igemm_direct_body<half_t, 8, 2, 0, 2, 2>(a, b, lds)))
-KDEF(igemm_f16_quad4, 256, lds_direct(4), IgemmArgs, (igemm_quad_body<half_t, 4, 0, 2, 2>(a, b, lds)))
-KDEF(igemm_f16_quad8, 512, lds_direct(8), IgemmArgs, (igemm_quad_body<half_t, 8, 0, 2, 2>(a, b, lds)))
-KDEF2(igemm_f16_quad64x4, 256, 2, lds_quad64(4), IgemmArgs, (igemm_quad64_body<half_t, 4, 0>(a, b, lds)))
+KDEF2(igemm_f16_quad4, 256, 2, lds_split(2, 2, 2), IgemmArgs, (igemm_split_body<half_t, 2, 2, 2, 0>(a, b, lds)))
+KDEF2(igemm_f16_quad64x4, 256, 3, lds_split(4, 2, 1), IgemmArgs, (igemm_split_body<half_t, 4, 2, 1, 0>(a, b, lds)))
+KDEF2(igemm_f16_quad64x64, 256, 2, lds_split(4, 4, 1), IgemmArgs, (igemm_split_body<half_t, 4, 4, 1, 0>(a, b, lds)))
 KDEF(igemm_f16_t64x64_scalar, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, false, 0>(a, b, lds)))
-KDEF2(igemm_f32_t128x64, 256, 2, lds_pipe(128, 64), IgemmArgs, (igemm_pipe_body<float, 128, 64, 2, 2, 4, 0>(a, b, lds)))
+KDEF2(igemm_f32_t128x64, 256, 2, lds_tile(128, 64, 2), IgemmArgs, (igemm_tile_body<float, 128, 64, 2, 2, 2, 0>(a, b, lds)))
+KDEF2(igemm_f32_tile64x64, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_body<float, 64, 64, 2, 2, 3, 0>(a, b, lds)))
+KDEF2(igemm_f32_tile128x128, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<float, 128, 128, 2, 2, 2, 0>(a, b, lds)))
 KDEF(igemm_f32_t64x64, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<float, 64, 64, 2, 2, true, 0>(a, b, lds)))
 KDEF(igemm_f32_direct4, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 2, 2>(a, b, lds)))
-KDEF(igemm_f32_direct8, 512, lds_direct(8), IgemmArgs, (igemm_direct_body<float, 8, 2, 0, 2, 2>(a, b, lds)))
-KDEF(igemm_f32_quad4, 256, lds_direct(4), IgemmArgs, (igemm_quad_body<float, 4, 0, 2, 2>(a, b, lds)))
-KDEF(igemm_f32_quad8, 512, lds_direct(8), IgemmArgs, (igemm_quad_body<float, 8, 0, 2, 2>(a, b, lds)))
-KDEF2(igemm_f32_quad64x4, 256, 2, lds_quad64(4), IgemmArgs, (igemm_quad64_body<float, 4, 0>(a, b, lds)))
+KDEF2(igemm_f32_quad4, 256, 2, lds_split(2, 2, 2), IgemmArgs, (igemm_split_body<float, 2, 2, 2, 0>(a, b, lds)))
+KDEF2(igemm_f32_quad64x4, 256, 3, lds_split(4, 2, 1), IgemmArgs, (igemm_split_body<float, 4, 2, 1, 0>(a, b, lds)))
+KDEF2(igemm_f32_quad64x64, 256, 2, lds_split(4, 4, 1), IgemmArgs, (igemm_split_body<float, 4, 4, 1, 0>(a, b, lds)))
 KDEF(igemm_f32_t64x64_scalar, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<float, 64, 64, 2, 2, false, 0>(a, b, lds)))
 KDEF(gemv_f16, 256, kLdsNone, IgemmArgs, (gemv_body<half_t, 0>(a, b, lds)))
 KDEF(gemv_f32, 256, kLdsNone, IgemmArgs, (gemv_body<float, 0>(a, b, lds)))
@@ -1552,9 +1387,40 @@ KDEF(concat_f32_vec, 256, kLdsNone, ConcatArgs, (concat_body<float, 4, 0>(a, b, 
 KDEF(concat_f32_scalar, 256, kLdsNone, ConcatArgs, (concat_body<float, 1, 0>(a, b, lds)))
 // 16 x 16 output tiles: four times the workgroups of the 32 x 32 forms, half the operand bytes per workgroup
 KDEF(igemm_f16_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 1, 1>(a, b, lds)))
-KDEF(igemm_f16_quad4s, 256, lds_direct(4), IgemmArgs, (igemm_quad_body<half_t, 4, 0, 1, 1>(a, b, lds)))
+KDEF2(igemm_f16_quad4s, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<half_t, 1, 1, 2, 0>(a, b, lds)))
 KDEF(igemm_f32_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 1, 1>(a, b, lds)))
-KDEF(igemm_f32_quad4s, 256, lds_direct(4), IgemmArgs, (igemm_quad_body<float, 4, 0, 1, 1>(a, b, lds)))
+KDEF2(igemm_f32_quad4s, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<float, 1, 1, 2, 0>(a, b, lds)))
+
+// The 256-thread bodies by the vector registers they need (see the group kernels below):
+// X(kernel name, argument record, body call); T / tn: element type, C: access policy.
+#define STREAM_BODIES(X, T, VE, tn, C)                                                                        \
+  X(gemv_##tn, IgemmArgs, (gemv_body<T, C>(a, b, lds)))                                                       \
+  X(pool_##tn##_vec, PoolArgs, (pool_body<T, VE, C>(a, b, lds)))                                              \
+  X(pool_##tn##_scalar, PoolArgs, (pool_body<T, 1, C>(a, b, lds)))                                            \
+  X(gap_##tn, GapArgs, (gap_body<T, C>(a, b, lds)))                                                           \
+  X(layernorm_##tn##_wave, RowArgs, (row_cached_body<T, true, 64, 2, C>(a, b, lds)))                          \
+  X(layernorm_##tn##_block, RowArgs, (row_cached_body<T, true, 256, kRowCacheChunks, C>(a, b, lds)))          \
+  X(layernorm_##tn##_generic, RowArgs, (row_generic_body<T, true, C>(a, b, lds)))                             \
+  X(softmax_##tn##_wave, RowArgs, (row_cached_body<T, false, 64, 2, C>(a, b, lds)))                           \
+  X(softmax_##tn##_block, RowArgs, (row_cached_body<T, false, 256, kRowCacheChunks, C>(a, b, lds)))           \
+  X(softmax_##tn##_generic, RowArgs, (row_generic_body<T, false, C>(a, b, lds)))                              \
+  X(elt_##tn##_vec, EltArgs, (elt_body<T, VE, C>(a, b, lds)))                                                 \
+  X(elt_##tn##_scalar, EltArgs, (elt_body<T, 1, C>(a, b, lds)))                                               \
+  X(concat_##tn##_vec, ConcatArgs, (concat_body<T, VE, C>(a, b, lds)))                                        \
+  X(concat_##tn##_scalar, ConcatArgs, (concat_body<T, 1, C>(a, b, lds)))
+#define LIGHT_BODIES(X, T, tn, C)                                                                             \
+  X(igemm_##tn##_t64x64, IgemmArgs, (igemm_body<T, 64, 64, 2, 2, true, C>(a, b, lds)))                        \
+  X(igemm_##tn##_t64x64_scalar, IgemmArgs, (igemm_body<T, 64, 64, 2, 2, false, C>(a, b, lds)))                \
+  X(igemm_##tn##_direct4, IgemmArgs, (igemm_direct_body<T, 4, 2, C, 2, 2>(a, b, lds)))                        \
+  X(igemm_##tn##_direct4s, IgemmArgs, (igemm_direct_body<T, 4, 2, C, 1, 1>(a, b, lds)))                       \
+  X(igemm_##tn##_quad4s, IgemmArgs, (igemm_split_body<T, 1, 1, 2, C>(a, b, lds)))                             \
+  X(igemm_##tn##_quad4, IgemmArgs, (igemm_split_body<T, 2, 2, 2, C>(a, b, lds)))
+#define HEAVY_BODIES(X, T, tn, C)                                                                             \
+  X(igemm_##tn##_quad64x4, IgemmArgs, (igemm_split_body<T, 4, 2, 1, C>(a, b, lds)))                           \
+  X(igemm_##tn##_quad64x64, IgemmArgs, (igemm_split_body<T, 4, 4, 1, C>(a, b, lds)))                          \
+  X(igemm_##tn##_tile64x64, IgemmArgs, (igemm_tile_body<T, 64, 64, 2, 2, 3, C>(a, b, lds)))                   \
+  X(igemm_##tn##_t128x64, IgemmArgs, (igemm_tile_body<T, 128, 64, 2, 2, 2, C>(a, b, lds)))                    \
+  X(igemm_##tn##_tile128x128, IgemmArgs, (igemm_tile_body<T, 128, 128, 2, 2, 2, C>(a, b, lds)))
 
 // ---------------------------------------------------------------------------------
 // Persistent executor.  One launch runs the whole DAG: each workgroup repeatedly takes
@@ -1579,80 +1445,36 @@ template <typename A> __device__ __forceinline__ A load_uniform(const void *p) {
   return u.a;
 }
 
-// Inputs inside the persistent kernel: either every load is device-coherent, or loads are
-// plain and each work item starts with one cache invalidate (acquire at device scope).
-#ifndef OPARA_PERSIST_COHERENT_LOADS
-#define OPARA_PERSIST_COHERENT_LOADS 0
-#endif
-constexpr int kPersistAct = OPARA_PERSIST_COHERENT_LOADS ? kCohAct : kCohStore;
-constexpr int kPersistActW = OPARA_PERSIST_COHERENT_LOADS ? (kCohAct | kCohW) : kCohStore;
-
+// Loads inside the persistent kernel are plain: each work item starts with one cache
+// invalidate (acquire at device scope).  (Device-coherent loads instead cost 5-10 % more
+// latency: every operand re-read goes past the L2.)
 template <bool F16>
 __device__ __forceinline__ void persist_run(int kernel, const PersistOp *r, const Blk &b, unsigned char *lds) {
-#define PCASE_(label, Args, call)                             \
-  case label: {                                               \
+#define PCASE(name, Args, call)                               \
+  case K_##name: {                                            \
     typedef const Args __attribute__((address_space(4))) CA;  \
     CA &a = *(CA *)(uintptr_t)&r->args;                       \
     call;                                                     \
   } break;
-#define PCASE(name, Args, call) PCASE_(K_##name, Args, call)
-#define PCASEW(name, Args, call) PCASE_(K_##name + kPersistActivationB, Args, call)
-  if (F16) {
+#define PERSIST_BODIES(T, VE, tn)                                                                             \
+  PCASE(igemm_##tn##_t128x64, IgemmArgs, (igemm_tile_body<T, 128, 64, 2, 2, 2, kCohStore>(a, b, lds)))        \
+  PCASE(igemm_##tn##_t64x64, IgemmArgs, (igemm_body<T, 64, 64, 2, 2, true, kCohStore>(a, b, lds)))            \
+  PCASE(igemm_##tn##_direct4, IgemmArgs, (igemm_direct_body<T, 4, 2, kCohStore, 2, 2>(a, b, lds)))            \
+  PCASE(igemm_##tn##_t64x64_scalar, IgemmArgs, (igemm_body<T, 64, 64, 2, 2, false, kCohStore>(a, b, lds)))    \
+  STREAM_BODIES(PCASE, T, VE, tn, kCohStore)
+  if constexpr (F16) {
     switch (kernel) {
-      PCASE(igemm_f16_t128x64, IgemmArgs, (igemm_pipe_body<half_t, 128, 64, 2, 2, 4, kPersistAct>(a, b, lds)))
-      PCASE(igemm_f16_t64x64, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, kPersistAct>(a, b, lds)))
-      PCASE(igemm_f16_direct4, IgemmArgs, (igemm_direct_body<half_t, 4, 2, kPersistAct, 2, 2>(a, b, lds)))
-      PCASE(igemm_f16_t64x64_scalar, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, false, kPersistAct>(a, b, lds)))
-      PCASEW(igemm_f16_t128x64, IgemmArgs, (igemm_pipe_body<half_t, 128, 64, 2, 2, 4, kPersistActW>(a, b, lds)))
-      PCASEW(igemm_f16_t64x64, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, kPersistActW>(a, b, lds)))
-      PCASEW(igemm_f16_direct4, IgemmArgs, (igemm_direct_body<half_t, 4, 2, kPersistActW, 2, 2>(a, b, lds)))
-      PCASEW(igemm_f16_t64x64_scalar, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, false, kPersistActW>(a, b, lds)))
-      PCASE(gemv_f16, IgemmArgs, (gemv_body<half_t, kPersistAct>(a, b, lds)))
-      PCASE(pool_f16_vec, PoolArgs, (pool_body<half_t, 8, kPersistAct>(a, b, lds)))
-      PCASE(pool_f16_scalar, PoolArgs, (pool_body<half_t, 1, kPersistAct>(a, b, lds)))
-      PCASE(gap_f16, GapArgs, (gap_body<half_t, kPersistAct>(a, b, lds)))
-      PCASE(layernorm_f16_wave, RowArgs, (row_cached_body<half_t, true, 64, 2, kPersistAct>(a, b, lds)))
-      PCASE(layernorm_f16_block, RowArgs, (row_cached_body<half_t, true, 256, kRowCacheChunks, kPersistAct>(a, b, lds)))
-      PCASE(layernorm_f16_generic, RowArgs, (row_generic_body<half_t, true, kPersistAct>(a, b, lds)))
-      PCASE(softmax_f16_wave, RowArgs, (row_cached_body<half_t, false, 64, 2, kPersistAct>(a, b, lds)))
-      PCASE(softmax_f16_block, RowArgs, (row_cached_body<half_t, false, 256, kRowCacheChunks, kPersistAct>(a, b, lds)))
-      PCASE(softmax_f16_generic, RowArgs, (row_generic_body<half_t, false, kPersistAct>(a, b, lds)))
-      PCASE(elt_f16_vec, EltArgs, (elt_body<half_t, 8, kPersistAct>(a, b, lds)))
-      PCASE(elt_f16_scalar, EltArgs, (elt_body<half_t, 1, kPersistAct>(a, b, lds)))
-      PCASE(concat_f16_vec, ConcatArgs, (concat_body<half_t, 8, kPersistAct>(a, b, lds)))
-      PCASE(concat_f16_scalar, ConcatArgs, (concat_body<half_t, 1, kPersistAct>(a, b, lds)))
+      PERSIST_BODIES(half_t, 8, f16)
       default: break;
     }
   } else {
     switch (kernel) {
-      PCASE(igemm_f32_t128x64, IgemmArgs, (igemm_pipe_body<float, 128, 64, 2, 2, 4, kPersistAct>(a, b, lds)))
-      PCASE(igemm_f32_t64x64, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, true, kPersistAct>(a, b, lds)))
-      PCASE(igemm_f32_direct4, IgemmArgs, (igemm_direct_body<float, 4, 2, kPersistAct, 2, 2>(a, b, lds)))
-      PCASE(igemm_f32_t64x64_scalar, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, false, kPersistAct>(a, b, lds)))
-      PCASEW(igemm_f32_t128x64, IgemmArgs, (igemm_pipe_body<float, 128, 64, 2, 2, 4, kPersistActW>(a, b, lds)))
-      PCASEW(igemm_f32_t64x64, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, true, kPersistActW>(a, b, lds)))
-      PCASEW(igemm_f32_direct4, IgemmArgs, (igemm_direct_body<float, 4, 2, kPersistActW, 2, 2>(a, b, lds)))
-      PCASEW(igemm_f32_t64x64_scalar, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, false, kPersistActW>(a, b, lds)))
-      PCASE(gemv_f32, IgemmArgs, (gemv_body<float, kPersistAct>(a, b, lds)))
-      PCASE(pool_f32_vec, PoolArgs, (pool_body<float, 4, kPersistAct>(a, b, lds)))
-      PCASE(pool_f32_scalar, PoolArgs, (pool_body<float, 1, kPersistAct>(a, b, lds)))
-      PCASE(gap_f32, GapArgs, (gap_body<float, kPersistAct>(a, b, lds)))
-      PCASE(layernorm_f32_wave, RowArgs, (row_cached_body<float, true, 64, 2, kPersistAct>(a, b, lds)))
-      PCASE(layernorm_f32_block, RowArgs, (row_cached_body<float, true, 256, kRowCacheChunks, kPersistAct>(a, b, lds)))
-      PCASE(layernorm_f32_generic, RowArgs, (row_generic_body<float, true, kPersistAct>(a, b, lds)))
-      PCASE(softmax_f32_wave, RowArgs, (row_cached_body<float, false, 64, 2, kPersistAct>(a, b, lds)))
-      PCASE(softmax_f32_block, RowArgs, (row_cached_body<float, false, 256, kRowCacheChunks, kPersistAct>(a, b, lds)))
-      PCASE(softmax_f32_generic, RowArgs, (row_generic_body<float, false, kPersistAct>(a, b, lds)))
-      PCASE(elt_f32_vec, EltArgs, (elt_body<float, 4, kPersistAct>(a, b, lds)))
-      PCASE(elt_f32_scalar, EltArgs, (elt_body<float, 1, kPersistAct>(a, b, lds)))
-      PCASE(concat_f32_vec, ConcatArgs, (concat_body<float, 4, kPersistAct>(a, b, lds)))
-      PCASE(concat_f32_scalar, ConcatArgs, (concat_body<float, 1, kPersistAct>(a, b, lds)))
+      PERSIST_BODIES(float, 4, f32)
       default: break;
     }
   }
+#undef PERSIST_BODIES
 #undef PCASE
-#undef PCASEW
-#undef PCASE_
 }
 
 // Thread 0 only: wait until every predecessor of the operator at queue position `pos`
@@ -1775,7 +1597,7 @@ __device__ __forceinline__ void persist_body(const PersistArgs &pa) {
       if (!padding && !persist_wait(pa, preds + pos, pos, epoch, limit)) ctl[0] = 1;
       if (trace) t_ready = wall_clock64();
     }
-    if (!OPARA_PERSIST_COHERENT_LOADS && tid < 64)               // one wavefront invalidates the caches this
+    if (tid < 64)                                                // one wavefront invalidates the caches this
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");         // workgroup reads through (L1 of the CU, L2 of the XCD)
     __syncthreads();                                             // predecessors complete (or abort)
     if (ctl[0]) { prev = -1; break; }
@@ -1879,7 +1701,7 @@ __device__ __forceinline__ void group_body() {
   // paying a third dependent memory round trip.  The touched words only feed a sink.
   typedef const uint32_t __attribute__((address_space(4))) *CW;
   const CW rec = (CW)&ga.args[i];
-  const uint32_t touch = (rec[0] ^ rec[16]) + (rec[32] ^ rec[47]);
+  const uint32_t touch = (rec[0] ^ rec[16]) + (rec[32] ^ rec[sizeof(KernelArgs) / 4 - 1]);
   typedef const GroupMeta __attribute__((address_space(4))) CM;
   CM &me = ga.meta[i];
   const int tile = blk - me.block_begin;
@@ -1904,34 +1726,15 @@ __device__ __forceinline__ void group_body() {
   } break;
   if constexpr (F16) {
     switch (me.kernel) {
-      GCASE(gemv_f16, IgemmArgs, (gemv_body<half_t, 0>(a, b, lds)))
-      GCASE(pool_f16_vec, PoolArgs, (pool_body<half_t, 8, 0>(a, b, lds)))
-      GCASE(pool_f16_scalar, PoolArgs, (pool_body<half_t, 1, 0>(a, b, lds)))
-      GCASE(gap_f16, GapArgs, (gap_body<half_t, 0>(a, b, lds)))
-      GCASE(layernorm_f16_wave, RowArgs, (row_cached_body<half_t, true, 64, 2, 0>(a, b, lds)))
-      GCASE(layernorm_f16_block, RowArgs, (row_cached_body<half_t, true, 256, kRowCacheChunks, 0>(a, b, lds)))
-      GCASE(layernorm_f16_generic, RowArgs, (row_generic_body<half_t, true, 0>(a, b, lds)))
-      GCASE(softmax_f16_wave, RowArgs, (row_cached_body<half_t, false, 64, 2, 0>(a, b, lds)))
-      GCASE(softmax_f16_block, RowArgs, (row_cached_body<half_t, false, 256, kRowCacheChunks, 0>(a, b, lds)))
-      GCASE(softmax_f16_generic, RowArgs, (row_generic_body<half_t, false, 0>(a, b, lds)))
-      GCASE(elt_f16_vec, EltArgs, (elt_body<half_t, 8, 0>(a, b, lds)))
-      GCASE(elt_f16_scalar, EltArgs, (elt_body<half_t, 1, 0>(a, b, lds)))
-      GCASE(concat_f16_vec, ConcatArgs, (concat_body<half_t, 8, 0>(a, b, lds)))
-      GCASE(concat_f16_scalar, ConcatArgs, (concat_body<half_t, 1, 0>(a, b, lds)))
+      STREAM_BODIES(GCASE, half_t, 8, f16, 0)
       default:
         if constexpr (FLAVOR >= 1) {
           switch (me.kernel) {
-            GCASE(igemm_f16_t64x64, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, 0>(a, b, lds)))
-            GCASE(igemm_f16_direct4, IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 2, 2>(a, b, lds)))
-            GCASE(igemm_f16_direct4s, IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 1, 1>(a, b, lds)))
-            GCASE(igemm_f16_quad4s, IgemmArgs, (igemm_quad_body<half_t, 4, 0, 1, 1>(a, b, lds)))
-            GCASE(igemm_f16_t64x64_scalar, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, false, 0>(a, b, lds)))
+            LIGHT_BODIES(GCASE, half_t, f16, 0)
             default:
               if constexpr (FLAVOR >= 2) {
                 switch (me.kernel) {
-                  GCASE(igemm_f16_t128x64, IgemmArgs, (igemm_pipe_body<half_t, 128, 64, 2, 2, 4, 0>(a, b, lds)))
-                  GCASE(igemm_f16_quad4, IgemmArgs, (igemm_quad_body<half_t, 4, 0, 2, 2>(a, b, lds)))
-                  GCASE(igemm_f16_quad64x4, IgemmArgs, (igemm_quad64_body<half_t, 4, 0>(a, b, lds)))
+                  HEAVY_BODIES(GCASE, half_t, f16, 0)
                   default: break;
                 }
               }
@@ -1942,34 +1745,15 @@ __device__ __forceinline__ void group_body() {
     }
   } else {
     switch (me.kernel) {
-      GCASE(gemv_f32, IgemmArgs, (gemv_body<float, 0>(a, b, lds)))
-      GCASE(pool_f32_vec, PoolArgs, (pool_body<float, 4, 0>(a, b, lds)))
-      GCASE(pool_f32_scalar, PoolArgs, (pool_body<float, 1, 0>(a, b, lds)))
-      GCASE(gap_f32, GapArgs, (gap_body<float, 0>(a, b, lds)))
-      GCASE(layernorm_f32_wave, RowArgs, (row_cached_body<float, true, 64, 2, 0>(a, b, lds)))
-      GCASE(layernorm_f32_block, RowArgs, (row_cached_body<float, true, 256, kRowCacheChunks, 0>(a, b, lds)))
-      GCASE(layernorm_f32_generic, RowArgs, (row_generic_body<float, true, 0>(a, b, lds)))
-      GCASE(softmax_f32_wave, RowArgs, (row_cached_body<float, false, 64, 2, 0>(a, b, lds)))
-      GCASE(softmax_f32_block, RowArgs, (row_cached_body<float, false, 256, kRowCacheChunks, 0>(a, b, lds)))
-      GCASE(softmax_f32_generic, RowArgs, (row_generic_body<float, false, 0>(a, b, lds)))
-      GCASE(elt_f32_vec, EltArgs, (elt_body<float, 4, 0>(a, b, lds)))
-      GCASE(elt_f32_scalar, EltArgs, (elt_body<float, 1, 0>(a, b, lds)))
-      GCASE(concat_f32_vec, ConcatArgs, (concat_body<float, 4, 0>(a, b, lds)))
-      GCASE(concat_f32_scalar, ConcatArgs, (concat_body<float, 1, 0>(a, b, lds)))
+      STREAM_BODIES(GCASE, float, 4, f32, 0)
       default:
         if constexpr (FLAVOR >= 1) {
           switch (me.kernel) {
-            GCASE(igemm_f32_t64x64, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, true, 0>(a, b, lds)))
-            GCASE(igemm_f32_direct4, IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 2, 2>(a, b, lds)))
-            GCASE(igemm_f32_direct4s, IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 1, 1>(a, b, lds)))
-            GCASE(igemm_f32_quad4s, IgemmArgs, (igemm_quad_body<float, 4, 0, 1, 1>(a, b, lds)))
-            GCASE(igemm_f32_t64x64_scalar, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, false, 0>(a, b, lds)))
+            LIGHT_BODIES(GCASE, float, f32, 0)
             default:
               if constexpr (FLAVOR >= 2) {
                 switch (me.kernel) {
-                  GCASE(igemm_f32_t128x64, IgemmArgs, (igemm_pipe_body<float, 128, 64, 2, 2, 4, 0>(a, b, lds)))
-                  GCASE(igemm_f32_quad4, IgemmArgs, (igemm_quad_body<float, 4, 0, 2, 2>(a, b, lds)))
-                  GCASE(igemm_f32_quad64x4, IgemmArgs, (igemm_quad64_body<float, 4, 0>(a, b, lds)))
+                  HEAVY_BODIES(GCASE, float, f32, 0)
                   default: break;
                 }
               }
@@ -2056,99 +1840,52 @@ __device__ __forceinline__ void chain_body(const ChainArgs &pa) {
   b.y = rest % b.gy;
   b.z = rest / b.gy;
   unsigned char *lds = dyn_lds;
-#define CCASE_(label, Args, call)                             \
-  case label: {                                               \
+#define CCASE(name, Args, call)                               \
+  case K_##name: {                                            \
     typedef const Args __attribute__((address_space(4))) CA;  \
     CA &a = *(CA *)&r.args;                                   \
     call;                                                     \
   } break;
-#define CCASE(name, Args, call) CCASE_(K_##name, Args, call)
-#define CCASEW(name, Args, call) CCASE_(K_##name + kPersistActivationB, Args, call)
-  constexpr int A = kCohStore, AW = kCohStore;
   if constexpr (F16) {
     switch (r.kernel) {
-      CCASE(igemm_f16_t64x64, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, A>(a, b, lds)))
-      CCASE(igemm_f16_direct4, IgemmArgs, (igemm_direct_body<half_t, 4, 2, A, 2, 2>(a, b, lds)))
-      CCASE(igemm_f16_direct4s, IgemmArgs, (igemm_direct_body<half_t, 4, 2, A, 1, 1>(a, b, lds)))
-      CCASEW(igemm_f16_direct4s, IgemmArgs, (igemm_direct_body<half_t, 4, 2, AW, 1, 1>(a, b, lds)))
-      CCASE(igemm_f16_quad4s, IgemmArgs, (igemm_quad_body<half_t, 4, A, 1, 1>(a, b, lds)))
-      CCASEW(igemm_f16_quad4s, IgemmArgs, (igemm_quad_body<half_t, 4, AW, 1, 1>(a, b, lds)))
-      CCASE(igemm_f16_t64x64_scalar, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, false, A>(a, b, lds)))
-      CCASEW(igemm_f16_t64x64, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, AW>(a, b, lds)))
-      CCASEW(igemm_f16_direct4, IgemmArgs, (igemm_direct_body<half_t, 4, 2, AW, 2, 2>(a, b, lds)))
-      CCASEW(igemm_f16_t64x64_scalar, IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, false, AW>(a, b, lds)))
-      CCASE(gemv_f16, IgemmArgs, (gemv_body<half_t, A>(a, b, lds)))
-      CCASE(pool_f16_vec, PoolArgs, (pool_body<half_t, 8, A>(a, b, lds)))
-      CCASE(pool_f16_scalar, PoolArgs, (pool_body<half_t, 1, A>(a, b, lds)))
-      CCASE(gap_f16, GapArgs, (gap_body<half_t, A>(a, b, lds)))
-      CCASE(layernorm_f16_wave, RowArgs, (row_cached_body<half_t, true, 64, 2, A>(a, b, lds)))
-      CCASE(layernorm_f16_block, RowArgs, (row_cached_body<half_t, true, 256, kRowCacheChunks, A>(a, b, lds)))
-      CCASE(layernorm_f16_generic, RowArgs, (row_generic_body<half_t, true, A>(a, b, lds)))
-      CCASE(softmax_f16_wave, RowArgs, (row_cached_body<half_t, false, 64, 2, A>(a, b, lds)))
-      CCASE(softmax_f16_block, RowArgs, (row_cached_body<half_t, false, 256, kRowCacheChunks, A>(a, b, lds)))
-      CCASE(softmax_f16_generic, RowArgs, (row_generic_body<half_t, false, A>(a, b, lds)))
-      CCASE(elt_f16_vec, EltArgs, (elt_body<half_t, 8, A>(a, b, lds)))
-      CCASE(elt_f16_scalar, EltArgs, (elt_body<half_t, 1, A>(a, b, lds)))
-      CCASE(concat_f16_vec, ConcatArgs, (concat_body<half_t, 8, A>(a, b, lds)))
-      CCASE(concat_f16_scalar, ConcatArgs, (concat_body<half_t, 1, A>(a, b, lds)))
+      STREAM_BODIES(CCASE, half_t, 8, f16, kCohStore)
       default:
-        if constexpr (!LIGHT) {
+        if constexpr (true) {
           switch (r.kernel) {
-            CCASE(igemm_f16_t128x64, IgemmArgs, (igemm_pipe_body<half_t, 128, 64, 2, 2, 4, A>(a, b, lds)))
-            CCASE(igemm_f16_quad4, IgemmArgs, (igemm_quad_body<half_t, 4, A, 2, 2>(a, b, lds)))
-            CCASE(igemm_f16_quad64x4, IgemmArgs, (igemm_quad64_body<half_t, 4, A>(a, b, lds)))
-            CCASEW(igemm_f16_t128x64, IgemmArgs, (igemm_pipe_body<half_t, 128, 64, 2, 2, 4, AW>(a, b, lds)))
-            CCASEW(igemm_f16_quad4, IgemmArgs, (igemm_quad_body<half_t, 4, AW, 2, 2>(a, b, lds)))
-            CCASEW(igemm_f16_quad64x4, IgemmArgs, (igemm_quad64_body<half_t, 4, AW>(a, b, lds)))
-            default: break;
+            LIGHT_BODIES(CCASE, half_t, f16, kCohStore)
+            default:
+              if constexpr (!LIGHT) {
+                switch (r.kernel) {
+                  HEAVY_BODIES(CCASE, half_t, f16, kCohStore)
+                  default: break;
+                }
+              }
+              break;
           }
         }
         break;
     }
   } else {
     switch (r.kernel) {
-      CCASE(igemm_f32_t64x64, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, true, A>(a, b, lds)))
-      CCASE(igemm_f32_direct4, IgemmArgs, (igemm_direct_body<float, 4, 2, A, 2, 2>(a, b, lds)))
-      CCASE(igemm_f32_direct4s, IgemmArgs, (igemm_direct_body<float, 4, 2, A, 1, 1>(a, b, lds)))
-      CCASEW(igemm_f32_direct4s, IgemmArgs, (igemm_direct_body<float, 4, 2, AW, 1, 1>(a, b, lds)))
-      CCASE(igemm_f32_quad4s, IgemmArgs, (igemm_quad_body<float, 4, A, 1, 1>(a, b, lds)))
-      CCASEW(igemm_f32_quad4s, IgemmArgs, (igemm_quad_body<float, 4, AW, 1, 1>(a, b, lds)))
-      CCASE(igemm_f32_t64x64_scalar, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, false, A>(a, b, lds)))
-      CCASEW(igemm_f32_t64x64, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, true, AW>(a, b, lds)))
-      CCASEW(igemm_f32_direct4, IgemmArgs, (igemm_direct_body<float, 4, 2, AW, 2, 2>(a, b, lds)))
-      CCASEW(igemm_f32_t64x64_scalar, IgemmArgs, (igemm_body<float, 64, 64, 2, 2, false, AW>(a, b, lds)))
-      CCASE(gemv_f32, IgemmArgs, (gemv_body<float, A>(a, b, lds)))
-      CCASE(pool_f32_vec, PoolArgs, (pool_body<float, 4, A>(a, b, lds)))
-      CCASE(pool_f32_scalar, PoolArgs, (pool_body<float, 1, A>(a, b, lds)))
-      CCASE(gap_f32, GapArgs, (gap_body<float, A>(a, b, lds)))
-      CCASE(layernorm_f32_wave, RowArgs, (row_cached_body<float, true, 64, 2, A>(a, b, lds)))
-      CCASE(layernorm_f32_block, RowArgs, (row_cached_body<float, true, 256, kRowCacheChunks, A>(a, b, lds)))
-      CCASE(layernorm_f32_generic, RowArgs, (row_generic_body<float, true, A>(a, b, lds)))
-      CCASE(softmax_f32_wave, RowArgs, (row_cached_body<float, false, 64, 2, A>(a, b, lds)))
-      CCASE(softmax_f32_block, RowArgs, (row_cached_body<float, false, 256, kRowCacheChunks, A>(a, b, lds)))
-      CCASE(softmax_f32_generic, RowArgs, (row_generic_body<float, false, A>(a, b, lds)))
-      CCASE(elt_f32_vec, EltArgs, (elt_body<float, 4, A>(a, b, lds)))
-      CCASE(elt_f32_scalar, EltArgs, (elt_body<float, 1, A>(a, b, lds)))
-      CCASE(concat_f32_vec, ConcatArgs, (concat_body<float, 4, A>(a, b, lds)))
-      CCASE(concat_f32_scalar, ConcatArgs, (concat_body<float, 1, A>(a, b, lds)))
+      STREAM_BODIES(CCASE, float, 4, f32, kCohStore)
       default:
-        if constexpr (!LIGHT) {
+        if constexpr (true) {
           switch (r.kernel) {
-            CCASE(igemm_f32_t128x64, IgemmArgs, (igemm_pipe_body<float, 128, 64, 2, 2, 4, A>(a, b, lds)))
-            CCASE(igemm_f32_quad4, IgemmArgs, (igemm_quad_body<float, 4, A, 2, 2>(a, b, lds)))
-            CCASE(igemm_f32_quad64x4, IgemmArgs, (igemm_quad64_body<float, 4, A>(a, b, lds)))
-            CCASEW(igemm_f32_t128x64, IgemmArgs, (igemm_pipe_body<float, 128, 64, 2, 2, 4, AW>(a, b, lds)))
-            CCASEW(igemm_f32_quad4, IgemmArgs, (igemm_quad_body<float, 4, AW, 2, 2>(a, b, lds)))
-            CCASEW(igemm_f32_quad64x4, IgemmArgs, (igemm_quad64_body<float, 4, AW>(a, b, lds)))
-            default: break;
+            LIGHT_BODIES(CCASE, float, f32, kCohStore)
+            default:
+              if constexpr (!LIGHT) {
+                switch (r.kernel) {
+                  HEAVY_BODIES(CCASE, float, f32, kCohStore)
+                  default: break;
+                }
+              }
+              break;
           }
         }
         break;
     }
   }
 #undef CCASE
-#undef CCASEW
-#undef CCASE_
   __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0): this wavefront's stores are complete
   __syncthreads();                                               // ... for every wavefront of the workgroup
   if (tid == 0) {
@@ -2315,17 +2052,11 @@ void *group_func(bool f16, int flavor, bool traced) {
 
 int group_flavor(int id) {
   switch (id) {
-    case K_igemm_f16_t128x64: case K_igemm_f32_t128x64: case K_igemm_f16_quad4: case K_igemm_f32_quad4:
-    case K_igemm_f16_quad64x4: case K_igemm_f32_quad64x4:
-      return 2;
-    case K_igemm_f16_direct8: case K_igemm_f32_direct8: case K_igemm_f16_quad8: case K_igemm_f32_quad8:
-      return -1;                          // 512-thread bodies
-    case K_igemm_f16_t64x64: case K_igemm_f32_t64x64: case K_igemm_f16_direct4: case K_igemm_f32_direct4:
-    case K_igemm_f16_direct4s: case K_igemm_f32_direct4s: case K_igemm_f16_quad4s: case K_igemm_f32_quad4s:
-    case K_igemm_f16_t64x64_scalar: case K_igemm_f32_t64x64_scalar:
-      return 1;
-    default:
-      return id >= 0 && id < K_COUNT ? 0 : -1;
+#define FCASE(name, Args, call) case K_##name:
+    HEAVY_BODIES(FCASE, half_t, f16, 0) HEAVY_BODIES(FCASE, float, f32, 0) return 2;
+    LIGHT_BODIES(FCASE, half_t, f16, 0) LIGHT_BODIES(FCASE, float, f32, 0) return 1;
+#undef FCASE
+    default: return id >= 0 && id < K_COUNT ? 0 : -1;
   }
 }
 
@@ -2410,14 +2141,10 @@ hipError_t launch_chain(bool f16, bool light, const ChainArgs &a, uint32_t lds_b
 
 int persist_kernel_id(int id) {
   switch (id) {
-    // One tile shape, one workgroup size: inside the persistent kernel every
-    // latency-oriented contraction runs the four-wavefront fragment-loading body.
-    case K_igemm_f16_direct8: case K_igemm_f16_quad4: case K_igemm_f16_quad8: return K_igemm_f16_direct4;
-    case K_igemm_f32_direct8: case K_igemm_f32_quad4: case K_igemm_f32_quad8: return K_igemm_f32_direct4;
-    case K_igemm_f16_quad64x4: case K_igemm_f32_quad64x4:
-    case K_igemm_f16_direct4s: case K_igemm_f16_quad4s: case K_igemm_f32_direct4s: case K_igemm_f32_quad4s:
-      return -1;                          // never in a persistent plan
-    default: return (id >= 0 && id < K_COUNT) ? id : -1;
+    case K_igemm_f16_t128x64: case K_igemm_f32_t128x64: case K_igemm_f16_t64x64: case K_igemm_f32_t64x64:
+    case K_igemm_f16_t64x64_scalar: case K_igemm_f32_t64x64_scalar: case K_igemm_f16_direct4: case K_igemm_f32_direct4:
+      return id;                          // one tile shape for every latency-oriented contraction
+    default: return group_flavor(id) == 0 ? id : -1;
   }
 }
 

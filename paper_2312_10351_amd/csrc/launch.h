@@ -50,11 +50,9 @@ constexpr int kPersistCounterStride = 64;        // uint32 words between complet
 constexpr int kPersistReplicas = 32;             // copies of each operator's "complete" flag, 128 bytes apart:
 constexpr int kPersistFlagStride = 32;           // a workgroup polls copy (blockIdx % replicas), so that a
                                                  // flag has at most 1/32 of the waiting workgroups polling it
-constexpr uint32_t kPersistBodyLds = 2 * (128 + 64) * 144;   // largest body: the 128x64 pipelined tile
+constexpr uint32_t kPersistBodyLds = 2 * (128 + 64) * 128;   // largest body: the 128x64 tile
 constexpr uint32_t kPersistMaxLds = 160 * 1024;                // per workgroup on gfx950
 constexpr uint32_t kPersistDefaultSpinLimit = 1u << 22;
-constexpr int32_t kPersistActivationB = 0x100;   // added to a record's kernel id: the second
-                                                 // operand of the contraction is an activation
 struct PersistHeader {            // 64 bytes at the start of the workspace
   uint32_t reserved0;
   uint32_t exited;                // workgroups that have left; reset by the last one out
@@ -87,8 +85,7 @@ struct PersistArgs {
   const PersistOp *rec;           // [n]
   int32_t n, total;               // operators, work items
 };
-// Kernel ids the persistent kernel can run (256-thread bodies); others map through
-// persist_kernel_id (the 8- and 16-wavefront contractions run their 4-wavefront form).
+// Kernel ids the persistent kernel can run.
 int persist_kernel_id(int kernel_id);              // -1: not available
 bool kernel_is_f16(int kernel_id);
 // Workgroups of the persistent kernel the device holds at once (all must be resident).
@@ -107,7 +104,7 @@ hipError_t launch_persist(bool f16, const PersistArgs &a, uint32_t n_workgroups,
 // unfinished block never waits for a block that has not been dispatched: the launch drains
 // whatever number of workgroups the device holds at a time.
 struct ChainRec {                 // one operator, read through the constant address space
-  int32_t kernel, gx, gy, gz;     // body (KernelId, + kPersistActivationB for two-activation contractions) and grid
+  int32_t kernel, gx, gy, gz;     // body (KernelId) and grid
   int32_t begin, tiles;           // first block of the operator, gx * gy * gz
   uint16_t n_preds, reserved;
   uint16_t preds[kPersistMaxPreds];   // queue positions of the predecessors inside the kernel

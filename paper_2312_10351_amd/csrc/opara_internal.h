@@ -28,7 +28,6 @@ struct opara_dag {
   std::vector<int32_t> topo, tindex;
   std::vector<opara::KernelPlan> plan;          // graph executors (and the demand table)
   std::vector<opara::KernelPlan> plan_persist;  // persistent executor
-  std::vector<opara::KernelPlan> plan_group;    // inside a group node of the fused executor (256-thread bodies)
   std::vector<opara_demand> dem;
   std::vector<int32_t> stream_of;   // empty until opara_assign_streams
   int32_t n_streams = 0;
@@ -53,11 +52,14 @@ int sync_keep_mask(const opara_dag *g, std::vector<uint8_t> *keep);
 
 // Chooses the kernel, grid and arguments for operator `v`; `in[i]` are the resolved
 // device pointers of its inputs.  kPlanGraph is the plan the graph executors launch and the
-// demand table describes; kPlanPersistent the one the persistent executor runs (one
-// workgroup size, fragment-loading contractions, its own hand-over point to the tiled
-// kernel); kPlanGroup the one for operators inside a group kernel (one workgroup size,
-// quad-coalesced contractions allowed).  Returns an opara_status.
-enum { kPlanGraph = 0, kPlanPersistent = 1, kPlanGroup = 2 };
+// demand table describes (also the starting point of the fused executor); kPlanPersistent the
+// one the persistent executor runs (two contraction kernels, its own hand-over point between
+// them).  Returns an opara_status.
+enum { kPlanGraph = 0, kPlanPersistent = 1 };
 int plan_op(const opara_op_desc &op, const void *const *in, int kind, KernelPlan *out);
+
+// Tile shapes of contractions that run together; only for kernels whose shape is open.
+bool tile_choice_open(int kernel_id);
+void choose_tiles(KernelPlan *const *plans, int n);
 
 }  // namespace opara

@@ -2,7 +2,10 @@
 // The demand record of an operator (paper Sec. 3.2: threads, shared memory and
 // registers of one block; Sec. 2.3: number of blocks) follows from the plan made
 // here plus the static resources of the chosen kernel.
+#include <algorithm>
+#include <cmath>
 #include <cstring>
+#include <vector>
 #include "opara_internal.h"
 
 namespace opara {
@@ -18,13 +21,34 @@ namespace {
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline uint32_t cdiv(int64_t a, int64_t b) { return (uint32_t)((a + b - 1) / b); }
 
+inline uint32_t div_magic(int32_t d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint64_t)d) : 0xffffffffu; }
+
+// The contractions fed through workgroup memory, and what one workgroup of each costs, in
+// microseconds: a 128-byte step of K when the workgroup has a compute unit to itself
+// (`alone`) and when the launch keeps every CU busy (`busy`), and everything outside the K
+// walk (`fixed`).  Fitted to isolated fp16 products, M x N x K = 49..346688 x 32..4096 x
+// 320..4096, within 15 %.  In fp32 a step cannot take less than its multiply-adds at the
+// matrix rate of a CU (0.6 TFLOP/s).
+struct TileKernel { int ids[2]; int bn, bm; double alone, busy, fixed; };   // ids: f32, f16
+const TileKernel kTileKernels[] = {
+    {{K_igemm_f32_quad4s, K_igemm_f16_quad4s}, 16, 16, 0.060, 0.037, 0.25},
+    {{K_igemm_f32_quad4, K_igemm_f16_quad4}, 32, 32, 0.080, 0.075, 0.58},
+    {{K_igemm_f32_quad64x4, K_igemm_f16_quad64x4}, 64, 32, 0.122, 0.125, 0.50},
+    {{K_igemm_f32_quad64x64, K_igemm_f16_quad64x64}, 64, 64, 0.160, 0.165, 1.6},
+    {{K_igemm_f32_tile64x64, K_igemm_f16_tile64x64}, 64, 64, 0.28, 0.18, 0.8},
+    {{K_igemm_f32_t128x64, K_igemm_f16_t128x64}, 128, 64, 0.45, 0.33, 1.2},
+    {{K_igemm_f32_tile128x128, K_igemm_f16_tile128x128}, 128, 128, 0.56, 0.48, 1.7},
+};
+constexpr int kTileKernelCount = sizeof kTileKernels / sizeof kTileKernels[0];
+constexpr double kCus = 256.0;
+
 int fail(const char *what, const opara_op_desc &op) {
   set_error("operator type %d: %s", op.op_type, what);
   return OPARA_EINVAL;
 }
 
 int plan_igemm(const opara_op_desc &op, const void *const *in, int kind, KernelPlan *out) {
-  const bool persistent = kind == kPlanPersistent, group = kind == kPlanGroup;
+  const bool persistent = kind == kPlanPersistent;
   const opara_op_params &p = op.params;
   const bool f16 = op.dtype == OPARA_F16;
   const int ve = f16 ? 8 : 4;
@@ -34,6 +58,7 @@ int plan_igemm(const opara_op_desc &op, const void *const *in, int kind, KernelP
   a.bias = op.bias;
   a.y = op.out;
   a.alpha = 1.0f;
+  a.HoWo = a.Wo = a.Cin = a.kw = 1;
   a.relu = (p.flags & OPARA_FLAG_RELU) ? 1 : 0;
   int64_t batch = 1;
   bool vec;
@@ -89,108 +114,52 @@ int plan_igemm(const opara_op_desc &op, const void *const *in, int kind, KernelP
           (!a.b_kmajor || p.n % ve == 0);
   }
   vec = vec && aligned16(a.x) && aligned16(a.w);
-  int kernel;
-  IgemmTile t = kTile64;
-  if (vec && op.op_type == OPARA_GEMM && a.M <= kGemvMaxM) {
-    kernel = f16 ? K_gemv_f16 : K_gemv_f32;
+  a.div_HoWo = div_magic(a.HoWo); a.div_Wo = div_magic(a.Wo);
+  a.div_Cin = div_magic(a.Cin); a.div_kw = div_magic(a.kw);
+  auto set = [&](int kernel, int bn, int bm) {
     out->kernel = kernel;
-    out->gx = cdiv(a.N, 4);            // one wave per output column, four waves per workgroup
-    out->gy = out->gz = 1;
+    out->gx = cdiv(a.M, bm);
+    out->gy = cdiv(a.N, bn);
+    out->gz = (uint32_t)batch;
     out->block = 256;
     out->args.igemm = a;
     return OPARA_OK;
+  };
+  if (vec && op.op_type == OPARA_GEMM && a.M <= kGemvMaxM) {
+    set(f16 ? K_gemv_f16 : K_gemv_f32, 1, 1);
+    out->gx = cdiv(a.N, 4);            // one wave per output column, four waves per workgroup
+    out->gy = 1;
+    return OPARA_OK;
   }
-  if (!vec) {
-    kernel = f16 ? K_igemm_f16_t64x64_scalar : K_igemm_f32_t64x64_scalar;
-  } else {
-    const int64_t n128 = (int64_t)cdiv(a.M, 128) * cdiv(a.N, 128) * batch;
+  if (!vec) return set(f16 ? K_igemm_f16_t64x64_scalar : K_igemm_f32_t64x64_scalar, kTile64.bn, kTile64.bm);
+  const int64_t es = f16 ? 2 : 4;
+  const int64_t x_bytes = es * (a.gather ? (int64_t)(a.M / a.HoWo) * a.img_stride : (int64_t)(a.M - 1) * a.lda + a.K);
+  const int64_t w_bytes = es * ((int64_t)(a.N - 1) * a.ldb + a.K);
+  const bool fits = x_bytes < (int64_t)kOperandMaxBytes && w_bytes < (int64_t)kOperandMaxBytes && a.K * es < (int64_t)1 << 29 &&
+                    (!a.gather || ((int64_t)a.kh * a.W + a.kw < 1 << 24 && a.Cin < 1 << 24));
+  a.x_bytes = fits ? (uint32_t)x_bytes : 0;
+  a.w_bytes = fits ? (uint32_t)w_bytes : 0;
+  // [K][N] operand, or operands past the reach of 32-bit offsets: staged through registers.
+  if (a.b_kmajor || !fits)
+    return set(f16 ? K_igemm_f16_t64x64 : K_igemm_f32_t64x64, kTile64.bn, kTile64.bm);
+  const int64_t row_bytes = a.K * es;
+  const int64_t tiles32 = (int64_t)cdiv(a.M, kDirectTile) * cdiv(a.N, kDirectTile) * batch;
+  if (persistent) {
+    // One tile shape for the latency-oriented work, a larger one for heavy contractions.
     const double flops = 2.0 * a.M * a.N * a.K * (double)batch;
     const int64_t tiles = (int64_t)cdiv(a.M, kTile128x64.bm) * cdiv(a.N, kTile128x64.bn) * batch;
-    (void)n128;
-    const int64_t lim32 = (int64_t)1 << 31;
-    const bool fits32 = (int64_t)a.M * a.lda < lim32 && (int64_t)a.N * a.ldb < lim32 &&
-                        (!a.gather || (int64_t)(a.M / a.HoWo) * a.img_stride < lim32);
-    const bool quad64 = !persistent && !a.b_kmajor && !a.gather && fits32 && flops < kQuad64MaxFlops &&
-                        (int64_t)cdiv(a.M, 64) * cdiv(a.N, 64) * batch >= kQuad64MinTiles &&
-                        (int64_t)a.K * (f16 ? 2 : 4) >= kQuadMinRowBytes;
-    if (quad64) {
-      // GEMM-shaped and at least one 64 x 64 tile per compute unit: the quad-coalesced
-      // kernel whose wavefronts each multiply a whole tile over their share of K.
-      // Four wavefronts whatever K is: two such workgroups share a CU (70 KB of LDS each),
-      // which beat one eight-wavefront workgroup on every shape measured and leaves room
-      // for workgroups of co-running operators.
-      const int waves = 4;
-      out->kernel = f16 ? K_igemm_f16_quad64x4 : K_igemm_f32_quad64x4;
-      out->gx = cdiv(a.M, 64);
-      out->gy = cdiv(a.N, 64);
-      out->gz = (uint32_t)batch;
-      out->block = waves * 64;
-      out->args.igemm = a;
-      return OPARA_OK;
-    }
-    if (!a.b_kmajor && tiles >= kTiledMinTiles && flops >= (persistent ? kTiledMinFlopsPersistent : kTiledMinFlops)) {
-      // Throughput-oriented tiled kernel (128 output columns x 64 rows per workgroup):
-      // pays once the contraction is heavy and has enough tiles to occupy the device.
-      t = kTile128x64;
-      kernel = f16 ? K_igemm_f16_t128x64 : K_igemm_f32_t128x64;
-    } else if (a.b_kmajor) {           // [K][N] operand: staged (and transposed) through LDS
-      t = kTile64;
-      kernel = f16 ? K_igemm_f16_t64x64 : K_igemm_f32_t64x64;
-    } else if (!fits32) {              // the latency-oriented kernel keeps 32-bit element offsets
-      t = kTile64;
-      kernel = f16 ? K_igemm_f16_t64x64 : K_igemm_f32_t64x64;
-    } else {
-      // Latency-oriented kernels, one 32 x 32 tile per workgroup, K split between its
-      // wavefronts.  Deep contractions take the variant whose loads are coalesced in lane
-      // groups of four (three times the load rate, paid for with a register transposition
-      // per 256-byte step); shallow ones, where a wavefront walks a step or two, the
-      // variant that loads MFMA fragments as they are.
-      static const int ids[2][4] = {{K_igemm_f32_direct4, K_igemm_f32_direct8, K_igemm_f32_quad4, K_igemm_f32_quad8},
-                                    {K_igemm_f16_direct4, K_igemm_f16_direct8, K_igemm_f16_quad4, K_igemm_f16_quad8}};
-      // Convolutions with a tile or more for every other compute unit and rows of K up to 2 KiB
-      // keep the fragment-loading kernel: with that many workgroups its four resident
-      // workgroups per CU (105 registers against 211) hide more latency than the faster
-      // loads of the quad-coalesced one save (GoogLeNet-like stem 3x3: 10.6 -> 9.2 us).  GEMMs
-      // of that shape are better off with the quad-coalesced kernel (BERT-like FFN: measured).
-      const int64_t row_bytes = (int64_t)a.K * (f16 ? 2 : 4);
-      const int64_t tiles32q = (int64_t)cdiv(a.M, kDirectTile) * cdiv(a.N, kDirectTile) * batch;
-      const bool quad = !persistent && row_bytes >= kQuadMinRowBytes &&
-                        !(a.gather && tiles32q >= kQuadFourWaveTiles && row_bytes <= 2 * kQuadMinRowBytes);
-      int waves;
-      // Deep K on few tiles: eight wavefronts share it (latency).  With a tile or more per
-      // compute unit, four: more workgroups per CU overlap better than longer ones.
-      const int64_t tiles32 = (int64_t)cdiv(a.M, kDirectTile) * cdiv(a.N, kDirectTile) * batch;
-      if (group) waves = 4;                                    // one workgroup size inside a group kernel
-      else if (quad) waves = (cdiv(a.K, 16 * ve) <= 8 || tiles32 >= (int64_t)kQuadFourWaveTiles) ? 4 : 8;   // 256-byte steps
-      else waves = cdiv(a.K, 8 * ve) <= 16 ? 4 : 8;            // 128-byte steps
-      // Few tiles (the 14 x 14 and 7 x 7 stages of the CNNs): the load rate of ONE compute unit
-      // bounds a workgroup, so 16 x 16 tiles on four times as many compute units finish sooner
-      // although they move twice the operand bytes in total.
-      static const int small_ids[2][2] = {{K_igemm_f32_direct4s, K_igemm_f32_quad4s}, {K_igemm_f16_direct4s, K_igemm_f16_quad4s}};
-      if (!persistent && tiles32 <= kSmallTileMaxTiles32) {
-        out->kernel = small_ids[f16][quad ? 1 : 0];
-        out->gx = cdiv(a.M, kSmallTile);
-        out->gy = cdiv(a.N, kSmallTile);
-        out->gz = (uint32_t)batch;
-        out->block = 256;
-        out->args.igemm = a;
-        return OPARA_OK;
-      }
-      out->kernel = ids[f16][(quad ? 2 : 0) + (waves == 8 ? 1 : 0)];
-      out->gx = cdiv(a.M, kDirectTile);
-      out->gy = cdiv(a.N, kDirectTile);
-      out->gz = (uint32_t)batch;
-      out->block = waves * 64;
-      out->args.igemm = a;
-      return OPARA_OK;
-    }
+    if (tiles >= kTiledMinTiles && flops >= kTiledMinFlopsPersistent)
+      return set(f16 ? K_igemm_f16_t128x64 : K_igemm_f32_t128x64, kTile128x64.bn, kTile128x64.bm);
+    return set(f16 ? K_igemm_f16_direct4 : K_igemm_f32_direct4, kDirectTile, kDirectTile);
   }
-  out->kernel = kernel;
-  out->gx = cdiv(a.M, t.bm);
-  out->gy = cdiv(a.N, t.bn);
-  out->gz = (uint32_t)batch;
-  out->block = t.threads;
-  out->args.igemm = a;
+  if (row_bytes < kQuadMinRowBytes && tiles32 < kDirectMaxTiles32) {
+    // A wavefront walks a step or two of K: operands go to the matrix cores as they are loaded.
+    if (tiles32 <= kSmallTileMaxTiles32) return set(f16 ? K_igemm_f16_direct4s : K_igemm_f32_direct4s, kSmallTile, kSmallTile);
+    return set(f16 ? K_igemm_f16_direct4 : K_igemm_f32_direct4, kDirectTile, kDirectTile);
+  }
+  set(kTileKernels[0].ids[f16], kTileKernels[0].bn, kTileKernels[0].bm);
+  KernelPlan *one = out;
+  choose_tiles(&one, 1);
   return OPARA_OK;
 }
 
@@ -306,6 +275,67 @@ int plan_concat(const opara_op_desc &op, const void *const *in, KernelPlan *out)
 }
 
 }  // namespace
+
+// Tile shapes of contractions that run together (the members of one launch, or a single
+// operator).  Small tiles finish one operator sooner (more CUs share it), large ones move
+// fewer bytes per multiply-add; what counts is the longer of the time the work takes on all
+// CUs together and the time the longest workgroup takes.  For every bound L on the latter,
+// each operator takes its cheapest tile shape within L; the best L wins.
+void choose_tiles(KernelPlan *const *plans, int n) {
+  struct Option { double longest, work; };
+  std::vector<std::vector<Option>> opt(n);
+  std::vector<double> bounds;
+  for (int i = 0; i < n; ++i) {
+    const IgemmArgs &a = plans[i]->args.igemm;
+    const bool f16 = plans[i]->kernel == kTileKernels[0].ids[1] || std::any_of(kTileKernels, kTileKernels + kTileKernelCount,
+                     [&](const TileKernel &t) { return t.ids[1] == plans[i]->kernel; });
+    const double steps = std::ceil(a.K * (f16 ? 2.0 : 4.0) / 128.0);
+    for (const TileKernel &t : kTileKernels) {
+      const double tiles = (double)cdiv(a.M, t.bm) * cdiv(a.N, t.bn) * plans[i]->gz;
+      const double least = f16 ? 0.0 : t.bn * t.bm * 32 * 2.0 / 0.6e6;
+      Option o;
+      o.longest = steps * std::max(t.alone, least) + t.fixed;
+      o.work = tiles * (steps * std::max(t.busy, least) + t.fixed) / kCus;
+      if (n == 1 && tiles > kCus && tiles < 4 * kCus)      // a single launch: whole rounds over the CUs
+        o.work *= std::ceil(tiles / kCus) * kCus / tiles;
+      opt[i].push_back(o);
+      bounds.push_back(o.longest);
+    }
+  }
+  std::sort(bounds.begin(), bounds.end());
+  double best = -1.0;
+  std::vector<int> pick(n), take(n);
+  for (double bound : bounds) {
+    double work = 0.0, longest = 0.0;
+    bool ok = true;
+    for (int i = 0; i < n && ok; ++i) {
+      int k = -1;
+      for (int j = 0; j < kTileKernelCount; ++j)
+        if (opt[i][j].longest <= bound && (k < 0 || opt[i][j].work < opt[i][k].work)) k = j;
+      ok = k >= 0;
+      if (!ok) break;
+      take[i] = k;
+      work += opt[i][k].work;
+      longest = std::max(longest, opt[i][k].longest);
+    }
+    if (!ok) continue;
+    const double cost = std::max(work, longest);
+    if (best < 0.0 || cost < best) { best = cost; pick = take; }
+  }
+  for (int i = 0; i < n; ++i) {
+    const TileKernel &t = kTileKernels[pick[i]];
+    const bool f16 = std::any_of(kTileKernels, kTileKernels + kTileKernelCount, [&](const TileKernel &q) { return q.ids[1] == plans[i]->kernel; });
+    const IgemmArgs &a = plans[i]->args.igemm;
+    plans[i]->kernel = t.ids[f16];
+    plans[i]->gx = cdiv(a.M, t.bm);
+    plans[i]->gy = cdiv(a.N, t.bn);
+  }
+}
+
+bool tile_choice_open(int kernel_id) {
+  return std::any_of(kTileKernels, kTileKernels + kTileKernelCount,
+                     [&](const TileKernel &t) { return t.ids[0] == kernel_id || t.ids[1] == kernel_id; });
+}
 
 int plan_op(const opara_op_desc &op, const void *const *in, int kind, KernelPlan *out) {
   std::memset(out, 0, sizeof *out);

@@ -139,7 +139,6 @@ extern "C" int opara_build_dag(const opara_op_desc *ops, int32_t n_ops, void *co
     // ---- kernel plan + demand record per operator
     g->plan.resize(n_ops);
     g->plan_persist.resize(n_ops);
-    g->plan_group.resize(n_ops);
     g->dem.resize(n_ops);
     for (int v = 0; v < n_ops; ++v) {
       const opara_op_desc &op = g->ops[v];
@@ -151,9 +150,8 @@ extern "C" int opara_build_dag(const opara_op_desc *ops, int32_t n_ops, void *co
       }
       rc = plan_op(op, in, kPlanGraph, &g->plan[v]);
       if (rc == OPARA_OK) rc = plan_op(op, in, kPlanPersistent, &g->plan_persist[v]);
-      if (rc == OPARA_OK) rc = plan_op(op, in, kPlanGroup, &g->plan_group[v]);
       if (rc != OPARA_OK) { delete g; return rc; }
-      g->plan[v].tag = g->plan_persist[v].tag = g->plan_group[v].tag = v;
+      g->plan[v].tag = g->plan_persist[v].tag = v;
       const KernelPlan &p = g->plan[v];
       const KernelResource &r = kKernelResources[p.kernel];
       opara_demand &d = g->dem[v];
