@@ -36,12 +36,15 @@ struct PoolArgs {
   int32_t H, W, C, Ho, Wo, kh, kw, sh, sw, ph, pw;
   int32_t is_avg;
   int32_t B;                    // images
+  uint32_t items;               // output pixels x channel chunks; 0: more than 32-bit byte offsets reach
+  uint32_t div_cch, div_Wo, div_HoWo;   // reciprocals for fast_div
 };
 
 struct GapArgs {
   const void *x;
   void *y;
   int32_t HW, C;              // per image; blockIdx.y is the image
+  int32_t vec;                // 16-byte chunks, two threads per pixel (1 << kGapShare)
 };
 
 struct RowArgs {               // LayerNorm / softmax over rows of the summed inputs
@@ -62,6 +65,7 @@ struct ConcatArgs {
   const void *in[8];
   void *y;
   int32_t cols[8], col_off[8];
+  uint32_t div_cols[8];         // reciprocals of the chunks per row
   int32_t n_in, rows, out_cols;
 };
 
@@ -187,5 +191,7 @@ constexpr int kRowGroupWave = 64;     // threads cooperating on one row (wave va
 constexpr int kRowGroupBlock = 256;   // block variant
 constexpr int kRowCacheChunks = 4;    // 16-byte chunks a thread keeps in registers
 constexpr int kGemvMaxM = 4;
+constexpr int kGapShare = 1;          // global average: log2 of the threads that share a pixel (vector form)
+constexpr int kGapVecMinPixels = 128; // ... taken from this many pixels on
 
 }  // namespace opara
