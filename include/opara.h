@@ -508,7 +508,11 @@ int opara_run_persistent_noalloc(opara_dag *g, void *hip_stream, uint32_t *error
  * every node (host int32[n_nodes]: a kernel id of the kernel table for a single operator,
  * OPARA_GROUP_KERNEL_STREAM / _LIGHT / _HEAVY for a group node: the group kernel that holds
  * the bodies with at most 64 vector registers, at most 128, or all bodies); each may be
- * NULL.  Operators that share a node run concurrently inside one kernel.
+ * NULL.  Operators that share a node run concurrently inside one kernel.  An operator that is
+ * alone in its wave and consumes the only operator of the wave before may be computed by that
+ * operator's kernel (scores, softmax and context of an attention); it keeps a node of its own,
+ * which launches nothing: opara_fused_time_nodes reports 0 for it and opara_exec_info does not
+ * count it.  Executors captured with the operator timeline on run every operator by itself.
  */
 enum { OPARA_GROUP_KERNEL_LIGHT = -1, OPARA_GROUP_KERNEL_HEAVY = -2, OPARA_GROUP_KERNEL_STREAM = -3 };
 int opara_fused_plan(const opara_exec *e, int32_t *node_of, int32_t *n_nodes, int32_t *node_kernel);

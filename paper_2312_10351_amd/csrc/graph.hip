@@ -33,7 +33,8 @@ struct opara_exec {
   struct FusedNode {
     bool is_group = false, f16 = false;
     int flavor = 0;                      // group kernel flavour: 0 stream, 1 light, 2 heavy
-    int32_t op = -1;                     // single operator (ordinary kernel of the graph executors' plan)
+    opara::KernelPlan plan;              // single operator, or the first of several that share a kernel
+    bool launches = true;                // false: computed by the kernel of an earlier node
     uint32_t blocks = 0, lds = 0;
     opara::GroupArgs ga;                 // group: the launch record
   };
@@ -172,7 +173,9 @@ hipError_t assemble_parallel(const opara_dag *g, const std::vector<uint8_t> &kee
 // Fused executor: the launch queue is cut into waves (every operator whose predecessors lie
 // in earlier waves, in queue order); a wave of one operator is an ordinary kernel node with
 // the graph executors' kernel, a wave of several becomes group nodes (one kernel whose grid
-// is the sum of the members' grids); all nodes form one chain.
+// is the sum of the members' grids); all nodes form one chain.  Operators that share a kernel
+// with the one before them (find_merges) keep a node of their own that launches nothing; with
+// the operator timeline on, every operator runs by itself and leaves its stamps.
 int capture_fused(opara_dag *g, opara_exec **out) {
   if (g->order.empty()) { set_error("opara_capture: call opara_order_launch first"); return OPARA_ESTATE; }
   const int32_t n = g->n;
@@ -185,6 +188,10 @@ int capture_fused(opara_dag *g, opara_exec **out) {
   for (int32_t v = 0; v < n; ++v) indeg[v] = g->pred_off[v + 1] - g->pred_off[v];
   uint32_t max_lds = 0;
   int32_t placed = 0;
+  const std::vector<Merge> merges = current_op_trace() ? std::vector<Merge>() : find_merges(g);
+  std::vector<const Merge *> merge_of(n, nullptr);
+  for (const Merge &m : merges)
+    for (int32_t i = 0; i < m.count; ++i) merge_of[m.ops[i]] = &m;
   std::vector<KernelPlan> plan(g->plan);           // a wave's contractions get their tile shapes together
   while (placed < n) {
     wave.clear();
@@ -211,7 +218,9 @@ int capture_fused(opara_dag *g, opara_exec **out) {
       if (members.empty()) return;
       opara_exec::FusedNode node;
       if (members.size() == 1) {
-        node.op = members[0];
+        const Merge *m = merge_of[members[0]];
+        node.plan = m ? m->plan : g->plan[members[0]];
+        node.launches = !m || m->ops[0] == members[0];
       } else {
         node.is_group = true;
         node.flavor = 0;
@@ -310,14 +319,15 @@ int capture_fused(opara_dag *g, opara_exec **out) {
     HIP_TRY(group_prepare(std::max(max_lds, 16u)));
     HIP_TRY(hipGraphCreate(&e->graph, 0));
     for (const opara_exec::FusedNode &fn : e->fused) {
+      if (!fn.launches) continue;
+      ++e->n_nodes;
       if (fn.is_group)
         HIP_TRY(add_group_node(e->graph, fn.f16, fn.flavor, fn.ga, fn.blocks, fn.lds, last ? &last : nullptr, last ? 1 : 0, &node));
       else
-        HIP_TRY(add_plan_node(e->graph, g->plan[fn.op], last ? &last : nullptr, last ? 1 : 0, &node));
+        HIP_TRY(add_plan_node(e->graph, fn.plan, last ? &last : nullptr, last ? 1 : 0, &node));
       last = node;
     }
     HIP_TRY(hipGraphInstantiate(&e->exec, e->graph, nullptr, nullptr, 0));
-    e->n_nodes = (int32_t)e->fused.size();
     e->n_edges = e->n_nodes - 1;
   }
   *out = e;
@@ -1056,7 +1066,7 @@ extern "C" int opara_fused_plan(const opara_exec *e, int32_t *node_of, int32_t *
   if (node_kernel)
     for (size_t i = 0; i < e->fused.size(); ++i) {
       const opara_exec::FusedNode &fn = e->fused[i];
-      node_kernel[i] = fn.is_group ? (fn.flavor == 0 ? OPARA_GROUP_KERNEL_STREAM : fn.flavor == 1 ? OPARA_GROUP_KERNEL_LIGHT : OPARA_GROUP_KERNEL_HEAVY) : e->dag->plan[fn.op].kernel;
+      node_kernel[i] = fn.is_group ? (fn.flavor == 0 ? OPARA_GROUP_KERNEL_STREAM : fn.flavor == 1 ? OPARA_GROUP_KERNEL_LIGHT : OPARA_GROUP_KERNEL_HEAVY) : fn.plan.kernel;
     }
   return OPARA_OK;
 }
@@ -1070,10 +1080,12 @@ extern "C" int opara_fused_time_nodes(opara_exec *e, void *hip_stream, int32_t l
   for (size_t i = 0; i < e->fused.size(); ++i) {
     const opara_exec::FusedNode &fn = e->fused[i];
     float ms = 0.f;
+    us[i] = 0.f;
+    if (!fn.launches) continue;
     for (int32_t k = -2; k < launches; ++k) {       // two untimed launches first
       if (k == 0) HIP_TRY(hipEventRecord(t0, st));
       if (fn.is_group) HIP_TRY(launch_group(fn.f16, fn.flavor, fn.ga, fn.blocks, fn.lds, st));
-      else HIP_TRY(launch_plan(e->dag->plan[fn.op], st));
+      else HIP_TRY(launch_plan(fn.plan, st));
     }
     HIP_TRY(hipEventRecord(t1, st));
     HIP_TRY(hipEventSynchronize(t1));

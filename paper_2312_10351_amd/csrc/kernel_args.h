@@ -69,6 +69,18 @@ struct ConcatArgs {
   int32_t n_in, rows, out_cols;
 };
 
+// Scores, softmax and context of one attention in one launch (fused executor); z: head.
+//   s[z] = alpha_s * q[z] . k[z]^T,  p[z] = softmax(s[z]),  y[z] = alpha_c * p[z] . v[z]
+struct AttnArgs {
+  const void *q, *k, *v;
+  void *s, *p, *y;              // s, p: [heads][M][N] without gaps
+  int64_t q_bs, k_bs, v_bs, y_bs, ldy;
+  int32_t ldq, ldk, ldv;
+  int32_t M, N, D, D2;          // query rows, key rows, width of a row of q and k, of v
+  uint32_t q_bytes, k_bytes, v_bytes;   // one head
+  float alpha_s, alpha_c;
+};
+
 // X(name, ArgsType).  Order defines kernel ids.
 #define OPARA_KERNEL_LIST(X)            \
   X(igemm_f16_t128x64, IgemmArgs)       \
@@ -120,7 +132,8 @@ struct ConcatArgs {
   X(igemm_f16_direct4s, IgemmArgs)      \
   X(igemm_f16_quad4s, IgemmArgs)        \
   X(igemm_f32_direct4s, IgemmArgs)      \
-  X(igemm_f32_quad4s, IgemmArgs)
+  X(igemm_f32_quad4s, IgemmArgs)        \
+  X(attention_f16, AttnArgs)
 
 enum KernelId : int32_t {
 #define X(name, T) K_##name,
@@ -136,6 +149,7 @@ union KernelArgs {
   RowArgs row;
   EltArgs elt;
   ConcatArgs concat;
+  AttnArgs attn;
 };
 
 // One planned launch: which kernel, its grid and its arguments.
@@ -190,6 +204,8 @@ constexpr int kSmallTileMaxTiles32 = 100;   // at most this many 32 x 32 tiles: 
 constexpr int kRowGroupWave = 64;     // threads cooperating on one row (wave variant)
 constexpr int kRowGroupBlock = 256;   // block variant
 constexpr int kRowCacheChunks = 4;    // 16-byte chunks a thread keeps in registers
+constexpr int kAttnMaxCols = 512;     // attention kernel: one 16-byte chunk of scores per lane of a wavefront
+constexpr int kAttnMaxWidth = 64;     // ... one 128-byte line per row of q, k and v
 constexpr int kGemvMaxM = 4;
 constexpr int kGapShare = 1;          // global average: log2 of the threads that share a pixel (vector form)
 constexpr int kGapVecMinPixels = 128; // ... taken from this many pixels on

@@ -1371,6 +1371,8 @@ __device__ __forceinline__ void concat_body(const AR &a, const Blk &b, unsigned 
   else stg<CS, T>(dst, ldg<T>(src));
 }
 
+#include "attention.h"
+
 }  // namespace opara
 
 using namespace opara;
@@ -1487,6 +1489,8 @@ KDEF(igemm_f16_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<half_
 KDEF2(igemm_f16_quad4s, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<half_t, 1, 1, 2, 0>(a, b, lds)))
 KDEF(igemm_f32_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 1, 1>(a, b, lds)))
 KDEF2(igemm_f32_quad4s, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<float, 1, 1, 2, 0>(a, b, lds)))
+
+KDEF2(attention_f16, 256, 3, kLdsAttention, AttnArgs, (attention_body(a, b, lds)))
 
 // The 256-thread bodies by the vector registers they need (see the group kernels below):
 // X(kernel name, argument record, body call); T / tn: element type, C: access policy.
@@ -2061,6 +2065,7 @@ template <> const GapArgs &arg_of<GapArgs>(const KernelArgs &u) { return u.gap; 
 template <> const RowArgs &arg_of<RowArgs>(const KernelArgs &u) { return u.row; }
 template <> const EltArgs &arg_of<EltArgs>(const KernelArgs &u) { return u.elt; }
 template <> const ConcatArgs &arg_of<ConcatArgs>(const KernelArgs &u) { return u.concat; }
+template <> const AttnArgs &arg_of<AttnArgs>(const KernelArgs &u) { return u.attn; }
 }  // namespace
 
 hipError_t launch_plan(const KernelPlan &p, hipStream_t s) {
@@ -2153,6 +2158,7 @@ int group_flavor(int id) {
     HEAVY_BODIES(FCASE, half_t, f16, 0) HEAVY_BODIES(FCASE, float, f32, 0) return 2;
     LIGHT_BODIES(FCASE, half_t, f16, 0) LIGHT_BODIES(FCASE, float, f32, 0) return 1;
 #undef FCASE
+    case K_attention_f16: return -1;     // runs as a launch of its own
     default: return id >= 0 && id < K_COUNT ? 0 : -1;
   }
 }

@@ -1,0 +1,89 @@
+// Operators that share a kernel in the fused executor (host only, no HIP calls).
+//
+// A node of the executor's chain costs 2.3 us whatever it does, so a wave whose only operator
+// consumes the only operator of the wave before is worth no launch of its own when the
+// producer's kernel can go on to compute it.  Every operator's result is still written, and
+// the consumer computes from the stored (rounded) values: results do not change.
+//
+// An operator that is alone in its wave runs when everything of earlier waves is complete,
+// and the operators of a merge are alone in theirs: whatever else they read is ready when the
+// first of them starts.  Buffers must not overlap (a caller may have let the result of a later
+// operator replace what an earlier one reads); merges with overlapping buffers are not made.
+#include <algorithm>
+#include <cstring>
+#include "opara_internal.h"
+
+namespace opara {
+namespace {
+
+struct Range { uintptr_t begin, end; };
+Range range_of(const void *p, int64_t bytes) { return {(uintptr_t)p, (uintptr_t)p + (uintptr_t)bytes}; }
+bool disjoint(const Range &a, const Range &b) { return a.end <= b.begin || b.end <= a.begin; }
+bool disjoint(const Range &a, std::initializer_list<Range> l) {
+  return std::all_of(l.begin(), l.end(), [&](const Range &b) { return disjoint(a, b); });
+}
+bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
+bool vectors(const void *p, int64_t ld, int64_t bs) { return aligned16(p) && ld % 8 == 0 && bs % 8 == 0; }
+
+// scores (batched product) -> softmax -> context (batched product with a [K][N] operand).
+bool merge_attention(const opara_dag *g, int32_t u, int32_t v, int32_t w, Merge *out) {
+  const opara_op_desc &du = g->ops[u], &dv = g->ops[v], &dw = g->ops[w];
+  if (du.op_type != OPARA_BGEMM || dv.op_type != OPARA_SOFTMAX || dw.op_type != OPARA_BGEMM) return false;
+  if (du.dtype != OPARA_F16 || dv.dtype != OPARA_F16 || dw.dtype != OPARA_F16) return false;
+  if (dv.n_inputs != 1 || dv.inputs[0] != u || dw.inputs[0] != v || dw.inputs[1] == u || dw.inputs[1] == v) return false;
+  const IgemmArgs &s = g->plan[u].args.igemm, &c = g->plan[w].args.igemm;
+  const RowArgs &r = g->plan[v].args.row;
+  const int64_t heads = g->plan[u].gz, rows = heads * s.M, cells = (int64_t)s.M * s.N;
+  if (s.b_kmajor || s.relu || s.bias || !c.b_kmajor || c.relu || c.bias) return false;
+  if (s.K > kAttnMaxWidth || s.K % 8 || s.N > kAttnMaxCols || c.N > kAttnMaxWidth || c.N % 8) return false;
+  if (!vectors(s.x, s.lda, s.a_bs) || !vectors(s.w, s.ldb, s.b_bs) || !vectors(c.w, c.ldb, c.b_bs)) return false;
+  if (s.ldy != s.N || s.y_bs != cells || r.in[0] != s.y || r.rows != rows || r.cols != s.N) return false;
+  if (c.x != r.y || (int64_t)g->plan[w].gz != heads || c.M != s.M || c.K != s.N || c.lda != s.N || c.a_bs != cells) return false;
+  const int64_t q_bytes = 2 * ((int64_t)(s.M - 1) * s.lda + s.K), k_bytes = 2 * ((int64_t)(s.N - 1) * s.ldb + s.K),
+                v_bytes = 2 * ((int64_t)(c.K - 1) * c.ldb + c.N);
+  if (std::max({q_bytes, k_bytes, v_bytes}) >= (int64_t)kOperandMaxBytes) return false;
+  const Range q = range_of(s.x, 2 * (heads - 1) * s.a_bs + q_bytes), k = range_of(s.w, 2 * (heads - 1) * s.b_bs + k_bytes),
+              vv = range_of(c.w, 2 * (heads - 1) * c.b_bs + v_bytes), sc = range_of(s.y, 2 * heads * cells),
+              pr = range_of(r.y, 2 * heads * cells),
+              y = range_of(c.y, 2 * ((heads - 1) * c.y_bs + (int64_t)(c.M - 1) * c.ldy + c.N));
+  if (!disjoint(sc, vv) || !disjoint(pr, {q, k, vv, sc}) || !disjoint(y, {q, k, vv, sc, pr})) return false;
+  out->count = 3;
+  out->ops[0] = u; out->ops[1] = v; out->ops[2] = w;
+  KernelPlan &p = out->plan;
+  std::memset(&p, 0, sizeof p);
+  p.kernel = K_attention_f16;
+  p.gx = (uint32_t)((s.M + 15) / 16); p.gy = (uint32_t)heads; p.gz = 1; p.block = 256; p.tag = u;
+  AttnArgs &a = p.args.attn;
+  a.q = s.x; a.k = s.w; a.v = c.w; a.s = s.y; a.p = r.y; a.y = c.y;
+  a.q_bs = s.a_bs; a.k_bs = s.b_bs; a.v_bs = c.b_bs; a.y_bs = c.y_bs; a.ldy = c.ldy;
+  a.ldq = (int32_t)s.lda; a.ldk = (int32_t)s.ldb; a.ldv = (int32_t)c.ldb;
+  a.M = s.M; a.N = s.N; a.D = s.K; a.D2 = c.N;
+  a.q_bytes = (uint32_t)q_bytes; a.k_bytes = (uint32_t)k_bytes; a.v_bytes = (uint32_t)v_bytes;
+  a.alpha_s = s.alpha; a.alpha_c = c.alpha;
+  return true;
+}
+
+}  // namespace
+
+std::vector<Merge> find_merges(const opara_dag *g) {
+  std::vector<int32_t> wave(g->n, 0), alone;        // alone[w]: the only operator of wave w, -1 if there are more
+  for (int32_t i = 0; i < g->n; ++i) {
+    const int32_t v = g->topo[i];
+    for (int32_t j = g->pred_off[v]; j < g->pred_off[v + 1]; ++j) wave[v] = std::max(wave[v], wave[g->pred[j]] + 1);
+    if (wave[v] >= (int32_t)alone.size()) alone.resize(wave[v] + 1, -2);
+    alone[wave[v]] = alone[wave[v]] == -2 ? v : -1;
+  }
+  std::vector<Merge> found;
+  const int32_t waves = (int32_t)alone.size();
+  for (int32_t w = 0; w + 1 < waves; ++w) {
+    Merge m;
+    if (alone[w] < 0 || alone[w + 1] < 0) continue;
+    if (w + 2 < waves && alone[w + 2] >= 0 && merge_attention(g, alone[w], alone[w + 1], alone[w + 2], &m)) {
+      found.push_back(m);
+      w += m.count - 1;
+    }
+  }
+  return found;
+}
+
+}  // namespace opara

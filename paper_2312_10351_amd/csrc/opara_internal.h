@@ -58,6 +58,11 @@ int sync_keep_mask(const opara_dag *g, std::vector<uint8_t> *keep);
 enum { kPlanGraph = 0, kPlanPersistent = 1 };
 int plan_op(const opara_op_desc &op, const void *const *in, int kind, KernelPlan *out);
 
+// Operators of consecutive waves that the fused executor runs as one kernel, each
+// the only operator of its wave; the kernel is launched in the place of the first.
+struct Merge { int32_t count, ops[3]; KernelPlan plan; };
+std::vector<Merge> find_merges(const opara_dag *g);
+
 // Tile shapes of contractions that run together; only for kernels whose shape is open.
 bool tile_choice_open(int kernel_id);
 void choose_tiles(KernelPlan *const *plans, int n);

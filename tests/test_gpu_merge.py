@@ -1,0 +1,93 @@
+"""Operators that the fused executor runs as one kernel, at the edges of what that kernel takes:
+against the oracle, every operator's result, and refused where buffers overlap."""
+import numpy as np
+import pytest
+
+from oracle import executor
+from workloads import Builder
+from paper_2312_10351_amd import binding as B
+from paper_2312_10351_amd.runtime import Session
+from util import compare_all
+
+pytestmark = pytest.mark.gpu
+
+
+def run_fused(wl, launches, reps=2):
+    """Replays the fused executor on clean buffers; it must launch `launches` kernels."""
+    ref = executor.run_dag(wl)
+    s = Session(wl)
+    try:
+        exe = s.capture(B.FUSED)
+        assert B.opara_exec_info(exe) == (launches, launches - 1)
+        node_of, n = B.opara_fused_plan(exe, len(wl.ops))
+        assert n == B.opara_wave_of(s.dag)[1]
+        us = B.opara_fused_time_nodes(exe, s.make_streams(1).handles[0], 2)
+        assert sum(u > 0 for u in us) == launches
+        for _ in range(reps):
+            for t in s.out_dev:
+                t.fill_(float("nan"))
+            s.replay(exe)
+            assert not compare_all(s, ref)
+    finally:
+        s.close()
+
+
+def attention(heads, seq, d, dtype):
+    b = Builder("attention", dtype)
+    q, k, v = (b.ext((seq, heads * d)) for _ in range(3))
+    att = dict(heads=heads, seq=seq, dhead=d)
+    s = b.add("bgemm", [q, k], [(seq, heads * d)] * 2, (heads, seq, seq), dict(mode="qk", alpha=1.0 / d ** 0.5, **att))
+    p = b.rowwise("softmax", [s], heads * seq, seq)
+    b.add("bgemm", [p, v], [(heads, seq, seq), (seq, heads * d)], (seq, heads * d), dict(mode="pv", alpha=1.0, **att))
+    return b.build(23)
+
+
+@pytest.mark.parametrize("heads,seq,d", [(1, 1, 8), (2, 15, 64), (12, 16, 64), (3, 33, 24), (12, 128, 64), (3, 77, 64), (2, 129, 56),
+                                         (5, 256, 40), (2, 300, 64), (1, 511, 8), (4, 512, 64)])
+def test_attention(heads, seq, d):
+    run_fused(attention(heads, seq, d, "f16"), 1)
+
+
+@pytest.mark.parametrize("heads,seq,d,dtype", [(2, 520, 64, "f16"), (2, 64, 72, "f16"), (3, 48, 20, "f16"), (2, 64, 64, "f32")])
+def test_attention_outside_its_range_stays_three_launches(heads, seq, d, dtype):
+    run_fused(attention(heads, seq, d, dtype), 3)
+
+
+def test_attention_with_masked_scores():
+    """Rows that hold minus infinity and the type's lowest value."""
+    wl = attention(2, 64, 64, "f16")
+    wl.ext_inputs[0][3] = 60000.0
+    wl.ext_inputs[1][:, 5] = -60000.0
+    s = Session(wl)
+    try:
+        got = []
+        for mode in (B.SEQUENTIAL, B.FUSED):
+            for t in s.out_dev:
+                t.zero_()
+            s.replay(s.capture(mode))
+            got.append([s.output(v).astype(np.float64) for v in range(3)])
+        for a, b in zip(*got):
+            assert (np.isnan(a) == np.isnan(b)).all()
+            ok = np.isfinite(a)
+            assert (np.isfinite(b) == ok).all() and np.allclose(a[ok], b[ok], rtol=2e-3, atol=2e-3)
+    finally:
+        s.close()
+
+
+def test_overlapping_buffers_are_not_merged():
+    wl = attention(2, 64, 64, "f16")
+    ref = executor.run_dag(wl)
+    s = Session(wl)
+    try:
+        s.descs[2].out = s.ext_dev[0].data_ptr()         # the context replaces the queries
+        dag = B.opara_build_dag(s.descs, [t.data_ptr() for t in s.ext_dev])
+        B.opara_order_launch(dag)
+        exe = B.opara_capture(dag, s.make_streams(1).handles[:1], B.FUSED)
+        assert B.opara_exec_info(exe) == (3, 2)
+        s.replay(exe)
+        got = s.ext_dev[0].cpu().numpy().astype(np.float64)
+        assert np.abs(got - ref[2].astype(np.float64)).max() < 1e-2
+        B.opara_exec_destroy(exe)
+        B.opara_dag_destroy(dag)
+    finally:
+        s.close()
