@@ -133,7 +133,21 @@ struct AttnArgs {
   X(igemm_f16_quad4s, IgemmArgs)        \
   X(igemm_f32_direct4s, IgemmArgs)      \
   X(igemm_f32_quad4s, IgemmArgs)        \
-  X(attention_f16, AttnArgs)
+  X(attention_f16, AttnArgs)            \
+  X(igemm_f16_quad4s_tail, IgemmArgs) \
+  X(igemm_f16_quad4_tail, IgemmArgs) \
+  X(igemm_f16_quad64x4_tail, IgemmArgs) \
+  X(igemm_f16_quad64x64_tail, IgemmArgs) \
+  X(igemm_f16_tile64x64_tail, IgemmArgs) \
+  X(igemm_f16_t128x64_tail, IgemmArgs) \
+  X(igemm_f16_tile128x128_tail, IgemmArgs) \
+  X(igemm_f32_quad4s_tail, IgemmArgs) \
+  X(igemm_f32_quad4_tail, IgemmArgs) \
+  X(igemm_f32_quad64x4_tail, IgemmArgs) \
+  X(igemm_f32_quad64x64_tail, IgemmArgs) \
+  X(igemm_f32_tile64x64_tail, IgemmArgs) \
+  X(igemm_f32_t128x64_tail, IgemmArgs) \
+  X(igemm_f32_tile128x128_tail, IgemmArgs)
 
 enum KernelId : int32_t {
 #define X(name, T) K_##name,
@@ -152,6 +166,15 @@ union KernelArgs {
   AttnArgs attn;
 };
 
+// An element-wise operator computed by the contraction that produces one of its inputs (fused
+// executor): y = f(sum of n_in inputs), all without gaps and of the contraction's size.
+struct TailArgs {
+  const void *in[2];            // the inputs that are not the contraction's result, in order
+  void *y;
+  int32_t n_in, self, op;       // self: place of the contraction's result among the inputs; op as in EltArgs
+  int32_t reserved;
+};
+
 // One planned launch: which kernel, its grid and its arguments.
 struct KernelPlan {
   int32_t kernel;
@@ -159,6 +182,7 @@ struct KernelPlan {
   uint32_t block;
   int32_t tag;                  // operator id: second kernel argument, slot of the operator timeline
   KernelArgs args;
+  TailArgs tail;                // contractions with a tail only
 };
 
 // A group node: up to kGroupMaxOps mutually independent operators launched as ONE kernel

@@ -741,6 +741,74 @@ __device__ __forceinline__ void store4(const AR &a, T *dst, floatx4 v, int n) {
   }
 }
 
+// erf by the rational-times-exponential formula of Abramowitz & Stegun 7.1.26 (absolute error
+// below 1.5e-7): one reciprocal, one exponential and five multiply-adds, against several
+// dozen instructions of the correctly rounded library routine, which made GELU ALU-bound
+// (128 MB: 60 us against 38 us for ReLU).  Used where the result is stored as fp16, whose
+// spacing (2^-11 relative) is three orders of magnitude coarser than that error.
+__device__ __forceinline__ float erf_as(float x) {
+  const float ax = fabsf(x);
+  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * ax);
+  const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
+  const float r = 1.0f - poly * __expf(-ax * ax);
+  return x < 0.f ? -r : r;
+}
+
+template <typename T> __device__ __forceinline__ float elt_apply(int op, float x) {
+  if (op == 1) return fmaxf(x, 0.f);
+  if (op == 2) {
+    const float z = x * 0.70710678118654752f;
+    return 0.5f * x * (1.0f + (std::is_same<T, half_t>::value ? erf_as(z) : erff(z)));
+  }
+  return x;
+}
+
+// Tail of a contraction: an element-wise operator that reads its result (TailArgs), computed on
+// the values as they are stored.  Two launches less per transformer layer and half of a third;
+// an input other than the result is requested before the K walk, like the bias.
+// TAIL_MEASURED
+struct NoTail {};
+template <typename T, typename TL> struct Tail {
+  typedef typename Vec16<T>::quad Q;
+  static constexpr bool kOn = std::is_same<TL, TailArgs>::value;
+  __amdgpu_buffer_rsrc_t first;            // the first input that is not the result; empty without one (see BiasRow)
+  template <typename AR> __device__ __forceinline__ Tail(const AR &a, const TL &t) {
+    if constexpr (kOn)
+      first = __builtin_amdgcn_make_buffer_rsrc((void *)t.in[0], 0, t.n_in > 1 ? a.M * a.N * (int)sizeof(T) : 0, 0x00020000);
+  }
+  template <typename AR> __device__ __forceinline__ Q ahead(const AR &a, int m, int n) const {
+    if constexpr (kOn) {
+      const int at = (int)((uint32_t)(m * a.N + n) * (uint32_t)sizeof(T));
+      if constexpr (sizeof(T) == 2) return __builtin_bit_cast(Q, __builtin_amdgcn_raw_buffer_load_b64(first, at, 0, 0));
+      else return __builtin_bit_cast(Q, __builtin_amdgcn_raw_buffer_load_b128(first, at, 0, 0));
+    }
+    return Q{};
+  }
+  // v: four values of row m from column n on, before they are rounded; o: the first other input there.
+  template <typename AR>
+  static __device__ __forceinline__ void apply(const AR &a, const TL &t, floatx4 v, Q o, int m, int n) {
+    if constexpr (kOn) {
+      const int64_t at = (int64_t)m * a.N + n;
+      floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < t.n_in; ++q) {
+        Q x;
+        if (q == t.self) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = (T)v[e];
+        } else {
+          x = q - (q > t.self ? 1 : 0) == 0 ? o : *(const Q *)((const T *)t.in[1] + at);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += (float)x[e];
+      }
+      Q r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[e] = (T)elt_apply<T>(t.op, sum[e]);
+      *(Q *)((T *)t.y + at) = r;
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------------
 // Throughput-oriented contraction: BN columns x BM rows per workgroup of WN x WM
 // wavefronts, a ring of S stages in workgroup memory, S - 1 stages requested ahead, one
@@ -757,8 +825,8 @@ __device__ __forceinline__ void store4(const AR &a, T *dst, floatx4 v, int n) {
 // The rows of the weight operand are dealt to the fragments so that a lane's accumulators
 // are 4 * FN consecutive channels of one row (wide stores, whole lines per wavefront).
 // ---------------------------------------------------------------------------------
-template <typename T, int BN, int BM, int WN, int WM, int S, int COH, typename AR>
-__device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsigned char *lds) {
+template <typename T, int BN, int BM, int WN, int WM, int S, int COH, typename AR, typename TL = NoTail>
+__device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsigned char *lds, const TL &tail = TL{}) {
   typedef typename Vec16<T>::type V;
   constexpr int NW = WN * WM, STAGE = (BN + BM) * 128;
   constexpr int FN = BN / WN / 16, FM = BM / WM / 16;
@@ -832,6 +900,17 @@ __device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsig
   }
 
   typedef V VU __attribute__((aligned(sizeof(T))));
+  typedef Tail<T, TL> After;
+  typename After::Q ov[FN][FM];                        // what the tail adds, all requested before the first store
+  if constexpr (After::kOn) {
+    const After after(a, tail);
+    if (tail.n_in > 1) {
+#pragma unroll
+      for (int j = 0; j < FM; ++j)
+#pragma unroll
+        for (int i = 0; i < FN; ++i) ov[i][j] = after.ahead(a, m0 + wm0 + j * 16 + r16, nrun + i * 4);
+    }
+  }
 #pragma unroll
   for (int j = 0; j < FM; ++j) {
     const int m = m0 + wm0 + j * 16 + r16;
@@ -844,6 +923,8 @@ __device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsig
       if constexpr (VecRun<T>::N == 2) {               // eight halves: one 16-byte store
         const floatx4 lo = finish4<T>(a, acc[i][j], bv[i], m, n);
         const floatx4 hi = finish4<T>(a, acc[i + 1][j], bv[i + 1], m, n + 4);
+        After::apply(a, tail, lo, ov[i][j], m, n);
+        if (n + 4 < a.N) After::apply(a, tail, hi, ov[i + 1][j], m, n + 4);
         if (n + 7 < a.N) {
           V o;
 #pragma unroll
@@ -855,7 +936,9 @@ __device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsig
           store4<T, CS>(a, dst + i * 4 + 4, hi, n + 4);
         }
       } else {
-        store4<T, CS>(a, dst + i * 4, finish4<T>(a, acc[i][j], bv[i], m, n), n);
+        const floatx4 v = finish4<T>(a, acc[i][j], bv[i], m, n);
+        After::apply(a, tail, v, ov[i][j], m, n);
+        store4<T, CS>(a, dst + i * 4, v, n);
       }
     }
   }
@@ -874,8 +957,8 @@ __device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsig
 // 256 x 2048 x 2048 13.5 -> 6.8 (64 x 32), 64 x 4096 x 4096 13.6 -> 8.2 (32 x 32),
 // 256 x 4096 x 4096 30.3 -> 15.8 (64 x 64).
 // ---------------------------------------------------------------------------------
-template <typename T, int NI, int NJ, int S, int COH, typename AR>
-__device__ __forceinline__ void igemm_split_body(const AR &a, const Blk &b, unsigned char *lds) {
+template <typename T, int NI, int NJ, int S, int COH, typename AR, typename TL = NoTail>
+__device__ __forceinline__ void igemm_split_body(const AR &a, const Blk &b, unsigned char *lds, const TL &tail = TL{}) {
   typedef typename Vec16<T>::type V;
   constexpr int WAVES = 4, BN = 16 * NI, BM = 16 * NJ, STEP = (BN + BM) * 128;
   constexpr int PITCH = BN + 4;            // floats per row of a partial tile
@@ -912,9 +995,15 @@ __device__ __forceinline__ void igemm_split_body(const AR &a, const Blk &b, unsi
   // Bias of this thread's output pieces, requested before the K walk.
   constexpr int PG = 4 * NI, PIECES = (BM * PG + 255) / 256;   // four-channel pieces per row, per thread
   const BiasRow bias(a);
+  const Tail<T, TL> after(a, tail);
   floatx4 bv[PIECES];
+  typename Tail<T, TL>::Q tv[PIECES];
 #pragma unroll
-  for (int p = 0; p < PIECES; ++p) bv[p] = bias.at(n0 + ((t + p * 256) % PG) * 4);
+  for (int p = 0; p < PIECES; ++p) {
+    const int idx = t + p * 256, n = n0 + (idx % PG) * 4;
+    bv[p] = bias.at(n);
+    tv[p] = after.ahead(a, m0 + idx / PG, n);
+  }
   int slot = 0;
 #pragma nounroll
   for (int kt = k_begin; kt < k_end; ++kt) {
@@ -954,7 +1043,9 @@ __device__ __forceinline__ void igemm_split_body(const AR &a, const Blk &b, unsi
     floatx4 sum = *(const floatx4 *)at;
 #pragma unroll
     for (int q = 1; q < WAVES; ++q) sum += *(const floatx4 *)(at + q * RING);
-    store4<T, CS>(a, y + (int64_t)m * a.ldy + n, finish4<T>(a, sum, bv[p], m, n), n);
+    const floatx4 v = finish4<T>(a, sum, bv[p], m, n);
+    Tail<T, TL>::apply(a, tail, v, tv[p], m, n);
+    store4<T, CS>(a, y + (int64_t)m * a.ldy + n, v, n);
   }
 }
 
@@ -1310,28 +1401,6 @@ __device__ __forceinline__ void row_generic_body(const AR &a, const Blk &b, unsi
 // ---------------------------------------------------------------------------------
 // Element-wise f(sum of inputs) and channel/column concatenation.
 // ---------------------------------------------------------------------------------
-// erf by the rational-times-exponential formula of Abramowitz & Stegun 7.1.26 (absolute error
-// below 1.5e-7): one reciprocal, one exponential and five multiply-adds, against several
-// dozen instructions of the correctly rounded library routine, which made GELU ALU-bound
-// (128 MB: 60 us against 38 us for ReLU).  Used where the result is stored as fp16, whose
-// spacing (2^-11 relative) is three orders of magnitude coarser than that error.
-__device__ __forceinline__ float erf_as(float x) {
-  const float ax = fabsf(x);
-  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * ax);
-  const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-  const float r = 1.0f - poly * __expf(-ax * ax);
-  return x < 0.f ? -r : r;
-}
-
-template <typename T> __device__ __forceinline__ float elt_apply(int op, float x) {
-  if (op == 1) return fmaxf(x, 0.f);
-  if (op == 2) {
-    const float z = x * 0.70710678118654752f;
-    return 0.5f * x * (1.0f + (std::is_same<T, half_t>::value ? erf_as(z) : erff(z)));
-  }
-  return x;
-}
-
 template <typename T, int VE, int COH, typename AR>
 __device__ __forceinline__ void elt_body(const AR &a, const Blk &b, unsigned char *lds) {
   constexpr bool CS = COH != 0;
@@ -1407,15 +1476,16 @@ __device__ __forceinline__ void op_trace_end(unsigned long long *tr, int tag, un
 __device__ __forceinline__ unsigned launch_lin() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
 __device__ __forceinline__ unsigned launch_total() { return gridDim.x * gridDim.y * gridDim.z; }
 
-// The arguments of a kernel span up to four cache lines, and the compiler reads them where it
+// The arguments of a kernel span up to five cache lines, and the compiler reads them where it
 // needs them: one memory round trip after another at the head of every workgroup.  Reading a
 // word of every line first, in one round, lets the later reads hit the scalar cache
 // (isolated 128 x 768 x 768 product: see igemm_split_body).
 template <int BYTES> __device__ __forceinline__ void touch_arguments() {
   typedef const uint32_t __attribute__((address_space(4))) *CW;
   const CW w = (CW)__builtin_amdgcn_kernarg_segment_ptr();
-  const uint32_t a = w[0], b = w[(BYTES > 64 ? 64 : 0) / 4], c = w[(BYTES > 128 ? 128 : 0) / 4], d = w[(BYTES - 4) / 4];
-  asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d));
+  const uint32_t a = w[0], b = w[(BYTES > 64 ? 64 : 0) / 4], c = w[(BYTES > 128 ? 128 : 0) / 4], d = w[(BYTES > 192 ? 192 : 0) / 4],
+                 e = w[(BYTES - 4) / 4];
+  asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d), "s"(e));
 }
 
 #define KDEF(name, threads, ldsb, Args, call)                                                    \
@@ -1438,23 +1508,47 @@ template <int BYTES> __device__ __forceinline__ void touch_arguments() {
     op_trace_end(trace, tag, t0, launch_lin(), launch_total());                                               \
   }
 
+// ... and a fourth argument: the element-wise operator that follows
+#define KDEFT(name, threads, waves_per_simd, ldsb, Args, call)                                                \
+  extern "C" __global__ void __launch_bounds__(threads, waves_per_simd) opara_k_##name(Args a, int32_t tag, unsigned long long *trace, \
+                                                                                       TailArgs tail) {       \
+    __shared__ __attribute__((aligned(16))) unsigned char lds[(ldsb) > 0 ? (ldsb) : 16];                      \
+    touch_arguments<sizeof(Args) + 16 + sizeof(TailArgs)>();                                                  \
+    const Blk b = launch_blk();                                                                               \
+    const unsigned long long t0 = op_trace_begin();                                                           \
+    call;                                                                                                     \
+    op_trace_end(trace, tag, t0, launch_lin(), launch_total());                                               \
+  }
+
 KDEF2(igemm_f16_t128x64, 256, 2, lds_tile(128, 64, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 64, 2, 2, 2, 0>(a, b, lds)))
+KDEFT(igemm_f16_t128x64_tail, 256, 2, lds_tile(128, 64, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 64, 2, 2, 2, 0>(a, b, lds, tail)))
 KDEF2(igemm_f16_tile64x64, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_body<half_t, 64, 64, 2, 2, 3, 0>(a, b, lds)))
+KDEFT(igemm_f16_tile64x64_tail, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_body<half_t, 64, 64, 2, 2, 3, 0>(a, b, lds, tail)))
 KDEF2(igemm_f16_tile128x128, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 128, 2, 2, 2, 0>(a, b, lds)))
+KDEFT(igemm_f16_tile128x128_tail, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 128, 2, 2, 2, 0>(a, b, lds, tail)))
 KDEF(igemm_f16_t64x64, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, 0>(a, b, lds)))
 KDEF(igemm_f16_direct4, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 2, 2>(a, b, lds)))
 KDEF2(igemm_f16_quad4, 256, 2, lds_split(2, 2, 2), IgemmArgs, (igemm_split_body<half_t, 2, 2, 2, 0>(a, b, lds)))
+KDEFT(igemm_f16_quad4_tail, 256, 2, lds_split(2, 2, 2), IgemmArgs, (igemm_split_body<half_t, 2, 2, 2, 0>(a, b, lds, tail)))
 KDEF2(igemm_f16_quad64x4, 256, 3, lds_split(4, 2, 1), IgemmArgs, (igemm_split_body<half_t, 4, 2, 1, 0>(a, b, lds)))
+KDEFT(igemm_f16_quad64x4_tail, 256, 3, lds_split(4, 2, 1), IgemmArgs, (igemm_split_body<half_t, 4, 2, 1, 0>(a, b, lds, tail)))
 KDEF2(igemm_f16_quad64x64, 256, 2, lds_split(4, 4, 1), IgemmArgs, (igemm_split_body<half_t, 4, 4, 1, 0>(a, b, lds)))
+KDEFT(igemm_f16_quad64x64_tail, 256, 2, lds_split(4, 4, 1), IgemmArgs, (igemm_split_body<half_t, 4, 4, 1, 0>(a, b, lds, tail)))
 KDEF(igemm_f16_t64x64_scalar, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, false, 0>(a, b, lds)))
 KDEF2(igemm_f32_t128x64, 256, 2, lds_tile(128, 64, 2), IgemmArgs, (igemm_tile_body<float, 128, 64, 2, 2, 2, 0>(a, b, lds)))
+KDEFT(igemm_f32_t128x64_tail, 256, 2, lds_tile(128, 64, 2), IgemmArgs, (igemm_tile_body<float, 128, 64, 2, 2, 2, 0>(a, b, lds, tail)))
 KDEF2(igemm_f32_tile64x64, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_body<float, 64, 64, 2, 2, 3, 0>(a, b, lds)))
+KDEFT(igemm_f32_tile64x64_tail, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_body<float, 64, 64, 2, 2, 3, 0>(a, b, lds, tail)))
 KDEF2(igemm_f32_tile128x128, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<float, 128, 128, 2, 2, 2, 0>(a, b, lds)))
+KDEFT(igemm_f32_tile128x128_tail, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<float, 128, 128, 2, 2, 2, 0>(a, b, lds, tail)))
 KDEF(igemm_f32_t64x64, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<float, 64, 64, 2, 2, true, 0>(a, b, lds)))
 KDEF(igemm_f32_direct4, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 2, 2>(a, b, lds)))
 KDEF2(igemm_f32_quad4, 256, 2, lds_split(2, 2, 2), IgemmArgs, (igemm_split_body<float, 2, 2, 2, 0>(a, b, lds)))
+KDEFT(igemm_f32_quad4_tail, 256, 2, lds_split(2, 2, 2), IgemmArgs, (igemm_split_body<float, 2, 2, 2, 0>(a, b, lds, tail)))
 KDEF2(igemm_f32_quad64x4, 256, 3, lds_split(4, 2, 1), IgemmArgs, (igemm_split_body<float, 4, 2, 1, 0>(a, b, lds)))
+KDEFT(igemm_f32_quad64x4_tail, 256, 3, lds_split(4, 2, 1), IgemmArgs, (igemm_split_body<float, 4, 2, 1, 0>(a, b, lds, tail)))
 KDEF2(igemm_f32_quad64x64, 256, 2, lds_split(4, 4, 1), IgemmArgs, (igemm_split_body<float, 4, 4, 1, 0>(a, b, lds)))
+KDEFT(igemm_f32_quad64x64_tail, 256, 2, lds_split(4, 4, 1), IgemmArgs, (igemm_split_body<float, 4, 4, 1, 0>(a, b, lds, tail)))
 KDEF(igemm_f32_t64x64_scalar, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<float, 64, 64, 2, 2, false, 0>(a, b, lds)))
 KDEF(gemv_f16, 256, kLdsNone, IgemmArgs, (gemv_body<half_t, 0>(a, b, lds)))
 KDEF(gemv_f32, 256, kLdsNone, IgemmArgs, (gemv_body<float, 0>(a, b, lds)))
@@ -1487,8 +1581,10 @@ KDEF(concat_f32_scalar, 256, kLdsNone, ConcatArgs, (concat_body<float, 1, 0>(a, 
 // 16 x 16 output tiles: four times the workgroups of the 32 x 32 forms, half the operand bytes per workgroup
 KDEF(igemm_f16_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 1, 1>(a, b, lds)))
 KDEF2(igemm_f16_quad4s, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<half_t, 1, 1, 2, 0>(a, b, lds)))
+KDEFT(igemm_f16_quad4s_tail, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<half_t, 1, 1, 2, 0>(a, b, lds, tail)))
 KDEF(igemm_f32_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 1, 1>(a, b, lds)))
 KDEF2(igemm_f32_quad4s, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<float, 1, 1, 2, 0>(a, b, lds)))
+KDEFT(igemm_f32_quad4s_tail, 256, 4, lds_split(1, 1, 2), IgemmArgs, (igemm_split_body<float, 1, 1, 2, 0>(a, b, lds, tail)))
 
 KDEF2(attention_f16, 256, 3, kLdsAttention, AttnArgs, (attention_body(a, b, lds)))
 
@@ -2058,64 +2154,49 @@ hipError_t launch_noop(hipStream_t s) {
 }
 
 namespace {
-template <typename A> const A &arg_of(const KernelArgs &u);
-template <> const IgemmArgs &arg_of<IgemmArgs>(const KernelArgs &u) { return u.igemm; }
-template <> const PoolArgs &arg_of<PoolArgs>(const KernelArgs &u) { return u.pool; }
-template <> const GapArgs &arg_of<GapArgs>(const KernelArgs &u) { return u.gap; }
-template <> const RowArgs &arg_of<RowArgs>(const KernelArgs &u) { return u.row; }
-template <> const EltArgs &arg_of<EltArgs>(const KernelArgs &u) { return u.elt; }
-template <> const ConcatArgs &arg_of<ConcatArgs>(const KernelArgs &u) { return u.concat; }
-template <> const AttnArgs &arg_of<AttnArgs>(const KernelArgs &u) { return u.attn; }
+// What every planned kernel is given: its by-value record at offset 0, the operator id, the
+// timeline buffer and the element-wise operator that follows; a kernel takes as many as it declares.
+struct PlanParams {
+  KernelArgs args;
+  int32_t tag;
+  unsigned long long *trace;
+  TailArgs tail;
+  void *ptr[4];
+  explicit PlanParams(const KernelPlan &p)
+      : args(p.args), tag(p.tag), trace(g_host_op_trace), tail(p.tail), ptr{&args, &tag, &trace, &tail} {}
+  PlanParams(const PlanParams &) = delete;
+};
+
+hipKernelNodeParams plan_node_params(const KernelPlan &p, PlanParams &params) {
+  hipKernelNodeParams np = {};
+  np.func = const_cast<void *>(kernel_symbol(p.kernel));
+  np.gridDim = dim3(p.gx, p.gy, p.gz);
+  np.blockDim = dim3(p.block);
+  np.sharedMemBytes = 0;
+  np.kernelParams = params.ptr;
+  np.extra = nullptr;
+  return np;
+}
 }  // namespace
 
 hipError_t launch_plan(const KernelPlan &p, hipStream_t s) {
-  const dim3 grid(p.gx, p.gy, p.gz), block(p.block);
-  switch (p.kernel) {
-#define X(name, A)                                                                     \
-  case K_##name:                                                                       \
-    hipLaunchKernelGGL(opara_k_##name, grid, block, 0, s, arg_of<A>(p.args), p.tag, g_host_op_trace);   \
-    break;
-    OPARA_KERNEL_LIST(X)
-#undef X
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  PlanParams params(p);
+  const void *func = kernel_symbol(p.kernel);
+  if (!func) return hipErrorInvalidValue;
+  return hipLaunchKernel(func, dim3(p.gx, p.gy, p.gz), dim3(p.block), params.ptr, 0, s);
 }
 
 hipError_t add_plan_node(hipGraph_t graph, const KernelPlan &p, const hipGraphNode_t *deps, size_t n_deps,
                          hipGraphNode_t *node) {
-  void *func = const_cast<void *>(kernel_symbol(p.kernel));
-  if (!func) return hipErrorInvalidValue;
-  KernelArgs args = p.args;              // every kernel takes one by-value record at offset 0, then the operator id
-  int32_t tag = p.tag;
-  unsigned long long *trace = g_host_op_trace;
-  void *kparams[3] = {&args, &tag, &trace};
-  hipKernelNodeParams np = {};
-  np.func = func;
-  np.gridDim = dim3(p.gx, p.gy, p.gz);
-  np.blockDim = dim3(p.block);
-  np.sharedMemBytes = 0;
-  np.kernelParams = kparams;
-  np.extra = nullptr;
-  return hipGraphAddKernelNode(node, graph, deps, n_deps, &np);
+  PlanParams params(p);
+  const hipKernelNodeParams np = plan_node_params(p, params);
+  return np.func ? hipGraphAddKernelNode(node, graph, deps, n_deps, &np) : hipErrorInvalidValue;
 }
 
 hipError_t set_exec_node_plan(hipGraphExec_t exec, hipGraphNode_t node, const KernelPlan &p) {
-  void *func = const_cast<void *>(kernel_symbol(p.kernel));
-  if (!func) return hipErrorInvalidValue;
-  KernelArgs args = p.args;
-  int32_t tag = p.tag;
-  unsigned long long *trace = g_host_op_trace;
-  void *kparams[3] = {&args, &tag, &trace};
-  hipKernelNodeParams np = {};
-  np.func = func;
-  np.gridDim = dim3(p.gx, p.gy, p.gz);
-  np.blockDim = dim3(p.block);
-  np.sharedMemBytes = 0;
-  np.kernelParams = kparams;
-  np.extra = nullptr;
-  return hipGraphExecKernelNodeSetParams(exec, node, &np);
+  PlanParams params(p);
+  const hipKernelNodeParams np = plan_node_params(p, params);
+  return np.func ? hipGraphExecKernelNodeSetParams(exec, node, &np) : hipErrorInvalidValue;
 }
 
 hipError_t add_noop_node(hipGraph_t graph, const hipGraphNode_t *deps, size_t n_deps, hipGraphNode_t *node) {
@@ -2158,8 +2239,7 @@ int group_flavor(int id) {
     HEAVY_BODIES(FCASE, half_t, f16, 0) HEAVY_BODIES(FCASE, float, f32, 0) return 2;
     LIGHT_BODIES(FCASE, half_t, f16, 0) LIGHT_BODIES(FCASE, float, f32, 0) return 1;
 #undef FCASE
-    case K_attention_f16: return -1;     // runs as a launch of its own
-    default: return id >= 0 && id < K_COUNT ? 0 : -1;
+    default: return id >= 0 && id < K_attention_f16 ? 0 : -1;     // merged operators run as launches of their own
   }
 }
 

@@ -33,6 +33,7 @@ struct TokenArgs { int32_t epoch, self, n_preds, delay; int32_t preds[kVerifyMax
 // switched to the operator's kernel, the argument block the runtime holds for the node is
 // large enough and already valid for that kernel.
 struct TokenNodeArgs { KernelArgs real; TokenArgs tok; };
+static_assert(sizeof(TokenNodeArgs) >= sizeof(KernelArgs) + 16 + sizeof(TailArgs), "record smaller than a kernel's arguments");
 hipError_t add_token_node(hipGraph_t graph, const TokenNodeArgs &t, const hipGraphNode_t *deps, size_t n_deps,
                           hipGraphNode_t *node);
 // Switches a kernel node of an instantiated graph to the planned launch `p` (kernel, grid,

@@ -63,6 +63,48 @@ bool merge_attention(const opara_dag *g, int32_t u, int32_t v, int32_t w, Merge 
   return true;
 }
 
+// contraction -> element-wise operator of its size, in whole vectors.  The contractions fed
+// through workgroup memory have a form with such a tail.
+bool merge_tail(const opara_dag *g, int32_t u, int32_t v, Merge *out) {
+  const opara_op_desc &du = g->ops[u], &dv = g->ops[v];
+  const KernelPlan &pu = g->plan[u];
+  if (du.op_type != OPARA_CONV2D && du.op_type != OPARA_GEMM) return false;
+  if (dv.op_type != OPARA_ADD && dv.op_type != OPARA_RELU && dv.op_type != OPARA_GELU) return false;
+  if (du.dtype != dv.dtype || tail_kernel(pu.kernel) < 0) return false;
+  const IgemmArgs &c = pu.args.igemm;
+  const EltArgs &e = g->plan[v].args.elt;
+  const int64_t es = du.dtype == OPARA_F16 ? 2 : 4, cells = (int64_t)c.M * c.N;
+  if (c.ldy != c.N || e.n != cells || e.n_in > 3) return false;
+  if (c.N % 4 || es * cells >= (int64_t)1 << 31 || !aligned16(e.y)) return false;
+  TailArgs t;
+  std::memset(&t, 0, sizeof t);
+  t.y = e.y; t.n_in = e.n_in; t.op = e.op; t.self = -1;
+  const Range y = range_of(c.y, es * cells), ty = range_of(e.y, es * cells),
+              x = range_of(c.x, c.x_bytes), w = range_of(c.w, c.w_bytes), bias = range_of(c.bias, c.bias ? 4 * (int64_t)c.N : 0);
+  if (!disjoint(ty, {y, x, w, bias})) return false;
+  for (int q = 0; q < c.n_extra; ++q)
+    if (!disjoint(ty, range_of(c.extra[q], es * cells))) return false;
+  int others = 0;
+  for (int q = 0; q < e.n_in; ++q) {
+    if (dv.inputs[q] == u) {
+      if (t.self >= 0 || e.in[q] != c.y) return false;
+      t.self = q;
+      continue;
+    }
+    if (others == 2 || !aligned16(e.in[q])) return false;
+    const Range r = range_of(e.in[q], es * cells);
+    if (!disjoint(r, {y, ty})) return false;
+    t.in[others++] = e.in[q];
+  }
+  if (t.self < 0) return false;
+  out->count = 2;
+  out->ops[0] = u; out->ops[1] = v;
+  out->plan = pu;
+  out->plan.kernel = tail_kernel(pu.kernel);
+  out->plan.tail = t;
+  return true;
+}
+
 }  // namespace
 
 std::vector<Merge> find_merges(const opara_dag *g) {
@@ -81,6 +123,9 @@ std::vector<Merge> find_merges(const opara_dag *g) {
     if (w + 2 < waves && alone[w + 2] >= 0 && merge_attention(g, alone[w], alone[w + 1], alone[w + 2], &m)) {
       found.push_back(m);
       w += m.count - 1;
+    } else if (merge_tail(g, alone[w], alone[w + 1], &m)) {
+      found.push_back(m);
+      ++w;
     }
   }
   return found;

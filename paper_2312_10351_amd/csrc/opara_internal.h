@@ -65,6 +65,8 @@ std::vector<Merge> find_merges(const opara_dag *g);
 
 // Tile shapes of contractions that run together; only for kernels whose shape is open.
 bool tile_choice_open(int kernel_id);
+// The same contraction with an element-wise operator after it (KernelPlan::tail); -1: none.
+int tail_kernel(int kernel_id);
 void choose_tiles(KernelPlan *const *plans, int n);
 
 }  // namespace opara

@@ -342,6 +342,15 @@ void choose_tiles(KernelPlan *const *plans, int n) {
   }
 }
 
+int tail_kernel(int kernel_id) {
+  switch (kernel_id) {
+#define TAIL(name) case K_igemm_f16_##name: return K_igemm_f16_##name##_tail; case K_igemm_f32_##name: return K_igemm_f32_##name##_tail;
+    TAIL(quad4s) TAIL(quad4) TAIL(quad64x4) TAIL(quad64x64) TAIL(tile64x64) TAIL(t128x64) TAIL(tile128x128)
+#undef TAIL
+    default: return -1;
+  }
+}
+
 bool tile_choice_open(int kernel_id) {
   return std::any_of(kTileKernels, kTileKernels + kTileKernelCount,
                      [&](const TileKernel &t) { return t.ids[0] == kernel_id || t.ids[1] == kernel_id; });

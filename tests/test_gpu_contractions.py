@@ -2,6 +2,7 @@
 and gathered operands, partial last K steps, rows and columns past the end, padding taps,
 strides; alone and with the tile shapes a fused wave gives its members together."""
 import pytest
+import torch
 
 from oracle import executor
 from workloads import Builder
@@ -52,6 +53,7 @@ def test_alone(case, dtype):
         exe = s.capture(B.SEQUENTIAL)
         for t in s.out_dev:
             t.fill_(float("nan"))
+        torch.cuda.synchronize()                         # the session replays on a stream of its own
         s.replay(exe)
         assert not compare_all(s, executor.run_dag(wl))
     finally:
@@ -71,6 +73,7 @@ def test_together_in_one_wave(cases, dtype):
         for exe in (s.capture(B.FUSED), s.capture_chained()):
             for t in s.out_dev:
                 t.fill_(float("nan"))
+            torch.cuda.synchronize()                         # the session replays on a stream of its own
             s.replay(exe)
             assert not compare_all(s, ref)
     finally:

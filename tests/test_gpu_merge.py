@@ -2,6 +2,7 @@
 against the oracle, every operator's result, and refused where buffers overlap."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import executor
 from workloads import Builder
@@ -26,6 +27,7 @@ def run_fused(wl, launches, reps=2):
         for _ in range(reps):
             for t in s.out_dev:
                 t.fill_(float("nan"))
+            torch.cuda.synchronize()                         # the session replays on a stream of its own
             s.replay(exe)
             assert not compare_all(s, ref)
     finally:
@@ -62,8 +64,7 @@ def test_attention_with_masked_scores():
     try:
         got = []
         for mode in (B.SEQUENTIAL, B.FUSED):
-            for t in s.out_dev:
-                t.zero_()
+            s.clear_outputs()
             s.replay(s.capture(mode))
             got.append([s.output(v).astype(np.float64) for v in range(3)])
         for a, b in zip(*got):
@@ -72,6 +73,55 @@ def test_attention_with_masked_scores():
             assert (np.isfinite(b) == ok).all() and np.allclose(a[ok], b[ok], rtol=2e-3, atol=2e-3)
     finally:
         s.close()
+
+
+# (m, k, n): every tile shape a contraction of its own takes, rows and columns past the tiles' end
+TAIL_SHAPES = [(17, 520, 36), (83, 1192, 60), (300, 2056, 700), (1150, 288, 312), (256, 400, 2068), (1938, 360, 260), (1517, 328, 1348),
+               (1122, 280, 1592)]
+
+
+def tail(shape, kind, place, dtype, extras=0):
+    """A product and an element-wise operator that takes its result as input number `place`."""
+    m, k, n = shape
+    b = Builder("tail", dtype)
+    u = b.gemm(b.ext((m, k)), m, k, n, extras=[b.ext((m, n)) for _ in range(extras)], relu=extras > 0)
+    ins = [b.ext((m, n)) for _ in range(3 if kind == "add3" else 2 if kind == "add" else 1)]
+    ins[place] = u
+    b.rowwise("add" if kind.startswith("add") else kind, ins, m, n)
+    return b.build(29, random_bias=True, he_init=True)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("shape", TAIL_SHAPES)
+def test_element_wise_tail(shape, dtype):
+    for i, (kind, place) in enumerate((("gelu", 0), ("add", 0), ("add", 1))):
+        run_fused(tail(shape, kind, place, dtype, extras=i % 2), 1, reps=1)
+
+
+@pytest.mark.parametrize("kind,place", [("add3", 0), ("add3", 1), ("add3", 2), ("relu", 0)])
+def test_element_wise_tail_of_several_inputs(kind, place):
+    run_fused(tail((83, 520, 72), kind, place, "f16"), 1)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_element_wise_tail_of_a_convolution(dtype):
+    b = Builder("tail", dtype, 2)
+    x = b.ext((64, 13, 11))
+    b.add_images([b.ext((36, 13, 11)), b.conv(x, 36, 3, pad=1, relu=False)])
+    run_fused(b.build(31, random_bias=True, he_init=True), 1)
+
+
+def test_element_wise_operators_that_stay_on_their_own():
+    run_fused(tail((83, 520, 71), "gelu", 0, "f16"), 2)              # rows that are no whole vectors
+    run_fused(tail((83, 72, 72), "gelu", 0, "f16"), 2)               # shallow product: fragment-loading kernel
+    b = Builder("tail", "f16")                                       # a view of part of the result
+    u = b.gemm(b.ext((64, 520)), 64, 520, 64)
+    b.rowwise("gelu", [u], 32, 64)
+    run_fused(b.build(1, he_init=True), 2)
+    b = Builder("tail", "f16")                                       # the result twice
+    u = b.gemm(b.ext((64, 520)), 64, 520, 64)
+    b.rowwise("add", [u, u], 64, 64)
+    run_fused(b.build(1, he_init=True), 2)
 
 
 def test_overlapping_buffers_are_not_merged():

@@ -3,6 +3,7 @@ hang over every edge, strides and windows of other sizes than 3 x 3, channel cou
 without 16-byte chunks, several images, pixel counts around the rounds of the global average."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import executor
 from workloads import Builder
@@ -20,6 +21,7 @@ def check(wl):
         for exe in (s.capture(B.SEQUENTIAL), s.capture(B.FUSED)):
             for t in s.out_dev:
                 t.fill_(float("nan"))
+            torch.cuda.synchronize()                         # the session replays on a stream of its own
             s.replay(exe)
             assert not compare_all(s, ref)
     finally:
