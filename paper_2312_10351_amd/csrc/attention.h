@@ -35,7 +35,7 @@ __device__ __forceinline__ void attention_body(const AR &a, const Blk &b, unsign
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int grp = lane >> 4, r16 = lane & 15, l8 = lane >> 3, chunk = (lane & 7) ^ l8;
   int tile_x, z;
-  xcd_tile(b, tile_x, z);                                   // row tiles of one head share an L2
+  xcd_tile(b, a.div_gx, tile_x, z);                                // row tiles of one head share an L2
   const int m0 = tile_x * 16;
   const int N = a.N;
   const i32x4 qbuf = buffer_of((const T *)a.q + (int64_t)z * a.q_bs, a.q_bytes);

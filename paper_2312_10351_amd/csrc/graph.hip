@@ -239,6 +239,8 @@ int capture_fused(opara_dag *g, opara_exec **out) {
           node.ga.block_end[i] = (int32_t)end;
           node.ga.meta[i].kernel = p.kernel;
           node.ga.meta[i].gx = (int32_t)p.gx; node.ga.meta[i].gy = (int32_t)p.gy;
+          node.ga.meta[i].gz = (int32_t)p.gz;
+          node.ga.meta[i].div_gx = div_magic(p.gx);
           node.ga.meta[i].tiles = (int32_t)tiles;
           node.ga.meta[i].tag = members[i];
           node.ga.args[i] = p.args;

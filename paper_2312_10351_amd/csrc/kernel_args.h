@@ -28,6 +28,7 @@ struct IgemmArgs {
   float alpha;
   uint32_t div_HoWo, div_Wo, div_Cin, div_kw;   // min(2^32 / d, 2^32 - 1): see fast_div
   uint32_t x_bytes, w_bytes;    // what the operands span (one batch element), 0 if kOperandMaxBytes or more
+  uint32_t div_gx;              // reciprocal of the grid's width
 };
 
 struct PoolArgs {
@@ -79,6 +80,7 @@ struct AttnArgs {
   int32_t M, N, D, D2;          // query rows, key rows, width of a row of q and k, of v
   uint32_t q_bytes, k_bytes, v_bytes;   // one head
   float alpha_s, alpha_c;
+  uint32_t div_gx;              // reciprocal of the grid's width
 };
 
 // X(name, ArgsType).  Order defines kernel ids.
@@ -198,16 +200,22 @@ struct GroupMeta {                                 // one member: read with one 
   int32_t tiles;                                   // gx * gy * gz
   int32_t tag;                                     // operator id (slot of the operator timeline)
   int32_t block_begin;                             // first block of the member's range
-  int32_t reserved[2];
+  uint32_t div_gx;                                 // reciprocal of gx for fast_div
+  int32_t gz;
 };
 struct GroupArgs {
+  int32_t block_end[kGroupMaxOps];
   int32_t n;
   int32_t reserved;
   unsigned long long *trace;                       // operator-timeline buffer, null = off
-  int32_t block_end[kGroupMaxOps];
   GroupMeta meta[kGroupMaxOps];
   KernelArgs args[kGroupMaxOps];
 };
+// The first ends are kernel arguments of their own: the hardware puts up to fourteen words at the
+// head of the argument segment into scalar registers before a workgroup starts.
+constexpr int kGroupPreload = 14;
+struct GroupRest { alignas(8) unsigned char bytes[sizeof(GroupArgs) - 4 * kGroupPreload]; };
+static_assert(4 * kGroupPreload % 8 == 0 && sizeof(GroupRest) + 4 * kGroupPreload == sizeof(GroupArgs), "argument segment layout");
 
 // Operands of the LDS-fed contractions are addressed through 32-bit buffer offsets; this
 // offset is past the end of every operand they accept, and stays so with a row of K added.

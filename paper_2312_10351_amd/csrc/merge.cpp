@@ -59,6 +59,7 @@ bool merge_attention(const opara_dag *g, int32_t u, int32_t v, int32_t w, Merge 
   a.ldq = (int32_t)s.lda; a.ldk = (int32_t)s.ldb; a.ldv = (int32_t)c.ldb;
   a.M = s.M; a.N = s.N; a.D = s.K; a.D2 = c.N;
   a.q_bytes = (uint32_t)q_bytes; a.k_bytes = (uint32_t)k_bytes; a.v_bytes = (uint32_t)v_bytes;
+  a.div_gx = div_magic(p.gx);
   a.alpha_s = s.alpha; a.alpha_c = c.alpha;
   return true;
 }

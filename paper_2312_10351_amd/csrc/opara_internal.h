@@ -46,6 +46,9 @@ extern const KernelResource kKernelResources[K_COUNT];
 
 void set_error(const char *fmt, ...);
 
+// What the kernels' fast_div takes for a divisor.
+inline uint32_t div_magic(int64_t d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint64_t)d) : 0xffffffffu; }
+
 // One flag per entry of the opara_sync_edges list (same order): 0 = the dependency is
 // implied by other ordering constraints and needs no synchronisation of its own.
 int sync_keep_mask(const opara_dag *g, std::vector<uint8_t> *keep);

@@ -21,8 +21,6 @@ namespace {
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline uint32_t cdiv(int64_t a, int64_t b) { return (uint32_t)((a + b - 1) / b); }
 
-inline uint32_t div_magic(int32_t d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint64_t)d) : 0xffffffffu; }
-
 // The contractions fed through workgroup memory, and what one workgroup of each costs, in
 // microseconds: a 128-byte step of K when the workgroup has a compute unit to itself
 // (`alone`) and when the launch keeps every CU busy (`busy`), and everything outside the K
@@ -122,6 +120,7 @@ int plan_igemm(const opara_op_desc &op, const void *const *in, int kind, KernelP
     out->gy = cdiv(a.N, bn);
     out->gz = (uint32_t)batch;
     out->block = 256;
+    a.div_gx = div_magic((int64_t)out->gx);
     out->args.igemm = a;
     return OPARA_OK;
   };
@@ -339,6 +338,7 @@ void choose_tiles(KernelPlan *const *plans, int n) {
     plans[i]->kernel = t.ids[f16];
     plans[i]->gx = cdiv(a.M, t.bm);
     plans[i]->gy = cdiv(a.N, t.bn);
+    plans[i]->args.igemm.div_gx = div_magic((int64_t)plans[i]->gx);
   }
 }
 
