@@ -510,8 +510,9 @@ int opara_run_persistent_noalloc(opara_dag *g, void *hip_stream, uint32_t *error
  * the bodies with at most 64 vector registers, at most 128, or all bodies); each may be
  * NULL.  Operators that share a node run concurrently inside one kernel.  An operator that is
  * alone in its wave and consumes the only operator of the wave before may be computed by that
- * operator's kernel (scores, softmax and context of an attention); it keeps a node of its own,
- * which launches nothing: opara_fused_time_nodes reports 0 for it and opara_exec_info does not
+ * operator's kernel (scores, softmax and context of an attention; an element-wise operator after
+ * a product), and a concatenation by the element-wise operators whose results it joins; it keeps
+ * a node of its own, which launches nothing: opara_fused_time_nodes reports 0 for it and opara_exec_info does not
  * count it.  Executors captured with the operator timeline on run every operator by itself.
  */
 enum { OPARA_GROUP_KERNEL_LIGHT = -1, OPARA_GROUP_KERNEL_HEAVY = -2, OPARA_GROUP_KERNEL_STREAM = -3 };

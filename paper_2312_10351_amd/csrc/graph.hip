@@ -192,7 +192,13 @@ int capture_fused(opara_dag *g, opara_exec **out) {
   std::vector<const Merge *> merge_of(n, nullptr);
   for (const Merge &m : merges)
     for (int32_t i = 0; i < m.count; ++i) merge_of[m.ops[i]] = &m;
+  const std::vector<ConcatMerge> concats = current_op_trace() ? std::vector<ConcatMerge>() : find_concat_merges(g, merges);
+  std::vector<char> in_place(n, 0);                // concatenations that their inputs' kernels write
   std::vector<KernelPlan> plan(g->plan);           // a wave's contractions get their tile shapes together
+  for (const ConcatMerge &m : concats) {
+    in_place[m.concat] = 1;
+    for (size_t i = 0; i < m.ops.size(); ++i) plan[m.ops[i]].args.elt = m.args[i];
+  }
   while (placed < n) {
     wave.clear();
     for (int32_t i = 0; i < n; ++i) {
@@ -219,8 +225,9 @@ int capture_fused(opara_dag *g, opara_exec **out) {
       opara_exec::FusedNode node;
       if (members.size() == 1) {
         const Merge *m = merge_of[members[0]];
-        node.plan = m ? m->plan : g->plan[members[0]];
-        node.launches = !m || m->ops[0] == members[0];
+        // Alone in its launch a contraction keeps the tile shape it would have chosen by itself.
+        node.plan = m ? m->plan : tile_choice_open(plan[members[0]].kernel) ? g->plan[members[0]] : plan[members[0]];
+        node.launches = !in_place[members[0]] && (!m || m->ops[0] == members[0]);
       } else {
         node.is_group = true;
         node.flavor = 0;

@@ -60,6 +60,11 @@ struct EltArgs {               // f(sum of inputs), f in {identity, relu, gelu}
   void *y;
   int32_t n_in, op;            // op: 0 add, 1 relu, 2 gelu
   int64_t n;
+  // The result once more, as also_cols columns of rows also_pitch apart: the place of this
+  // operator's result in a concatenation (fused executor, vector form); null: nowhere.
+  void *also;
+  int32_t also_cols, also_pitch;
+  uint32_t div_also;           // reciprocal of the chunks per row
 };
 
 struct ConcatArgs {

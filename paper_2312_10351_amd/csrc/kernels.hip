@@ -1429,8 +1429,18 @@ __device__ __forceinline__ void elt_body(const AR &a, const Blk &b, unsigned cha
 #pragma unroll
   for (int e = 0; e < VE; ++e) o[e] = (T)elt_apply<T>(a.op, s[e]);
   T *dst = (T *)a.y + i;
-  if constexpr (VE > 1) stg<CS, typename Vec16<T>::type>(dst, *(const typename Vec16<T>::type *)o);
-  else stg<CS, T>(dst, o[0]);
+  if constexpr (VE > 1) {
+    typedef typename Vec16<T>::type V;
+    stg<CS, V>(dst, *(const V *)o);
+    if constexpr (!CS) {
+      if (a.also) {
+        const uint32_t item = (uint32_t)(i / VE), cch = (uint32_t)a.also_cols / VE, r = fast_div(item, cch, a.div_also);
+        *(V *)((T *)a.also + (int64_t)r * a.also_pitch + (item - r * cch) * VE) = *(const V *)o;
+      }
+    }
+  } else {
+    stg<CS, T>(dst, o[0]);
+  }
 }
 
 template <typename T, int VE, int COH, typename AR>

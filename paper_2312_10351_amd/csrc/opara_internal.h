@@ -65,6 +65,9 @@ int plan_op(const opara_op_desc &op, const void *const *in, int kind, KernelPlan
 // the only operator of its wave; the kernel is launched in the place of the first.
 struct Merge { int32_t count, ops[3]; KernelPlan plan; };
 std::vector<Merge> find_merges(const opara_dag *g);
+// Concatenations whose parts the element-wise operators that compute them write in place.
+struct ConcatMerge { int32_t concat; std::vector<int32_t> ops; std::vector<EltArgs> args; };
+std::vector<ConcatMerge> find_concat_merges(const opara_dag *g, const std::vector<Merge> &taken);
 
 // Tile shapes of contractions that run together; only for kernels whose shape is open.
 bool tile_choice_open(int kernel_id);

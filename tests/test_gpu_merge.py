@@ -124,6 +124,40 @@ def test_element_wise_operators_that_stay_on_their_own():
     run_fused(b.build(1, he_init=True), 2)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("rows,parts", [(1, (8,)), (7, (8, 40, 16)), (33, (72, 8, 8, 264)), (129, (16, 16))])
+def test_concatenation_of_element_wise_results(rows, parts, dtype):
+    b = Builder("concat", dtype)
+    us = [b.rowwise(("add", "gelu", "relu")[i % 3], [b.ext((rows, c)) for _ in range(2 if i % 3 == 0 else 1)], rows, c)
+          for i, c in enumerate(parts)]
+    b.add("concat", us, [(rows, c) for c in parts], (rows, sum(parts)), {"axis": 1})
+    run_fused(b.build(41), 1)
+
+
+def test_concatenations_that_stay_on_their_own():
+    for case in range(4):
+        b = Builder("concat", "f16")
+        n = 20 if case == 0 else 16                                  # parts that are no whole chunks
+        u, v = b.rowwise("add", [b.ext((9, 16))] * 2, 9, 16), b.rowwise("relu", [b.ext((9, n))], 9, n)
+        if case == 1:
+            v = u                                                    # one result twice
+        if case == 2:
+            v = b.ext((9, n))                                        # a part nobody computes
+        if case == 3:
+            v = b.rowwise("softmax", [b.ext((9, n))], 9, n)
+        b.add("concat", [u, v], [(9, 16), (9, n)], (9, 16 + n), {"axis": 1})
+        wl = b.build(43)
+        ref = executor.run_dag(wl)
+        s = Session(wl)
+        try:
+            exe = s.capture(B.FUSED)
+            assert B.opara_exec_info(exe)[0] == 2
+            s.replay(exe)
+            assert not compare_all(s, ref)
+        finally:
+            s.close()
+
+
 def test_overlapping_buffers_are_not_merged():
     wl = attention(2, 64, 64, "f16")
     ref = executor.run_dag(wl)
