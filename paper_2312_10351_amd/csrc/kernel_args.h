@@ -233,7 +233,8 @@ constexpr double kTiledMinFlopsPersistent = 2.0e9;   // persistent kernel: light
 constexpr int kTiledMinTiles = 80;               // ... and so do contractions with fewer 128x64 tiles
 constexpr IgemmTile kTile64{64, 64};
 constexpr int64_t kQuadMinRowBytes = 512;    // shorter rows of K stay on the fragment-loading kernels
-constexpr int64_t kDirectMaxTiles32 = 2048;  // ... unless there are so many tiles that bytes count, not latency
+constexpr int64_t kDirectMaxTiles32 = 512;  // ... unless there are so many tiles that bytes count, not latency
+                                             // (three 1 x 1 convolutions of 16 images of 192 x 35 x 35: 20.8 -> 15.4 us)
 constexpr int kDirectTile = 32;       // output tile edge of the fragment-loading kernels
 constexpr int kSmallTile = 16;        // ... of their small-tile form, for operators with few 32 x 32 tiles
 constexpr int kSmallTileMaxTiles32 = 100;   // at most this many 32 x 32 tiles: take 16 x 16 ones (four times as many workgroups)

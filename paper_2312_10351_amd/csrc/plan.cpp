@@ -24,18 +24,20 @@ inline uint32_t cdiv(int64_t a, int64_t b) { return (uint32_t)((a + b - 1) / b);
 // The contractions fed through workgroup memory, and what one workgroup of each costs, in
 // microseconds: a 128-byte step of K when the workgroup has a compute unit to itself
 // (`alone`) and when the launch keeps every CU busy (`busy`), and everything outside the K
-// walk (`fixed`).  Fitted to isolated fp16 products, M x N x K = 49..346688 x 32..4096 x
+// walk (`fixed`).  `together`: how much longer the work takes inside a group kernel, which holds
+// two workgroups per CU where the body by itself would leave room for three (three 512 x 768 x
+// 768 products: 8.3 -> 7.5 us with the tiles this makes them take).  Fitted to isolated fp16 products, M x N x K = 49..346688 x 32..4096 x
 // 320..4096, within 15 %.  In fp32 a step cannot take less than its multiply-adds at the
 // matrix rate of a CU (0.6 TFLOP/s).
-struct TileKernel { int ids[2]; int bn, bm; double alone, busy, fixed; };   // ids: f32, f16
+struct TileKernel { int ids[2]; int bn, bm; double alone, busy, fixed, together; };   // ids: f32, f16
 const TileKernel kTileKernels[] = {
-    {{K_igemm_f32_quad4s, K_igemm_f16_quad4s}, 16, 16, 0.060, 0.037, 0.25},
-    {{K_igemm_f32_quad4, K_igemm_f16_quad4}, 32, 32, 0.080, 0.075, 0.58},
-    {{K_igemm_f32_quad64x4, K_igemm_f16_quad64x4}, 64, 32, 0.122, 0.125, 0.50},
-    {{K_igemm_f32_quad64x64, K_igemm_f16_quad64x64}, 64, 64, 0.160, 0.165, 1.6},
-    {{K_igemm_f32_tile64x64, K_igemm_f16_tile64x64}, 64, 64, 0.28, 0.18, 0.8},
-    {{K_igemm_f32_t128x64, K_igemm_f16_t128x64}, 128, 64, 0.45, 0.33, 1.2},
-    {{K_igemm_f32_tile128x128, K_igemm_f16_tile128x128}, 128, 128, 0.56, 0.48, 1.7},
+    {{K_igemm_f32_quad4s, K_igemm_f16_quad4s}, 16, 16, 0.060, 0.037, 0.25, 1},
+    {{K_igemm_f32_quad4, K_igemm_f16_quad4}, 32, 32, 0.080, 0.075, 0.58, 1},
+    {{K_igemm_f32_quad64x4, K_igemm_f16_quad64x4}, 64, 32, 0.122, 0.125, 0.50, 1.15},
+    {{K_igemm_f32_quad64x64, K_igemm_f16_quad64x64}, 64, 64, 0.160, 0.165, 1.6, 1.2},
+    {{K_igemm_f32_tile64x64, K_igemm_f16_tile64x64}, 64, 64, 0.28, 0.18, 0.8, 1},
+    {{K_igemm_f32_t128x64, K_igemm_f16_t128x64}, 128, 64, 0.45, 0.33, 1.2, 1},
+    {{K_igemm_f32_tile128x128, K_igemm_f16_tile128x128}, 128, 128, 0.56, 0.48, 1.7, 1},
 };
 constexpr int kTileKernelCount = sizeof kTileKernels / sizeof kTileKernels[0];
 constexpr double kCus = 256.0;
@@ -304,7 +306,7 @@ void choose_tiles(KernelPlan *const *plans, int n) {
       const double least = f16 ? 0.0 : t.bn * t.bm * 32 * 2.0 / 0.6e6;
       Option o;
       o.longest = steps * std::max(t.alone, least) + t.fixed;
-      o.work = tiles * (steps * std::max(t.busy, least) + t.fixed) / kCus;
+      o.work = tiles * (steps * std::max(t.busy, least) + t.fixed) / kCus * (n > 1 ? t.together : 1.0);
       if (n == 1 && tiles > kCus && tiles < 4 * kCus)      // a single launch: whole rounds over the CUs
         o.work *= std::ceil(tiles / kCus) * kCus / tiles;
       opt[i].push_back(o);
