@@ -233,13 +233,14 @@ def bench_config(index, steps, warmup, zero_copy_concat="auto", cpu_budget_s=0.0
             for node, (name, t) in enumerate(zip(names, us)):
                 e = fk.setdefault(name, dict(launches=0, time_us=0.0, flops=0, bytes=0, ops=0))
                 members = [v for v in range(len(node_of)) if node_of[v] == node]
-                e["launches"] += 1; e["time_us"] += t; e["ops"] += len(members)
+                e["launches"] += t > 0                  # a node computed by an earlier one launches nothing
+                e["time_us"] += t; e["ops"] += len(members)
                 e["flops"] += sum(work[v][0] for v in members); e["bytes"] += sum(work[v][1] for v in members)
             dom = max(fk, key=lambda k: fk[k]["time_us"])
             kern = kernel_block(dom, fk[dom]["flops"], fk[dom]["bytes"], fk[dom]["launches"], fk[dom]["time_us"], wl.dtype,
                                 traffic.get((wl.name, dom + tag)), operators_in_these_launches=fk[dom]["ops"],
                                 share_of_node_time=fk[dom]["time_us"] / sum(us))
-            res["fused_node_kernels"] = {k: dict(launches=v["launches"], avg_us=v["time_us"] / v["launches"], operators=v["ops"])
+            res["fused_node_kernels"] = {k: dict(launches=v["launches"], avg_us=v["time_us"] / max(v["launches"], 1), operators=v["ops"])
                                          for k, v in fk.items()}
             res["fused_sum_of_node_times_us"] = float(sum(us))
         elif best in ("persistent", "chained"):
