@@ -216,12 +216,6 @@ struct GroupArgs {
   GroupMeta meta[kGroupMaxOps];
   KernelArgs args[kGroupMaxOps];
 };
-// The first ends are kernel arguments of their own: the hardware puts up to fourteen words at the
-// head of the argument segment into scalar registers before a workgroup starts.
-constexpr int kGroupPreload = 14;
-struct GroupRest { alignas(8) unsigned char bytes[sizeof(GroupArgs) - 4 * kGroupPreload]; };
-static_assert(4 * kGroupPreload % 8 == 0 && sizeof(GroupRest) + 4 * kGroupPreload == sizeof(GroupArgs), "argument segment layout");
-
 // Operands of the LDS-fed contractions are addressed through 32-bit buffer offsets; this
 // offset is past the end of every operand they accept, and stays so with a row of K added.
 constexpr uint32_t kOperandMaxBytes = 0xc0000000u;

@@ -1913,8 +1913,8 @@ extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f32(Persist
 // and 16 x 16-tile contractions; four per SIMD), "heavy" (all 256-thread bodies; two).
 // ---------------------------------------------------------------------------------
 template <bool F16, int FLAVOR, bool TRACE>
-__device__ __forceinline__ void group_body(const int32_t (&ends)[kGroupPreload]) {
-  // The record, its first words declared as arguments of their own, starts the kernel-argument
+__device__ __forceinline__ void group_body() {
+  // The record is the kernel's only argument and therefore starts the kernel-argument
   // segment.  It is read in place through the segment pointer: indexing the by-value
   // parameter with a run-time operator number would make the compiler copy all of it into
   // private memory first.
@@ -1922,22 +1922,14 @@ __device__ __forceinline__ void group_body(const int32_t (&ends)[kGroupPreload])
   CGA &ga = *(CGA *)__builtin_amdgcn_kernarg_segment_ptr();
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_lds[];
   const int blk = (int)blockIdx.x;
-  // The member this block belongs to: the number of range ends at or below the block (unused
-  // entries hold INT32_MAX).  Fourteen ends are in registers when the workgroup starts, which
-  // takes one memory round trip out of the head of every group node (27 nodes of the GoogLeNet-like
-  // network, 18 of them groups: 130.6 -> 122 us; NASNet-like 109 -> 101 us).
+  // The member this block belongs to: all sixteen range ends arrive with one 64-byte load
+  // (unused entries hold INT32_MAX), the member is the number of ends at or below the block.
+  // Range ends, shape and arguments all come from the one record in memory.  Taking the ends
+  // from registers that the hardware fills ahead of the workgroup (preloaded arguments) saves a
+  // round trip, 0.45 us a node, but then two sources have to agree before a store is in bounds.
   int i = 0;
-  asm("s_cmp_ge_i32 %1, %2\n\ts_addc_u32 %0, %0, 0\n\ts_cmp_ge_i32 %1, %3\n\ts_addc_u32 %0, %0, 0\n\t"
-      "s_cmp_ge_i32 %1, %4\n\ts_addc_u32 %0, %0, 0\n\ts_cmp_ge_i32 %1, %5\n\ts_addc_u32 %0, %0, 0\n\t"
-      "s_cmp_ge_i32 %1, %6\n\ts_addc_u32 %0, %0, 0\n\ts_cmp_ge_i32 %1, %7\n\ts_addc_u32 %0, %0, 0\n\t"
-      "s_cmp_ge_i32 %1, %8\n\ts_addc_u32 %0, %0, 0\n\ts_cmp_ge_i32 %1, %9\n\ts_addc_u32 %0, %0, 0\n\t"
-      "s_cmp_ge_i32 %1, %10\n\ts_addc_u32 %0, %0, 0\n\ts_cmp_ge_i32 %1, %11\n\ts_addc_u32 %0, %0, 0\n\t"
-      "s_cmp_ge_i32 %1, %12\n\ts_addc_u32 %0, %0, 0\n\ts_cmp_ge_i32 %1, %13\n\ts_addc_u32 %0, %0, 0\n\t"
-      "s_cmp_ge_i32 %1, %14\n\ts_addc_u32 %0, %0, 0\n\ts_cmp_ge_i32 %1, %15\n\ts_addc_u32 %0, %0, 0\n\t"
-      : "+s"(i)
-      : "s"(blk), "s"(ends[0]), "s"(ends[1]), "s"(ends[2]), "s"(ends[3]), "s"(ends[4]), "s"(ends[5]), "s"(ends[6]), "s"(ends[7]), "s"(ends[8]), "s"(ends[9]), "s"(ends[10]), "s"(ends[11]), "s"(ends[12]), "s"(ends[13])
-      : "scc");
-  if (i == kGroupPreload) i += blk >= ga.block_end[kGroupPreload] ? 1 : 0;
+#pragma unroll
+  for (int j = 0; j < kGroupMaxOps - 1; ++j) i += blk >= ga.block_end[j] ? 1 : 0;
   i = __builtin_amdgcn_readfirstlane(i);
   // The member's launch shape and, in the same round, a word of every cache line of its argument
   // record, so that the body's own argument loads (which the compiler issues only behind the
@@ -1949,7 +1941,7 @@ __device__ __forceinline__ void group_body(const int32_t (&ends)[kGroupPreload])
   asm volatile("" : : "s"(me.kernel), "s"(me.gx), "s"(me.gy), "s"(me.tiles), "s"(me.block_begin), "s"(me.div_gx), "s"(me.gz),
                "s"(rec[0]), "s"(rec[16]), "s"(rec[32]), "s"(rec[sizeof(KernelArgs) / 4 - 1]));
   const int tile = blk - me.block_begin;
-  if (tile >= me.tiles) return;                                    // padding of the operator's range
+  if ((uint32_t)tile >= (uint32_t)me.tiles) return;                // padding of the operator's range
   Blk b;
   b.gx = me.gx; b.gy = me.gy;
   b.remap = true;
@@ -2015,12 +2007,8 @@ __device__ __forceinline__ void group_body(const int32_t (&ends)[kGroupPreload])
   if constexpr (TRACE) op_trace_end(ga.trace, tag, t0, (unsigned)tile, (unsigned)me.tiles);
 }
 
-#define GROUP_ENDS int32_t e0, int32_t e1, int32_t e2, int32_t e3, int32_t e4, int32_t e5, int32_t e6, int32_t e7, int32_t e8, int32_t e9, int32_t e10, int32_t e11, int32_t e12, int32_t e13
-#define GROUPK2(name, waves, F16, FLAVOR, TRACE)                                                                  \
-  extern "C" __global__ void __launch_bounds__(256, waves) opara_k_group_##name(GROUP_ENDS, GroupRest) {          \
-    const int32_t ends[kGroupPreload] = {e0, e1, e2, e3, e4, e5, e6, e7, e8, e9, e10, e11, e12, e13};                \
-    group_body<F16, FLAVOR, TRACE>(ends);                                                                         \
-  }
+#define GROUPK2(name, waves, F16, FLAVOR, TRACE) \
+  extern "C" __global__ void __launch_bounds__(256, waves) opara_k_group_##name(GroupArgs) { group_body<F16, FLAVOR, TRACE>(); }
 #define GROUPK(name, waves, F16, FLAVOR) GROUPK2(name, waves, F16, FLAVOR, false) GROUPK2(name##_traced, waves, F16, FLAVOR, true)
 GROUPK(f16_stream, 8, true, 0)
 GROUPK(f16_light, 4, true, 1)
@@ -2288,16 +2276,6 @@ void *group_func(bool f16, int flavor, bool traced) {
 }
 }  // namespace
 
-namespace {
-struct GroupParams {                               // the arguments of a group kernel, in place
-  void *ptr[kGroupPreload + 1];
-  explicit GroupParams(GroupArgs &ga) {
-    for (int i = 0; i < kGroupPreload; ++i) ptr[i] = &ga.block_end[i];
-    ptr[kGroupPreload] = &ga.block_end[kGroupPreload];
-  }
-};
-}  // namespace
-
 int group_flavor(int id) {
   switch (id) {
 #define FCASE(name, Args, call) case K_##name:
@@ -2328,20 +2306,20 @@ hipError_t group_prepare(uint32_t max_lds_bytes) {
 hipError_t add_group_node(hipGraph_t graph, bool f16, int flavor, const GroupArgs &ga, uint32_t n_blocks,
                           uint32_t lds_bytes, const hipGraphNode_t *deps, size_t n_deps, hipGraphNode_t *node) {
   GroupArgs args = ga;
-  GroupParams params(args);
+  void *kparams[1] = {&args};
   hipKernelNodeParams np = {};
   np.func = group_func(f16, flavor, ga.trace != nullptr);
   np.gridDim = dim3(n_blocks);
   np.blockDim = dim3(256);
   np.sharedMemBytes = lds_bytes;
-  np.kernelParams = params.ptr;
+  np.kernelParams = kparams;
   return hipGraphAddKernelNode(node, graph, deps, n_deps, &np);
 }
 
 hipError_t launch_group(bool f16, int flavor, const GroupArgs &ga, uint32_t n_blocks, uint32_t lds_bytes, hipStream_t s) {
   GroupArgs args = ga;
-  GroupParams params(args);
-  return hipLaunchKernel(group_func(f16, flavor, ga.trace != nullptr), dim3(n_blocks), dim3(256), params.ptr, lds_bytes, s);
+  void *kparams[1] = {&args};
+  return hipLaunchKernel(group_func(f16, flavor, ga.trace != nullptr), dim3(n_blocks), dim3(256), kparams, lds_bytes, s);
 }
 
 namespace {

@@ -1,0 +1,54 @@
+"""What the compiler made of the kernels, read from the code object of the built library: how a
+kernel gets its arguments and how large its argument segment is."""
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2312_10351_amd import binding as B
+
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+
+
+@pytest.fixture(scope="module")
+def code_object(tmp_path_factory):
+    B.load()
+    data = open(B.LIB_PATH, "rb").read()
+    at = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    n, = struct.unpack_from("<Q", data, at + 24)
+    p, found = at + 32, []
+    for _ in range(n):
+        off, size, length = struct.unpack_from("<QQQ", data, p)
+        name = data[p + 24:p + 24 + length]
+        p += 24 + length
+        if name.endswith(b"gfx950") and size:
+            found.append(data[at + off:at + off + size])
+    assert len(found) == 1
+    path = tmp_path_factory.mktemp("co") / "kernels.elf"
+    path.write_bytes(found[0])
+    return path
+
+
+def descriptors(path):
+    """{kernel: its 64-byte descriptor}"""
+    image = path.read_bytes()
+    sections = subprocess.run([READELF, "-S", "-W", str(path)], check=True, capture_output=True, text=True).stdout
+    shift = {int(i): int(off, 16) - int(addr, 16)
+             for i, addr, off in re.findall(r"\[ *(\d+)\] \S+ +PROGBITS +([0-9a-f]+) ([0-9a-f]+)", sections)}
+    symbols = subprocess.run([READELF, "-s", "-W", str(path)], check=True, capture_output=True, text=True).stdout
+    out = {}
+    for addr, index, name in re.findall(r"^ *\d+: ([0-9a-f]+) +64 OBJECT +\w+ +\w+ +(\d+) (opara_k_\w+)\.kd$", symbols, re.M):
+        begin = int(addr, 16) + shift[int(index)]
+        out[name] = image[begin:begin + 64]
+    return out
+
+
+def test_no_kernel_takes_arguments_from_two_places(code_object):
+    """Arguments come from the argument segment only: a workgroup that finds its member of a group
+    from preloaded registers and reads the member's record from memory would store out of bounds if
+    the two ever disagreed."""
+    found = descriptors(code_object)
+    assert {"opara_k_group_f16_heavy", "opara_k_attention_f16", "opara_k_token"} <= set(found)
+    preloaded = {k: struct.unpack_from("<H", d, 58)[0] & 127 for k, d in found.items()}
+    assert not any(preloaded.values()), {k: v for k, v in preloaded.items() if v}
