@@ -145,16 +145,15 @@ hipError_t assemble_parallel(const opara_dag *g, const std::vector<uint8_t> &kee
     hipError_t rerr = hipSuccess;
     if (last_on_stream[sv]) deps.push_back(dep_on(last_op_on_stream[sv], &rerr));
     last_op_on_stream[sv] = v;
-    TokenNodeArgs t = {};
-    t.real = g->plan[v].args;
-    t.tok.epoch = 1; t.tok.self = v; t.tok.delay = 4;
+    TokenArgs t = {};
+    t.epoch = 1; t.self = v; t.delay = 4;
     for (int32_t j = g->pred_off[v]; j < g->pred_off[v + 1]; ++j) {
       const int32_t u = g->pred[j];
-      if (t.tok.n_preds < kVerifyMaxPreds) t.tok.preds[t.tok.n_preds++] = u;
+      if (t.n_preds < kVerifyMaxPreds) t.preds[t.n_preds++] = u;
       if (g->stream_of[u] != sv && keep_edge[j]) deps.push_back(dep_on(u, &rerr));
     }
     if (rerr != hipSuccess) return rerr;
-    hipError_t err = tokens ? add_token_node(graph, t, deps.empty() ? nullptr : deps.data(), deps.size(), &(*node_of)[v])
+    hipError_t err = tokens ? add_token_node(graph, g->plan[v], t, deps.empty() ? nullptr : deps.data(), deps.size(), &(*node_of)[v])
                             : add_plan_node(graph, g->plan[v], deps.empty() ? nullptr : deps.data(), deps.size(), &(*node_of)[v]);
     if (err != hipSuccess) return err;
     last_on_stream[sv] = (*node_of)[v];

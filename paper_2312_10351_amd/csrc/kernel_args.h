@@ -182,12 +182,19 @@ struct TailArgs {
   int32_t reserved;
 };
 
+// Second argument of every planned kernel: the operator id, the grid and the operator-timeline
+// buffer (null: off).
+struct LaunchArgs {
+  int32_t tag, gx, gy, gz;
+  unsigned long long *trace;
+};
+
 // One planned launch: which kernel, its grid and its arguments.
 struct KernelPlan {
   int32_t kernel;
   uint32_t gx, gy, gz;
   uint32_t block;
-  int32_t tag;                  // operator id: second kernel argument, slot of the operator timeline
+  int32_t tag;                  // operator id: slot of the operator timeline
   KernelArgs args;
   TailArgs tail;                // contractions with a tail only
 };

@@ -17,16 +17,15 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Position of a workgroup in its operator's launch grid.  An ordinary launch fills it
-// from blockIdx/gridDim; the persistent executor hands out grid positions itself.
+// Position of a workgroup in its operator's launch grid.  An ordinary launch fills it from
+// blockIdx and the launch's arguments; the persistent executor hands out grid positions itself.
 struct Blk {
   int x, y, z, gx, gy;
   int lin;                                 // y * gx + x
   bool remap;                              // apply the XCD-aware tile remap (hardware launch order only)
 };
-__device__ __forceinline__ Blk launch_blk() {
-  return Blk{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.x, (int)gridDim.y,
-             (int)(blockIdx.y * gridDim.x + blockIdx.x), true};
+__device__ __forceinline__ Blk launch_blk(const LaunchArgs &l) {
+  return Blk{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, l.gx, l.gy, (int)blockIdx.y * l.gx + (int)blockIdx.x, true};
 }
 // floor(n / d) with m = min(2^32 / d, 2^32 - 1): the product underestimates by at most one.
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t m) {
@@ -1491,8 +1490,10 @@ __device__ __forceinline__ void op_trace_end(unsigned long long *tr, int tag, un
     if (lin + 8 >= total) atomicMax(tr + 2 * (size_t)tag + 1, (unsigned long long)wall_clock64());
   }
 }
-__device__ __forceinline__ unsigned launch_lin() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
-__device__ __forceinline__ unsigned launch_total() { return gridDim.x * gridDim.y * gridDim.z; }
+__device__ __forceinline__ unsigned launch_lin(const LaunchArgs &l) {
+  return blockIdx.x + (unsigned)l.gx * (blockIdx.y + (unsigned)l.gy * blockIdx.z);
+}
+__device__ __forceinline__ unsigned launch_total(const LaunchArgs &l) { return (unsigned)l.gx * (unsigned)l.gy * (unsigned)l.gz; }
 
 // The arguments of a kernel span up to five cache lines, and the compiler reads them where it
 // needs them: one memory round trip after another at the head of every workgroup.  A contraction
@@ -1506,53 +1507,43 @@ template <int BYTES> __device__ __forceinline__ void touch_arguments() {
   asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d), "s"(e));
 }
 template <typename Args> struct Hold {
-  template <typename AR> static __device__ __forceinline__ void all(const AR &) {}
+  template <typename AR> static __device__ __forceinline__ void all(const AR &, const LaunchArgs &) {}
   static constexpr bool kOn = false;
 };
 template <> struct Hold<IgemmArgs> {
-  template <typename AR> static __device__ __forceinline__ void all(const AR &a) {
+  template <typename AR> static __device__ __forceinline__ void all(const AR &a, const LaunchArgs &l) {
     asm volatile("" : : "s"(a.x), "s"(a.w), "s"(a.bias), "s"(a.y), "s"(a.n_extra), "s"(a.M), "s"(a.N), "s"(a.K), "s"(a.gather), "s"(a.H),
                  "s"(a.W), "s"(a.Cin), "s"(a.Wo), "s"(a.kh), "s"(a.kw), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(a.HoWo),
                  "s"((uint32_t)a.img_stride), "s"((uint32_t)a.lda), "s"((uint32_t)a.ldb), "s"(a.ldy), "s"(a.relu));
     asm volatile("" : : "s"(a.alpha), "s"(a.div_HoWo), "s"(a.div_Wo), "s"(a.div_Cin), "s"(a.div_kw), "s"(a.x_bytes), "s"(a.w_bytes),
-                 "s"(a.div_gx));
+                 "s"(a.div_gx), "s"(l.gx), "s"(l.gy));
   }
   static constexpr bool kOn = true;
 };
 
-#define KDEF(name, threads, ldsb, Args, call)                                                    \
-  extern "C" __global__ void __launch_bounds__(threads) opara_k_##name(Args a, int32_t tag, unsigned long long *trace) {    \
+// The operator's record, the launch's own arguments (KDEFT: and the element-wise operator that
+// follows); nothing implicit, so that a kernel's argument segment is what is declared here: the
+// grid of a launch (gridDim) would be read from 256 bytes that the runtime appends.
+#define KBODY(ldsb, Args, call, extra)                                                           \
     __shared__ __attribute__((aligned(16))) unsigned char lds[(ldsb) > 0 ? (ldsb) : 16];         \
-    if constexpr (!Hold<Args>::kOn) touch_arguments<sizeof(Args) + 16>();    \
-    Hold<Args>::all(a);    \
-    const Blk b = launch_blk();                                                                  \
-    const unsigned long long t0 = trace ? op_trace_begin() : 0ull;    \
+    if constexpr (!Hold<Args>::kOn) touch_arguments<sizeof(Args) + sizeof(LaunchArgs) + extra>();  \
+    Hold<Args>::all(a, l);                                                                       \
+    const Blk b = launch_blk(l);                                                                 \
+    const unsigned long long t0 = l.trace ? op_trace_begin() : 0ull;                             \
     call;                                                                                        \
-    op_trace_end(trace, tag, t0, launch_lin(), launch_total());                                  \
+    op_trace_end(l.trace, l.tag, t0, launch_lin(l), launch_total(l));
+#define KDEF(name, threads, ldsb, Args, call)                                                    \
+  extern "C" __global__ void __launch_bounds__(threads) opara_k_##name(Args a, LaunchArgs l) {   \
+    KBODY(ldsb, Args, call, 0)                                                                   \
   }
 // second launch bound: wavefronts per SIMD the register allocation must leave room for
-#define KDEF2(name, threads, waves_per_simd, ldsb, Args, call)                                                \
-  extern "C" __global__ void __launch_bounds__(threads, waves_per_simd) opara_k_##name(Args a, int32_t tag, unsigned long long *trace) { \
-    __shared__ __attribute__((aligned(16))) unsigned char lds[(ldsb) > 0 ? (ldsb) : 16];                      \
-    if constexpr (!Hold<Args>::kOn) touch_arguments<sizeof(Args) + 16>();    \
-    Hold<Args>::all(a);    \
-    const Blk b = launch_blk();                                                                               \
-    const unsigned long long t0 = trace ? op_trace_begin() : 0ull;    \
-    call;                                                                                                     \
-    op_trace_end(trace, tag, t0, launch_lin(), launch_total());                                               \
+#define KDEF2(name, threads, waves_per_simd, ldsb, Args, call)                                   \
+  extern "C" __global__ void __launch_bounds__(threads, waves_per_simd) opara_k_##name(Args a, LaunchArgs l) { \
+    KBODY(ldsb, Args, call, 0)                                                                   \
   }
-
-// ... and a fourth argument: the element-wise operator that follows
-#define KDEFT(name, threads, waves_per_simd, ldsb, Args, call)                                                \
-  extern "C" __global__ void __launch_bounds__(threads, waves_per_simd) opara_k_##name(Args a, int32_t tag, unsigned long long *trace, \
-                                                                                       TailArgs tail) {       \
-    __shared__ __attribute__((aligned(16))) unsigned char lds[(ldsb) > 0 ? (ldsb) : 16];                      \
-    if constexpr (!Hold<Args>::kOn) touch_arguments<sizeof(Args) + 16 + sizeof(TailArgs)>();    \
-    Hold<Args>::all(a);    \
-    const Blk b = launch_blk();                                                                               \
-    const unsigned long long t0 = trace ? op_trace_begin() : 0ull;    \
-    call;                                                                                                     \
-    op_trace_end(trace, tag, t0, launch_lin(), launch_total());                                               \
+#define KDEFT(name, threads, waves_per_simd, ldsb, Args, call)                                   \
+  extern "C" __global__ void __launch_bounds__(threads, waves_per_simd) opara_k_##name(Args a, LaunchArgs l, TailArgs tail) { \
+    KBODY(ldsb, Args, call, sizeof(TailArgs))                                                    \
   }
 
 KDEF2(igemm_f16_t128x64, 256, 2, lds_tile(128, 64, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 64, 2, 2, 2, 0>(a, b, lds)))
@@ -2197,18 +2188,28 @@ hipError_t launch_noop(hipStream_t s) {
 }
 
 namespace {
-// What every planned kernel is given: its by-value record at offset 0, the operator id, the
-// timeline buffer and the element-wise operator that follows; a kernel takes as many as it declares.
+// What every planned kernel is given: its by-value record at offset 0, the launch's own arguments
+// and the element-wise operator that follows; a kernel takes as many as it declares.
 struct PlanParams {
   KernelArgs args;
-  int32_t tag;
-  unsigned long long *trace;
+  LaunchArgs launch;
   TailArgs tail;
-  void *ptr[4];
+  void *ptr[3];
   explicit PlanParams(const KernelPlan &p)
-      : args(p.args), tag(p.tag), trace(g_host_op_trace), tail(p.tail), ptr{&args, &tag, &trace, &tail} {}
+      : args(p.args), launch{p.tag, (int32_t)p.gx, (int32_t)p.gy, (int32_t)p.gz, g_host_op_trace}, tail(p.tail),
+        ptr{&args, &launch, &tail} {}
   PlanParams(const PlanParams &) = delete;
 };
+
+// Size of a kernel's operator record.
+size_t record_bytes(int id) {
+  switch (id) {
+#define X(name, A) case K_##name: return sizeof(A);
+    OPARA_KERNEL_LIST(X)
+#undef X
+    default: return sizeof(KernelArgs);
+  }
+}
 
 hipKernelNodeParams plan_node_params(const KernelPlan &p, PlanParams &params) {
   hipKernelNodeParams np = {};
@@ -2253,9 +2254,15 @@ hipError_t add_noop_node(hipGraph_t graph, const hipGraphNode_t *deps, size_t n_
   return hipGraphAddKernelNode(node, graph, deps, n_deps, &np);
 }
 
-hipError_t add_token_node(hipGraph_t graph, const TokenNodeArgs &t, const hipGraphNode_t *deps, size_t n_deps,
+hipError_t add_token_node(hipGraph_t graph, const KernelPlan &p, const TokenArgs &t, const hipGraphNode_t *deps, size_t n_deps,
                           hipGraphNode_t *node) {
-  TokenNodeArgs args = t;
+  const PlanParams params(p);
+  const size_t record = record_bytes(p.kernel);
+  TokenNodeArgs args = {};
+  __builtin_memcpy(args.real, &params.args, record);
+  __builtin_memcpy(args.real + record, &params.launch, sizeof(LaunchArgs));
+  __builtin_memcpy(args.real + record + sizeof(LaunchArgs), &params.tail, sizeof(TailArgs));
+  args.tok = t;
   void *kparams[1] = {&args};
   hipKernelNodeParams np = {};
   np.func = (void *)opara_k_token;

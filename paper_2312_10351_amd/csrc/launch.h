@@ -28,13 +28,16 @@ hipError_t group_prepare(uint32_t max_lds_bytes);   // raises the dynamic LDS li
 constexpr int kVerifyMaxOps = 1 << 16;
 constexpr int kVerifyMaxPreds = 16;
 struct TokenArgs { int32_t epoch, self, n_preds, delay; int32_t preds[kVerifyMaxPreds]; };
-// What a token node is given.  The operator's own argument record sits at offset 0 and the
-// record is as large as any kernel's: when the node of an instantiated graph is later
-// switched to the operator's kernel, the argument block the runtime holds for the node is
-// large enough and already valid for that kernel.
-struct TokenNodeArgs { KernelArgs real; TokenArgs tok; };
-static_assert(sizeof(TokenNodeArgs) >= sizeof(KernelArgs) + 16 + sizeof(TailArgs), "record smaller than a kernel's arguments");
-hipError_t add_token_node(hipGraph_t graph, const TokenNodeArgs &t, const hipGraphNode_t *deps, size_t n_deps,
+// What a token node is given: the whole argument segment of the operator's own kernel, then the
+// token's record.  When the node of an instantiated graph is later switched to the operator's
+// kernel, the argument block the runtime holds for the node is larger than that kernel's and
+// already valid for it.  (The planned kernels take nothing implicit; the segment sizes of the
+// built code object are tested against each other.)
+struct TokenNodeArgs {
+  alignas(8) unsigned char real[sizeof(KernelArgs) + sizeof(LaunchArgs) + sizeof(TailArgs)];
+  TokenArgs tok;
+};
+hipError_t add_token_node(hipGraph_t graph, const KernelPlan &p, const TokenArgs &t, const hipGraphNode_t *deps, size_t n_deps,
                           hipGraphNode_t *node);
 // Switches a kernel node of an instantiated graph to the planned launch `p` (kernel, grid,
 // workgroup size, arguments).  The node keeps its place and dependencies.

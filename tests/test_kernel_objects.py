@@ -52,3 +52,27 @@ def test_no_kernel_takes_arguments_from_two_places(code_object):
     assert {"opara_k_group_f16_heavy", "opara_k_attention_f16", "opara_k_token"} <= set(found)
     preloaded = {k: struct.unpack_from("<H", d, 58)[0] & 127 for k, d in found.items()}
     assert not any(preloaded.values()), {k: v for k, v in preloaded.items() if v}
+
+
+def segments(path):
+    """{kernel: (bytes of its argument segment, kinds of its arguments)}"""
+    notes = subprocess.run([READELF, "--notes", str(path)], check=True, capture_output=True, text=True).stdout
+    out = {}
+    for block in re.split(r"\n  - \.agpr_count:|\n  - \.args:", notes)[1:]:
+        name = re.search(r"^    \.name: +(opara_k_\w+)$", block, re.M)
+        if name:
+            out[name.group(1)] = (int(re.search(r"\.kernarg_segment_size: (\d+)", block).group(1)), re.findall(r"\.value_kind: +(\w+)", block))
+    return out
+
+
+def test_a_marker_node_has_room_for_every_kernel_it_may_be_switched_to(code_object):
+    """A node of the multi-stream graph is made with the marker kernel and later switched to its
+    operator's kernel in place: the argument block that the runtime holds for the node must be
+    large enough for it, implicit arguments included."""
+    found = segments(code_object)
+    count = B.opara_kernel_count()
+    planned = ["opara_k_" + B.opara_kernel_info(i)[0] for i in range(count)]
+    assert set(planned) <= set(found)
+    room = found["opara_k_token"][0]
+    assert {k: found[k][0] for k in planned if found[k][0] > room} == {}
+    assert {k for k in planned if any(kind.startswith("hidden") for kind in found[k][1])} == set()
