@@ -76,3 +76,37 @@ def test_a_marker_node_has_room_for_every_kernel_it_may_be_switched_to(code_obje
     room = found["opara_k_token"][0]
     assert {k: found[k][0] for k in planned if found[k][0] > room} == {}
     assert {k for k in planned if any(kind.startswith("hidden") for kind in found[k][1])} == set()
+
+
+def scalar_registers(operand):
+    run = re.fullmatch(r"s\[(\d+):(\d+)\]", operand)
+    if run:
+        return set(range(int(run.group(1)), int(run.group(2)) + 1))
+    return {int(operand[1:])} if re.fullmatch(r"s\d+", operand) else set()
+
+
+def test_memory_instructions_wait_for_scalar_registers_that_vector_instructions_write(code_object):
+    """A memory instruction may read a scalar register five wait states after a vector instruction
+    wrote it, and a load to workgroup memory m0 one after a scalar instruction did.  The compiler
+    sees to that for its own instructions, but does not look into inline assembly."""
+    text = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", "--no-show-raw-insn", str(code_object)], check=True, capture_output=True, text=True).stdout
+    loads, at, written, m0 = 0, 0, {}, -9
+    for line in text.splitlines():
+        line = line.split("//")[0].strip()
+        if line.endswith(">:"):
+            written = {}
+        op, _, rest = line.partition(" ")
+        operands = rest.replace(",", " ").split()
+        nop = re.fullmatch(r"s_nop (\d+)", line)
+        at += int(nop.group(1)) + 1 if nop else 1
+        if op.startswith(("v_readfirstlane", "v_readlane", "v_cmp")) and operands:
+            written.update({r: at for r in scalar_registers(operands[0])})
+        elif op.startswith(("buffer_", "global_", "flat_")):
+            read = set().union(*map(scalar_registers, operands))
+            assert not {r for r in read if at - written.get(r, -9) <= 5}, line
+            if operands[-1:] == ["lds"]:
+                loads += 1
+                assert at - m0 >= 2, line
+        elif operands[:1] == ["m0"]:
+            m0 = at
+    assert loads > 1000
