@@ -185,7 +185,6 @@ int capture_fused(opara_dag *g, opara_exec **out) {
   std::vector<int32_t> indeg(n), wave;
   std::vector<char> done(n, 0);
   for (int32_t v = 0; v < n; ++v) indeg[v] = g->pred_off[v + 1] - g->pred_off[v];
-  uint32_t max_lds = 0;
   int32_t placed = 0;
   const std::vector<Merge> merges = current_op_trace() ? std::vector<Merge>() : find_merges(g);
   std::vector<const Merge *> merge_of(n, nullptr);
@@ -254,7 +253,6 @@ int capture_fused(opara_dag *g, opara_exec **out) {
         }
         node.lds = std::max(node.lds, 16u);
         node.blocks = (uint32_t)end;
-        max_lds = std::max(max_lds, node.lds);
       }
       for (int32_t v : members) e->fused_node_of[v] = (int32_t)e->fused.size();
       e->fused.push_back(node);
@@ -324,7 +322,7 @@ int capture_fused(opara_dag *g, opara_exec **out) {
   }
   {
     hipGraphNode_t node = nullptr, last = nullptr;
-    HIP_TRY(group_prepare(std::max(max_lds, 16u)));
+    HIP_TRY(group_prepare());
     HIP_TRY(hipGraphCreate(&e->graph, 0));
     for (const opara_exec::FusedNode &fn : e->fused) {
       if (!fn.launches) continue;
@@ -927,7 +925,7 @@ extern "C" int opara_capture_chained(opara_dag *g, void *workspace, uint64_t wor
   opara_exec *e = new (std::nothrow) opara_exec();
   if (!e) { set_error("out of memory"); return OPARA_ENOMEM; }
   {
-    HIP_TRY(chain_max_lds(lds));
+    HIP_TRY(chain_prepare());
     HIP_TRY(hipMemcpy(workspace, host.data(), lay.bytes, hipMemcpyHostToDevice));
     unsigned char *ws = (unsigned char *)workspace;
     ChainArgs ca;

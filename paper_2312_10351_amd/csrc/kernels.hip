@@ -6,6 +6,7 @@
 // with wavefront (64-lane) reductions where rows are reduced.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <algorithm>
 #include <type_traits>
 #include "kernel_args.h"
 #include "launch.h"
@@ -1471,6 +1472,9 @@ constexpr int lds_tile(int bn, int bm, int stages) { return stages * (bn + bm) *
 constexpr int lds_split(int ni, int nj, int s) { return 4 * split_ring_bytes(ni, nj, s); }
 constexpr int lds_direct(int waves) { return waves * 32 * 36 * 4; }
 constexpr int kLdsGap = 4 * 64 * 4, kLdsRow = 16, kLdsNone = 0;
+// ... of the bodies that group and chained kernels hold: the most a node of theirs asks for.
+constexpr int kLdsLargestBody = std::max({lds_igemm(64, 64), lds_tile(128, 128, 2), lds_tile(64, 64, 3), lds_tile(128, 64, 2),
+                                          lds_split(1, 1, 3), lds_split(2, 2, 2), lds_split(4, 2, 1), lds_split(4, 4, 1), lds_direct(4)});
 
 // Operator timeline (tracing aid, off by default): while a buffer is set, thread 0 of every
 // workgroup folds the 100 MHz device clock at its start and end into the operator's slot
@@ -2301,12 +2305,13 @@ bool group_kernel_ok(int id, bool *light) {
   return f >= 0;
 }
 
-hipError_t group_prepare(uint32_t max_lds_bytes) {
+// The limit is the kernel's, not the executor's: it is the same for every capture, so that none
+// lowers it under an executor that is still in use.
+hipError_t group_prepare() {
   for (int f16 = 0; f16 < 2; ++f16)
     for (int flavor = 0; flavor < 3; ++flavor)
       for (int traced = 0; traced < 2; ++traced) {
-        hipError_t err = hipFuncSetAttribute(group_func(f16, flavor, traced), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)max_lds_bytes);
+        hipError_t err = hipFuncSetAttribute(group_func(f16, flavor, traced), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLargestBody);
         if (err != hipSuccess) return err;
       }
   return hipSuccess;
@@ -2340,10 +2345,10 @@ void *chain_func(bool f16, bool light) {
 
 bool chain_kernel_ok(int id, bool *light) { return group_kernel_ok(id, light); }
 
-hipError_t chain_max_lds(uint32_t lds_bytes) {
+hipError_t chain_prepare() {
   for (int f16 = 0; f16 < 2; ++f16)
     for (int light = 0; light < 2; ++light) {
-      hipError_t err = hipFuncSetAttribute(chain_func(f16, light), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+      hipError_t err = hipFuncSetAttribute(chain_func(f16, light), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLargestBody);
       if (err != hipSuccess) return err;
     }
   return hipSuccess;
@@ -2399,7 +2404,7 @@ hipError_t persist_max_workgroups(bool f16, uint32_t lds_bytes, uint32_t *n_work
   err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (err != hipSuccess) return err;
   const void *func = f16 ? (const void *)opara_k_persist_f16 : (const void *)opara_k_persist_f32;
-  err = hipFuncSetAttribute(func, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  err = hipFuncSetAttribute(func, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPersistMaxLds);   // for every executor alike
   if (err != hipSuccess) return err;
   err = f16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, opara_k_persist_f16, 256, lds_bytes)
             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, opara_k_persist_f32, 256, lds_bytes);

@@ -21,7 +21,7 @@ int group_flavor(int kernel_id);
 hipError_t add_group_node(hipGraph_t graph, bool f16, int flavor, const GroupArgs &ga, uint32_t n_blocks,
                           uint32_t lds_bytes, const hipGraphNode_t *deps, size_t n_deps, hipGraphNode_t *node);
 hipError_t launch_group(bool f16, int flavor, const GroupArgs &ga, uint32_t n_blocks, uint32_t lds_bytes, hipStream_t s);
-hipError_t group_prepare(uint32_t max_lds_bytes);   // raises the dynamic LDS limit of the group kernels once
+hipError_t group_prepare();   // lets the group kernels use as much LDS as their largest body needs
 
 // Dependency self-check (see opara_verify_dependencies): a token node marks its
 // operator as done after a short delay and counts predecessors not yet marked.
@@ -124,7 +124,7 @@ struct ChainArgs {
   int32_t n, total;
 };
 bool chain_kernel_ok(int kernel_id, bool *light);
-hipError_t chain_max_lds(uint32_t lds_bytes);
+hipError_t chain_prepare();
 hipError_t add_chain_node(hipGraph_t graph, bool f16, bool light, const ChainArgs &a, uint32_t lds_bytes,
                           const hipGraphNode_t *deps, size_t n_deps, hipGraphNode_t *node);
 hipError_t launch_chain(bool f16, bool light, const ChainArgs &a, uint32_t lds_bytes, hipStream_t s);
