@@ -8,7 +8,7 @@ from oracle import executor
 from workloads import Builder
 from paper_2312_10351_amd import binding as B
 from paper_2312_10351_amd.runtime import Session
-from util import compare_all
+from util import compare_all, mismatch
 
 pytestmark = pytest.mark.gpu
 
@@ -55,22 +55,41 @@ def test_attention_outside_its_range_stays_three_launches(heads, seq, d, dtype):
     run_fused(attention(heads, seq, d, dtype), 3)
 
 
-def test_attention_with_masked_scores():
-    """Rows that hold minus infinity and the type's lowest value."""
-    wl = attention(2, 64, 64, "f16")
-    wl.ext_inputs[0][3] = 60000.0
-    wl.ext_inputs[1][:, 5] = -60000.0
-    s = Session(wl)
+def masked_attention(seq):
+    """Rows 1 and 16 of the first head: keys at the ends of the kernels' lane groups have scores of
+    minus infinity and key 5 the lowest finite one; the same rows of the second head: all keys do."""
+    wl = attention(2, seq, 64, "f16")
+    q, k = wl.ext_inputs[:2]
+    q[:, [0, 64]] = 0
+    q[[1, 16], 0] = q[[1, 16], 64] = 65504
+    k[:, 0] = 0
+    k[[i for i in (0, 15, 16, 63, 127, 128, 255, 256, seq - 1) if i < seq], 0] = -60000
+    k[5, 0] = -8                                             # 65504 * -8 / sqrt(64), and a little
+    k[:, 64] = -60000
+    return wl
+
+
+@pytest.mark.parametrize("seq", [18, 64, 129, 300, 512])
+def test_attention_with_masked_scores(seq):
+    """Rows that hold minus infinity and the type's lowest value beside other scores, and nothing but
+    minus infinity."""
+    s = Session(masked_attention(seq))
     try:
         got = []
         for mode in (B.SEQUENTIAL, B.FUSED):
             s.clear_outputs()
             s.replay(s.capture(mode))
             got.append([s.output(v).astype(np.float64) for v in range(3)])
+        scores, probs = got[0][:2]
+        for row in (1, 16):
+            r = scores.reshape(2, seq, seq)[0, row]
+            assert np.isneginf(r).sum() >= 4 and r.min(where=np.isfinite(r), initial=0) == -65504 and not (r == np.inf).any()
+            assert np.isfinite(r).sum() > 8 and np.isfinite(probs.reshape(2, seq, seq)[0, row]).all()
+            assert np.isneginf(scores.reshape(2, seq, seq)[1, row]).all()
         for a, b in zip(*got):
-            assert (np.isnan(a) == np.isnan(b)).all()
+            assert (np.isnan(a) == np.isnan(b)).all() and (np.isinf(a) == np.isinf(b)).all()
             ok = np.isfinite(a)
-            assert (np.isfinite(b) == ok).all() and np.allclose(a[ok], b[ok], rtol=2e-3, atol=2e-3)
+            assert np.allclose(a[ok], b[ok], rtol=2e-3, atol=2e-3)
     finally:
         s.close()
 
@@ -173,5 +192,91 @@ def test_overlapping_buffers_are_not_merged():
         assert np.abs(got - ref[2].astype(np.float64)).max() < 1e-2
         B.opara_exec_destroy(exe)
         B.opara_dag_destroy(dag)
+    finally:
+        s.close()
+
+
+def run_with(wl, rebind, launches):
+    """Fused executor of `wl` with buffers that `rebind(session, descs, ext)` has changed: it must
+    launch `launches` kernels.  Returns the session (its `descs` and `ext_dev` hold the results)."""
+    s = Session(wl)
+    ext = [t.data_ptr() for t in s.ext_dev]
+    rebind(s, s.descs, ext)
+    dag = B.opara_build_dag(s.descs, ext)
+    B.opara_order_launch(dag)
+    exe = B.opara_capture(dag, s.make_streams(1).handles[:1], B.FUSED)
+    try:
+        assert B.opara_exec_info(exe)[0] == launches
+        torch.cuda.synchronize()
+        s.replay(exe)
+    finally:
+        B.opara_exec_destroy(exe)
+        B.opara_dag_destroy(dag)
+    return s
+
+
+@pytest.mark.parametrize("where", ["operand", "extra", "other input"])
+def test_overlapping_buffers_are_not_merged_with_a_tail(where):
+    b = Builder("tail", "f16")
+    x, e, z = (b.ext((83, 520)) for _ in range(3))
+    b.rowwise("add", [b.gemm(x, 83, 520, 520, extras=[e]), z], 83, 520)
+    wl = b.build(37, random_bias=True, he_init=True)
+    ref = executor.run_dag(wl)
+    slot = {"operand": 0, "extra": 1, "other input": 2}[where]
+
+    def rebind(s, descs, ext):
+        descs[1].out = ext[slot]
+
+    run_with(wl, lambda *a: None, 1).close()
+    s = run_with(wl, rebind, 2)
+    try:
+        assert mismatch(s.output(0), ref[0], "f16") is None
+        assert mismatch(s.ext_dev[slot].cpu().numpy().reshape(83, 520), ref[1], "f16") is None
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("kind", ["conv", "conv 1x1", "gemm", "bgemm", "pool", "gavgpool", "softmax", "add", "concat"])
+def test_a_concatenation_over_what_an_earlier_operator_reads_is_not_written_in_place(kind):
+    b = Builder("concat", "f16")
+    image = (16, 9, 9)
+    if kind in ("conv", "conv 1x1"):
+        x = b.ext(image)
+        o = b.conv(x, 16, 3 if kind == "conv" else 1, pad=1 if kind == "conv" else 0)
+    elif kind == "pool":
+        o = b.pool("maxpool", b.ext(image), 3, 1, 1)
+    elif kind == "gavgpool":
+        o = b.gavgpool(b.ext(image))
+    elif kind == "gemm":
+        o = b.gemm(b.ext((9, 520)), 9, 520, 16)
+    elif kind == "bgemm":
+        o = b.add("bgemm", [b.ext((16, 64)), b.ext((16, 64))], [(16, 64)] * 2, (2, 16, 16), dict(mode="qk", alpha=0.125, heads=2, seq=16, dhead=32))
+    elif kind == "concat":
+        o = b.add("concat", [b.ext((9, 16)), b.ext((9, 8))], [(9, 16), (9, 8)], (9, 24), {"axis": 1})
+    else:
+        o = b.rowwise(kind, [b.ext((9, 16))] * (2 if kind == "add" else 1), 9, 16)
+    shape = b.shape(o)
+    if len(shape) == 3 and kind != "bgemm":
+        part, whole, axis = shape, (2 * shape[0],) + tuple(shape[1:]), 0
+    else:
+        part, whole, axis = (int(np.prod(shape)) // 8, 8), (int(np.prod(shape)) // 8, 16), 1
+    n = int(np.prod(part))
+    u = b.add("relu", [b.ext(part)], [part], part)
+    v = b.add("gelu", [o], [part], part)
+    c = b.add("concat", [u, v], [part] * 2, whole, {"axis": axis})
+    wl = b.build(47, random_bias=True, he_init=True)
+    ref = executor.run_dag(wl)
+    keep = []
+
+    def rebind(s, descs, ext):                               # the concatenation's buffer begins with what `o` reads
+        keep.append(torch.zeros(max(2 * n, s.ext_dev[0].numel()), dtype=torch.float16, device=s.device))
+        keep[0][:s.ext_dev[0].numel()] = s.ext_dev[0].reshape(-1)
+        ext[0] = descs[c].out = keep[0].data_ptr()
+
+    run_with(wl, lambda *a: None, 2).close()
+    s = run_with(wl, rebind, 3)
+    try:
+        s.out_dev[c] = keep[0][:2 * n]
+        assert not compare_all(s, ref)
     finally:
         s.close()
