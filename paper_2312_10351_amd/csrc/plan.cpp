@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <tuple>
 #include <vector>
 #include "opara_internal.h"
 
@@ -41,6 +42,9 @@ const TileKernel kTileKernels[] = {
 };
 constexpr int kTileKernelCount = sizeof kTileKernels / sizeof kTileKernels[0];
 constexpr double kCus = 256.0;
+bool tile_kernel_is_f16(int id) {
+  return std::any_of(kTileKernels, kTileKernels + kTileKernelCount, [&](const TileKernel &t) { return t.ids[1] == id; });
+}
 
 int fail(const char *what, const opara_op_desc &op) {
   set_error("operator type %d: %s", op.op_type, what);
@@ -287,57 +291,64 @@ int plan_concat(const opara_op_desc &op, const void *const *in, KernelPlan *out)
 
 }  // namespace
 
-// Tile shapes of contractions that run together (the members of one launch, or a single
-// operator).  Small tiles finish one operator sooner (more CUs share it), large ones move
+// Tile shapes of contractions that run together (the contractions of a wave, or one by itself).
+// Small tiles finish one operator sooner (more CUs share it), large ones move
 // fewer bytes per multiply-add; what counts is the longer of the time the work takes on all
-// CUs together and the time the longest workgroup takes.  For every bound L on the latter,
-// each operator takes its cheapest tile shape within L; the best L wins.
+// CUs together and the time the longest workgroup takes.  For every bound on the latter,
+// each operator takes its cheapest tile shape within it; the best bound wins.  The bounds are
+// visited in increasing order, and each only changes the one operator whose shape it admits
+// (trying every operator again under every bound took seconds for a wave of some thousand).
 void choose_tiles(KernelPlan *const *plans, int n) {
-  struct Option { double longest, work; };
-  std::vector<std::vector<Option>> opt(n);
-  std::vector<double> bounds;
+  struct Option { double longest, work; int op, shape; };
+  std::vector<Option> options;
   for (int i = 0; i < n; ++i) {
     const IgemmArgs &a = plans[i]->args.igemm;
-    const bool f16 = plans[i]->kernel == kTileKernels[0].ids[1] || std::any_of(kTileKernels, kTileKernels + kTileKernelCount,
-                     [&](const TileKernel &t) { return t.ids[1] == plans[i]->kernel; });
+    const bool f16 = tile_kernel_is_f16(plans[i]->kernel);
     const double steps = std::ceil(a.K * (f16 ? 2.0 : 4.0) / 128.0);
-    for (const TileKernel &t : kTileKernels) {
+    for (int k = 0; k < kTileKernelCount; ++k) {
+      const TileKernel &t = kTileKernels[k];
       const double tiles = (double)cdiv(a.M, t.bm) * cdiv(a.N, t.bn) * plans[i]->gz;
       const double least = f16 ? 0.0 : t.bn * t.bm * 32 * 2.0 / 0.6e6;
       Option o;
+      o.op = i;
+      o.shape = k;
       o.longest = steps * std::max(t.alone, least) + t.fixed;
       o.work = tiles * (steps * std::max(t.busy, least) + t.fixed) / kCus * (n > 1 ? t.together : 1.0);
       if (n == 1 && tiles > kCus && tiles < 4 * kCus)      // a single launch: whole rounds over the CUs
         o.work *= std::ceil(tiles / kCus) * kCus / tiles;
-      opt[i].push_back(o);
-      bounds.push_back(o.longest);
+      options.push_back(o);
     }
   }
-  std::sort(bounds.begin(), bounds.end());
-  double best = -1.0;
-  std::vector<int> pick(n), take(n);
-  for (double bound : bounds) {
-    double work = 0.0, longest = 0.0;
-    bool ok = true;
-    for (int i = 0; i < n && ok; ++i) {
-      int k = -1;
-      for (int j = 0; j < kTileKernelCount; ++j)
-        if (opt[i][j].longest <= bound && (k < 0 || opt[i][j].work < opt[i][k].work)) k = j;
-      ok = k >= 0;
-      if (!ok) break;
-      take[i] = k;
-      work += opt[i][k].work;
-      longest = std::max(longest, opt[i][k].longest);
+  std::sort(options.begin(), options.end(), [](const Option &a, const Option &b) {
+    return std::tie(a.longest, a.op, a.shape) < std::tie(b.longest, b.op, b.shape);
+  });
+  // take[i]: the operator's cheapest shape so far, and how many of these decisions (in the order
+  // they fall) belong to the best bound.
+  std::vector<const Option *> take(n, nullptr);
+  std::vector<const Option *> made;
+  double work = 0.0, longest = 0.0, best = -1.0;
+  size_t best_made = 0;
+  int missing = n;
+  for (size_t j = 0; j < options.size(); ++j) {
+    const Option &o = options[j];
+    const Option *&t = take[o.op];
+    if (!t || o.work < t->work) {
+      work += o.work - (t ? t->work : 0.0);
+      missing -= t ? 0 : 1;
+      t = &o;
+      longest = o.longest;                                 // no operator had a longer one
+      made.push_back(&o);
     }
-    if (!ok) continue;
+    if (missing || (j + 1 < options.size() && options[j + 1].longest == o.longest)) continue;
     const double cost = std::max(work, longest);
-    if (best < 0.0 || cost < best) { best = cost; pick = take; }
+    if (best < 0.0 || cost < best) { best = cost; best_made = made.size(); }
   }
+  std::vector<int> pick(n, 0);
+  for (size_t j = 0; j < best_made; ++j) pick[made[j]->op] = made[j]->shape;
   for (int i = 0; i < n; ++i) {
     const TileKernel &t = kTileKernels[pick[i]];
-    const bool f16 = std::any_of(kTileKernels, kTileKernels + kTileKernelCount, [&](const TileKernel &q) { return q.ids[1] == plans[i]->kernel; });
     const IgemmArgs &a = plans[i]->args.igemm;
-    plans[i]->kernel = t.ids[f16];
+    plans[i]->kernel = t.ids[tile_kernel_is_f16(plans[i]->kernel)];
     plans[i]->gx = cdiv(a.M, t.bm);
     plans[i]->gy = cdiv(a.N, t.bn);
     plans[i]->args.igemm.div_gx = div_magic((int64_t)plans[i]->gx);
