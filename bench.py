@@ -9,11 +9,13 @@ buffers, each as ONE hipGraph:
   persistent executor  one kernel, Alg. 2 order, dependencies as completion flags
   chained executor     the same without a work-item loop: one tile per workgroup, blocks in queue order
   fused executor       the launch queue cut into waves, a wave of several operators is one kernel
-The headline value is the fastest operator-parallel executor (named in config.mode) on the
-GoogLeNet-like fp16 DAG; the other configs are reported beside it, each with its own
-roofline and CPU-oracle block.  One JSON line on stdout.
+The headline value is the fastest operator-parallel executor (named in config.executor) on the
+GoogLeNet-like fp16 DAG; of the other configs the line holds the speed-ups.  One short JSON line
+on stdout; everything measured, each config with its own roofline and CPU-oracle block, on
+stderr or in the file that --details names.
 """
 import argparse
+import contextlib
 import json
 import os
 import sys
@@ -260,8 +262,9 @@ def bench_config(index, steps, warmup, zero_copy_concat="auto", cpu_budget_s=0.0
         res["roofline"] = kern
         # ---- overlap measured inside the kernels (operator timeline: no profiler attached)
         from paper_2312_10351_amd.timeline import operator_overlap
+        # (the fused executor leaves stamps only where every operator runs by itself: without merges)
         res["operator_overlap"] = {name: operator_overlap(s.operator_trace(mode))
-                                   for name, mode in (("sequential", B.SEQUENTIAL), ("multi_stream_graph", B.PARALLEL), ("fused", B.FUSED))}
+                                   for name, mode in (("sequential", B.SEQUENTIAL), ("multi_stream_graph", B.PARALLEL), ("fused_without_merges", B.FUSED))}
         # ---- the oracle on the host cores, and the timed executor's result against it
         if cpu_budget_s > 0:
             block, ref = oracle_pass(wl, cpu_budget_s, one_thread=index == 1)
@@ -302,6 +305,13 @@ def calibration_copy(reps=10, mib=64):
         s.close()
 
 
+def rounded(v):
+    """Numbers to seven digits."""
+    if isinstance(v, dict):
+        return {k: rounded(x) for k, x in v.items()}
+    return float(f"{v:.7g}") if isinstance(v, float) else v
+
+
 MODE_TEXT = {
     "persistent": "persistent executor: one hipGraph replay = the serial stem as kernel nodes, then one kernel for the rest "
                   "(work items in launch-queue order, dependencies as completion flags)",
@@ -310,6 +320,29 @@ MODE_TEXT = {
     "multi_stream_graph": "multi-stream hipGraph replay (Alg. 1 streams, Alg. 2 launch order)",
     "fused": "fused executor: one hipGraph replay = a chain of kernel nodes, one per wave of the Alg. 2 launch queue; a wave of "
              "several operators is ONE kernel whose grid is the sum of their grids"}
+
+
+def result_line(steps, warmup, head, others, cpu_baseline=None):
+    """The line on standard output: short enough to be kept whole by whoever keeps the end of the
+    output only."""
+    ratio = lambda r: {k: round(r["speedup_" + k], 3) for k in ("multi_stream_graph", "persistent", "chained", "fused")}
+    roofline = {k: head["roofline"][k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic", "launches_per_step", "avg_launch_us")}
+    line = {
+        "metric": "batch1_dag_latency_us", "value": head["best"]["median_us"], "unit": "us",
+        "n_gpus": 1, "steps": steps, "warmup": warmup,
+        "ms_per_step": head["best"]["mean_us"] / 1e3, "higher_is_better": False, "scaling": "weak",
+        "vs_baseline": None, "dtype": "f16", "data": "synthetic",
+        "config": {"workload": "googlenet_like fp16 batch 1, 1x3x224x224, 81 operators", "model": "googlenet_like", "global_batch": 1,
+                   "parallelism": "operators", "concatenation": "zero-copy" if head["zero_copy_concat"] else "explicit",
+                   "executor": head["best_mode"]},
+        "throughput_inferences_per_s": 1e6 / head["best"]["back_to_back_us"],
+        "sequential_hipgraph_us": head["sequential"]["median_us"],
+        "speedup_vs_sequential_hipgraph": {r["workload"]: ratio(r) for r in [head] + others},
+        "dag_roofline_fraction": head["roofline_fraction"], "roofline": roofline,
+    }
+    if cpu_baseline:
+        line["cpu_baseline"] = cpu_baseline
+    return rounded(line)
 
 
 def main():
@@ -322,6 +355,7 @@ def main():
     ap.add_argument("--layouts", default="both", choices=["both", "zero_copy", "explicit"],
                     help="concatenation layouts of the headline DAG to run (profiling runs take one)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--details", help="file for everything measured (default: standard error)")
     ap.add_argument("--calibration-copy", action="store_true",
                     help="also launch a 64 MiB streaming kernel 10 times (scale for rocprofv3 --pmc traffic counters)")
     a = ap.parse_args()
@@ -341,32 +375,10 @@ def main():
     alt = next((r for r in heads if r is not head), None)
     others = [bench_config(idx, max(100, a.steps // 4), a.warmup, cpu_budget_s=1.0 * cpu, traffic=traffic)
               for idx in [int(x) for x in a.configs.split(",") if x != ""]]
-    line = {
-        "metric": "batch1_dag_latency_us", "value": head["best"]["median_us"], "unit": "us",
-        "n_gpus": 1, "steps": a.steps, "warmup": a.warmup,
-        "ms_per_step": head["best"]["mean_us"] / 1e3, "higher_is_better": False, "scaling": "weak",
-        "vs_baseline": None, "dtype": "f16", "data": "synthetic",
-        "config": {"workload": "googlenet_like fp16 batch 1, 1x3x224x224, 81 operators (configs[1])",
-                   "concatenation": ("zero-copy: the branches write their channel slices of the concatenated tensor, "
-                                     "%d of 81 operators are launched; the sequential baseline uses the same layout"
-                                     % head["n_ops_launched"]) if head["zero_copy_concat"] else "explicit concatenation kernels",
-                   "mode": MODE_TEXT[head["best_mode"]]},
-        "throughput_inferences_per_s": 1e6 / head["best"]["back_to_back_us"],
-        "speedup_vs_sequential_hipgraph": head["speedup_vs_sequential"],
-        "speedup_by_executor": {k: head["speedup_" + k] for k in ("multi_stream_graph", "persistent", "chained", "fused")},
-        "speedup_vs_sequential_hipgraph_all_configs": {r["workload"]: dict(best=r["best_mode"], speedup=r["speedup_vs_sequential"],
-                                                                            multi_stream_graph=r["speedup_multi_stream_graph"],
-                                                                            persistent=r["speedup_persistent"], chained=r["speedup_chained"],
-                                                                            fused=r["speedup_fused"])
-                                                       for r in [head] + others},
-        "dag_roofline_fraction": head["roofline_fraction"],
-        "roofline": head["roofline"],
-        "headline": head,
-        "headline_other_concatenation": alt,
-        "other_configs": others,
-    }
-    if "cpu_baseline" in heads[0]:
-        line["cpu_baseline"] = heads[0]["cpu_baseline"]
+    line = result_line(a.steps, a.warmup, head, others, heads[0].get("cpu_baseline"))
+    details = {"executor": MODE_TEXT[head["best_mode"]], "headline": head, "headline_other_concatenation": alt, "other_configs": others}
+    with open(a.details, "w") if a.details else contextlib.nullcontext(sys.stderr) as f:
+        print(json.dumps(details), file=f, flush=True)
     print(json.dumps(line))
 
 
