@@ -27,7 +27,7 @@ struct IgemmArgs {
   int32_t relu;
   float alpha;
   uint32_t div_HoWo, div_Wo, div_Cin, div_kw;   // min(2^32 / d, 2^32 - 1): see fast_div
-  uint32_t x_bytes, w_bytes;    // what the operands span (one batch element), 0 if kOperandMaxBytes or more
+  uint32_t x_bytes, w_bytes;    // what the operands span (one batch element), 0 if one of them kOperandMaxBytes or more
   uint32_t div_gx;              // reciprocal of the grid's width
 };
 
@@ -140,6 +140,8 @@ struct AttnArgs {
   X(igemm_f16_quad4s, IgemmArgs)        \
   X(igemm_f32_direct4s, IgemmArgs)      \
   X(igemm_f32_quad4s, IgemmArgs)        \
+  X(igemm_f16_far128x128, IgemmArgs)    \
+  X(igemm_f32_far128x128, IgemmArgs)    \
   X(attention_f16, AttnArgs)            \
   X(igemm_f16_quad4s_tail, IgemmArgs) \
   X(igemm_f16_quad4_tail, IgemmArgs) \
@@ -225,7 +227,11 @@ struct GroupArgs {
 };
 // Operands of the LDS-fed contractions are addressed through 32-bit buffer offsets; this
 // offset is past the end of every operand they accept, and stays so with a row of K added.
+// Larger operands take a body of their own, which counts from the first row, or image, of its tile
+// of kFarTile x kFarTile (fp16, 394,000 x 4096 x 512: 1.8 ms; register-staged, with 64-bit
+// addresses, 6.5 ms).  Every body doing so costs the small networks 1.3 %.
 constexpr uint32_t kOperandMaxBytes = 0xc0000000u;
+constexpr int kFarTile = 128;
 
 // Tile geometry of the implicit-GEMM kernels (output columns x rows per workgroup).
 struct IgemmTile { int bn, bm; };

@@ -614,7 +614,9 @@ constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
 
 // LW / LX: rows of the two operands this lane fetches per K step (one load instruction each).
 // Steps must be requested in increasing order from kt0 on.
-template <typename T, int LW, int LX> struct Stager {
+// FAR: the operands span more than 32-bit offsets reach; offsets then count from the tile's first row
+// (gather: its first image).
+template <typename T, int LW, int LX, bool FAR = false> struct Stager {
   static constexpr int VE = Vec16<T>::N, BKE = 8 * VE, ES = (int)sizeof(T);
   i32x4 wbuf, xbuf;
   uint32_t wo[LW], xo[LX];                // byte offset of this lane's chunk in K step 0 (gather: of tap 0, 0)
@@ -632,18 +634,30 @@ template <typename T, int LW, int LX> struct Stager {
     K = a.K; gather = a.gather; H = a.H; W = a.W; Cin = a.Cin; kh = a.kh; kw = a.kw;
     kw0 = wslot * VE;
     kx0 = xslot * VE;
-    wbuf = buffer_of(w, a.w_bytes);
-    xbuf = buffer_of(x, a.x_bytes);
+    uint32_t wbytes = a.w_bytes, xbytes = a.x_bytes, wat = 0, xat = 0;   // wat, xat: what the offsets leave out, modulo 2^32
+    if constexpr (FAR) {
+      const int64_t wb = (int64_t)n0 * a.ldb, xb = gather ? (int64_t)(m0 / a.HoWo) * a.img_stride : (int64_t)m0 * a.lda;
+      const int64_t we = (int64_t)(a.N - 1) * a.ldb + a.K;
+      const int64_t xe = gather ? (int64_t)(a.M / a.HoWo) * a.img_stride : (int64_t)(a.M - 1) * a.lda + a.K;
+      w += wb;
+      x += xb;
+      wat = (uint32_t)(wb * ES);
+      xat = (uint32_t)(xb * ES);
+      wbytes = (uint32_t)min((we - wb) * ES, (int64_t)kOperandMaxBytes);
+      xbytes = (uint32_t)min((xe - xb) * ES, (int64_t)kOperandMaxBytes);
+    }
+    wbuf = buffer_of(w, wbytes);
+    xbuf = buffer_of(x, xbytes);
 #pragma unroll
     for (int i = 0; i < LW; ++i) {
       const int n = n0 + (first + i * step) * 8 + l8;
-      wo[i] = n < a.N ? ((uint32_t)n * (uint32_t)a.ldb + (uint32_t)kw0) * ES : kOperandMaxBytes;
+      wo[i] = n < a.N ? ((uint32_t)n * (uint32_t)a.ldb + (uint32_t)kw0) * ES - wat : kOperandMaxBytes;
     }
     if (!a.gather) {
 #pragma unroll
       for (int i = 0; i < LX; ++i) {
         const int m = m0 + (first + i * step) * 8 + l8;
-        xo[i] = m < a.M ? ((uint32_t)m * (uint32_t)a.lda + (uint32_t)kx0) * ES : kOperandMaxBytes;
+        xo[i] = m < a.M ? ((uint32_t)m * (uint32_t)a.lda + (uint32_t)kx0) * ES - xat : kOperandMaxBytes;
       }
     } else {
 #pragma unroll
@@ -653,7 +667,7 @@ template <typename T, int LW, int LX> struct Stager {
         const int oh = (int)fast_div(pix, a.Wo, a.div_Wo), ow = pix - oh * a.Wo;
         ih0[i] = m < a.M ? oh * a.sh - a.ph : -(1 << 28);          // no tap of a row past the end is inside
         iw0[i] = ow * a.sw - a.pw;
-        xo[i] = ((uint32_t)img * (uint32_t)a.img_stride + (uint32_t)(((oh * a.sh - a.ph) * a.W + iw0[i]) * a.Cin)) * ES;
+        xo[i] = ((uint32_t)img * (uint32_t)a.img_stride + (uint32_t)(((oh * a.sh - a.ph) * a.W + iw0[i]) * a.Cin)) * ES - xat;
       }
       const int k = kt0 * BKE + kx0;
       const int rs = (int)fast_div(k, a.Cin, a.div_Cin);
@@ -833,7 +847,7 @@ template <typename T, typename TL> struct Tail {
 // The rows of the weight operand are dealt to the fragments so that a lane's accumulators
 // are 4 * FN consecutive channels of one row (wide stores, whole lines per wavefront).
 // ---------------------------------------------------------------------------------
-template <typename T, int BN, int BM, int WN, int WM, int S, int COH, typename AR, typename TL = NoTail>
+template <typename T, int BN, int BM, int WN, int WM, int S, int COH, bool FAR = false, typename AR, typename TL = NoTail>
 __device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsigned char *lds, const TL &tail = TL{}) {
   typedef typename Vec16<T>::type V;
   constexpr int NW = WN * WM, STAGE = (BN + BM) * 128;
@@ -856,7 +870,7 @@ __device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsig
 
   // Slot of chunk c of a row: c ^ fw(row) for the weights, c ^ (row & 7) for the other operand.
   auto fw = [](int row) { return (row & 3) | (((row >> FB) & 1) << 2); };
-  Stager<T, LW, LX> st;
+  Stager<T, LW, LX, FAR> st;
   st.init(a, w, x, n0, m0, 0, wave, NW, lane, (lane & 7) ^ fw(wave * 8 + (lane >> 3)), (lane & 7) ^ (lane >> 3));
   const uint32_t base = lds_address(lds) + wave * 1024;
   auto issue = [&](int kt, int slot) {
@@ -868,7 +882,7 @@ __device__ __forceinline__ void igemm_tile_body(const AR &a, const Blk &b, unsig
   for (int i = 0; i < FN; ++i)
 #pragma unroll
     for (int j = 0; j < FM; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int nst = (a.K + Stager<T, LW, LX>::BKE - 1) / Stager<T, LW, LX>::BKE;
+  const int nst = (a.K + Stager<T, LW, LX, FAR>::BKE - 1) / Stager<T, LW, LX, FAR>::BKE;
 #pragma unroll
   for (int s = 0; s < S - 1; ++s)
     if (s < nst) issue(s, s);
@@ -1558,6 +1572,8 @@ KDEF2(igemm_f16_tile64x64, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_b
 KDEFT(igemm_f16_tile64x64_tail, 256, 2, lds_tile(64, 64, 3), IgemmArgs, (igemm_tile_body<half_t, 64, 64, 2, 2, 3, 0>(a, b, lds, tail)))
 KDEF2(igemm_f16_tile128x128, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 128, 2, 2, 2, 0>(a, b, lds)))
 KDEFT(igemm_f16_tile128x128_tail, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 128, 2, 2, 2, 0>(a, b, lds, tail)))
+KDEF2(igemm_f16_far128x128, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<half_t, 128, 128, 2, 2, 2, 0, true>(a, b, lds)))
+KDEF2(igemm_f32_far128x128, 256, 2, lds_tile(128, 128, 2), IgemmArgs, (igemm_tile_body<float, 128, 128, 2, 2, 2, 0, true>(a, b, lds)))
 KDEF(igemm_f16_t64x64, 256, lds_igemm(64, 64), IgemmArgs, (igemm_body<half_t, 64, 64, 2, 2, true, 0>(a, b, lds)))
 KDEF(igemm_f16_direct4, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 2, 2>(a, b, lds)))
 KDEF2(igemm_f16_quad4, 256, 2, lds_split(2, 2, 2), IgemmArgs, (igemm_split_body<half_t, 2, 2, 2, 0>(a, b, lds)))
@@ -1649,7 +1665,8 @@ KDEF2(attention_f16, 256, 3, kLdsAttention, AttnArgs, (attention_body(a, b, lds)
   X(igemm_##tn##_quad64x64, IgemmArgs, (igemm_split_body<T, 4, 4, 1, C>(a, b, lds)))                          \
   X(igemm_##tn##_tile64x64, IgemmArgs, (igemm_tile_body<T, 64, 64, 2, 2, 3, C>(a, b, lds)))                   \
   X(igemm_##tn##_t128x64, IgemmArgs, (igemm_tile_body<T, 128, 64, 2, 2, 2, C>(a, b, lds)))                    \
-  X(igemm_##tn##_tile128x128, IgemmArgs, (igemm_tile_body<T, 128, 128, 2, 2, 2, C>(a, b, lds)))
+  X(igemm_##tn##_tile128x128, IgemmArgs, (igemm_tile_body<T, 128, 128, 2, 2, 2, C>(a, b, lds)))               \
+  X(igemm_##tn##_far128x128, IgemmArgs, (igemm_tile_body<T, 128, 128, 2, 2, 2, C, true>(a, b, lds)))
 
 // ---------------------------------------------------------------------------------
 // Persistent executor.  One launch runs the whole DAG: each workgroup repeatedly takes

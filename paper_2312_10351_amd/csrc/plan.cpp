@@ -140,13 +140,19 @@ int plan_igemm(const opara_op_desc &op, const void *const *in, int kind, KernelP
   const int64_t es = f16 ? 2 : 4;
   const int64_t x_bytes = es * (a.gather ? (int64_t)(a.M / a.HoWo) * a.img_stride : (int64_t)(a.M - 1) * a.lda + a.K);
   const int64_t w_bytes = es * ((int64_t)(a.N - 1) * a.ldb + a.K);
-  const bool fits = x_bytes < (int64_t)kOperandMaxBytes && w_bytes < (int64_t)kOperandMaxBytes && a.K * es < (int64_t)1 << 29 &&
-                    (!a.gather || ((int64_t)a.kh * a.W + a.kw < 1 << 24 && a.Cin < 1 << 24));
+  const int64_t reach = kOperandMaxBytes;
+  const bool fits = x_bytes < reach && w_bytes < reach;
   a.x_bytes = fits ? (uint32_t)x_bytes : 0;
   a.w_bytes = fits ? (uint32_t)w_bytes : 0;
-  // [K][N] operand, or operands past the reach of 32-bit offsets: staged through registers.
-  if (a.b_kmajor || !fits)
+  // What 32-bit offsets have to span inside one tile of larger operands.
+  const int64_t tile_x = es * (a.gather ? (int64_t)(kFarTile / a.HoWo + 2) * a.img_stride : (int64_t)kFarTile * a.lda + a.K);
+  const int64_t tile_w = es * ((int64_t)kFarTile * a.ldb + a.K);
+  const bool far = !fits && tile_x < reach && tile_w < reach && !persistent;   // the persistent kernel does not hold that body
+  const bool steps = a.K * es < (int64_t)1 << 29 && (!a.gather || ((int64_t)a.kh * a.W + a.kw < 1 << 24 && a.Cin < 1 << 24));
+  // [K][N] operand, or out of the reach of 32-bit offsets: staged through registers.
+  if (a.b_kmajor || !steps || !(fits || far))
     return set(f16 ? K_igemm_f16_t64x64 : K_igemm_f32_t64x64, kTile64.bn, kTile64.bm);
+  if (far) return set(f16 ? K_igemm_f16_far128x128 : K_igemm_f32_far128x128, kFarTile, kFarTile);
   const int64_t row_bytes = a.K * es;
   const int64_t tiles32 = (int64_t)cdiv(a.M, kDirectTile) * cdiv(a.N, kDirectTile) * batch;
   if (persistent) {
