@@ -78,3 +78,48 @@ def test_together_in_one_wave(cases, dtype):
             assert not compare_all(s, ref)
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("heads,seq,d", [(3, 17, 264), (5, 70, 320), (2, 200, 520), (2, 610, 264)])
+def test_batched(heads, seq, d, dtype):
+    """Batched products, the operands interleaved head by head in their rows."""
+    b = Builder("batched", dtype)
+    q, k = b.ext((seq, heads * d)), b.ext((seq, heads * d))
+    b.add("bgemm", [q, k], [(seq, heads * d)] * 2, (heads, seq, seq), dict(mode="qk", alpha=d ** -0.5, heads=heads, seq=seq, dhead=d))
+    b.add("bgemm", [k, q], [(seq, heads * d)] * 2, (heads, seq, seq), dict(mode="qk", alpha=d ** -0.5, heads=heads, seq=seq, dhead=d))
+    wl = b.build(33)
+    ref = executor.run_dag(wl)
+    s = Session(wl)
+    try:
+        for dem in B.opara_get_demands(s.dag):
+            assert "quad" in B.opara_kernel_info(dem.kernel_id)[0] or "tile" in B.opara_kernel_info(dem.kernel_id)[0]
+        for exe in (s.capture(B.SEQUENTIAL), s.capture(B.FUSED), s.capture_chained()):
+            for t in s.out_dev:
+                t.fill_(float("nan"))
+            torch.cuda.synchronize()                         # the session replays on a stream of its own
+            s.replay(exe)
+            assert not compare_all(s, ref)
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("hw,couts", [((9, 11), (7, 33, 22)), ((31, 23), (40, 3, 66)), ((70, 67), (101, 130, 5))])
+def test_convolutions_into_slices(hw, couts, dtype):
+    """Branches that write their channels into the concatenated tensor, at offsets of any parity."""
+    b = Builder("slices", dtype)
+    x = b.ext((72,) + hw)
+    b.concat_c([b.conv(x, c, 3 if i % 2 == 0 else 1, pad=1 - i % 2) for i, c in enumerate(couts)])
+    wl = b.build(34, random_bias=True, he_init=True)
+    ref = executor.run_dag(wl)
+    s = Session(wl, zero_copy_concat=True)
+    try:
+        assert s.elided
+        for exe in (s.capture(B.SEQUENTIAL), s.capture(B.FUSED), s.capture_chained()):
+            s.out_dev[len(couts)].fill_(float("nan"))
+            torch.cuda.synchronize()
+            s.replay(exe)
+            assert not compare_all(s, ref)
+    finally:
+        s.close()
