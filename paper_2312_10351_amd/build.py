@@ -20,7 +20,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(HERE, "..", "include"), "-I", BUILD, "-I", CSRC]
 HIPFLAGS = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-            "-Werror=inline-asm"]
+            "-Werror=inline-asm", "-Werror=pass-failed"]   # pass-failed: a launch bound that is not met
 
 
 def _run(cmd):

@@ -1628,13 +1628,13 @@ KDEF(concat_f32_vec, 256, kLdsNone, ConcatArgs, (concat_body<float, 4, 0>(a, b, 
 KDEF(concat_f32_scalar, 256, kLdsNone, ConcatArgs, (concat_body<float, 1, 0>(a, b, lds)))
 // 16 x 16 output tiles: four times the workgroups of the 32 x 32 forms, half the operand bytes per workgroup
 KDEF(igemm_f16_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<half_t, 4, 2, 0, 1, 1>(a, b, lds)))
-KDEF2(igemm_f16_quad4s, 256, 4, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<half_t, 1, 1, 3, 0>(a, b, lds)))
-KDEFT(igemm_f16_quad4s_tail, 256, 4, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<half_t, 1, 1, 3, 0>(a, b, lds, tail)))
+KDEF2(igemm_f16_quad4s, 256, 3, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<half_t, 1, 1, 3, 0>(a, b, lds)))
+KDEFT(igemm_f16_quad4s_tail, 256, 3, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<half_t, 1, 1, 3, 0>(a, b, lds, tail)))
 KDEF(igemm_f32_direct4s, 256, lds_direct(4), IgemmArgs, (igemm_direct_body<float, 4, 2, 0, 1, 1>(a, b, lds)))
-KDEF2(igemm_f32_quad4s, 256, 4, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<float, 1, 1, 3, 0>(a, b, lds)))
-KDEFT(igemm_f32_quad4s_tail, 256, 4, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<float, 1, 1, 3, 0>(a, b, lds, tail)))
+KDEF2(igemm_f32_quad4s, 256, 3, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<float, 1, 1, 3, 0>(a, b, lds)))
+KDEFT(igemm_f32_quad4s_tail, 256, 3, lds_split(1, 1, 3), IgemmArgs, (igemm_split_body<float, 1, 1, 3, 0>(a, b, lds, tail)))
 
-KDEF2(attention_f16, 256, 3, kLdsAttention, AttnArgs, (attention_body(a, b, lds)))
+KDEF2(attention_f16, 256, 2, kLdsAttention, AttnArgs, (attention_body(a, b, lds)))
 
 // The 256-thread bodies by the vector registers they need (see the group kernels below):
 // X(kernel name, argument record, body call); T / tn: element type, C: access policy.
