@@ -848,6 +848,12 @@ ChainLayout chain_layout(int32_t n, int64_t total_blocks) {
   return l;
 }
 
+// The graph executors' plan, for bodies that the chained kernel does not hold the persistent executor's.
+const KernelPlan &chain_plan(const opara_dag *g, int32_t v) {
+  bool light = true;
+  return chain_kernel_ok(g->plan[v].kernel, &light) ? g->plan[v] : g->plan_persist[v];
+}
+
 int64_t chain_blocks_of(const KernelPlan &p) {
   const int64_t t = (int64_t)p.gx * p.gy * p.gz;
   return (t + kGroupAlign - 1) / kGroupAlign * kGroupAlign;
@@ -858,7 +864,7 @@ int64_t chain_blocks_of(const KernelPlan &p) {
 extern "C" int opara_chained_workspace_bytes(const opara_dag *g, uint64_t *bytes) {
   if (!g || !bytes) { set_error("opara_chained_workspace_bytes: null pointer"); return OPARA_EINVAL; }
   int64_t total = 0;
-  for (int32_t v = 0; v < g->n; ++v) total += chain_blocks_of(g->plan[v]);
+  for (int32_t v = 0; v < g->n; ++v) total += chain_blocks_of(chain_plan(g, v));
   *bytes = chain_layout(g->n, total).bytes;
   return OPARA_OK;
 }
@@ -872,7 +878,7 @@ extern "C" int opara_capture_chained(opara_dag *g, void *workspace, uint64_t wor
   const int32_t np_ops = n - prefix;
   if (n > 65535) { set_error("opara_capture_chained: more than 65535 operators"); return OPARA_EUNSUPPORTED; }
   int64_t total = 0;
-  for (int32_t i = 0; i < np_ops; ++i) total += chain_blocks_of(g->plan[g->order[prefix + i]]);
+  for (int32_t i = 0; i < np_ops; ++i) total += chain_blocks_of(chain_plan(g, g->order[prefix + i]));
   if (total > (int64_t)1 << 30) { set_error("opara_capture_chained: %lld workgroups in one launch", (long long)total); return OPARA_EUNSUPPORTED; }
   const ChainLayout lay = chain_layout(n, total);
   const PersistLayout play = persist_layout(n);
@@ -895,7 +901,7 @@ extern "C" int opara_capture_chained(opara_dag *g, void *workspace, uint64_t wor
   int64_t at = 0;
   for (int32_t i = 0; i < np_ops; ++i) {
     const int32_t v = g->order[prefix + i];
-    const KernelPlan &p = g->plan[v];
+    const KernelPlan &p = chain_plan(g, v);
     bool light = true;
     if (!chain_kernel_ok(p.kernel, &light)) { set_error("opara_capture_chained: operator %d has no 256-thread kernel", v); return OPARA_EUNSUPPORTED; }
     if (i == 0) f16 = kernel_is_f16(p.kernel);

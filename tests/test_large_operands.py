@@ -91,6 +91,42 @@ def test_gemm_past_the_reach(m, k, n):
 
 
 @pytest.mark.gpu
+def test_executors_past_the_reach():
+    """A product past the reach beside a small one: as members of a group, and in the executors whose
+    kernel does not hold the body that counts from its tile."""
+    m, k, n = 394000, 4096, 40
+    x, w = half(m, k), half(n, k, std=k ** -0.5)
+    ys = [torch.empty(rows, n, dtype=torch.float16, device="cuda") for rows in (m, 64)]
+    descs = []
+    for rows, y in zip((m, 64), ys):
+        d = desc(B.GEMM, m=rows, n=n, k=k)
+        d.weight, d.out = w.data_ptr(), y.data_ptr()
+        descs.append(d)
+    dag = B.opara_build_dag(descs, [x.data_ptr()])
+    B.opara_order_launch(dag)
+    stream = torch.cuda.Stream()
+    spaces = [torch.zeros(f(dag) + 256, dtype=torch.uint8, device="cuda") for f in (B.opara_chained_workspace_bytes, B.opara_persistent_workspace_bytes)]
+    at = [(s.data_ptr() + 255) // 256 * 256 for s in spaces]
+    torch.cuda.synchronize()
+    execs = [B.opara_capture(dag, [stream.cuda_stream], B.FUSED), B.opara_capture_chained(dag, at[0], B.opara_chained_workspace_bytes(dag)),
+             B.opara_capture_persistent(dag, at[1], B.opara_persistent_workspace_bytes(dag), 0)]
+    try:
+        for exe in execs:
+            for y in ys:
+                y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            B.opara_replay(exe, stream.cuda_stream)
+            torch.cuda.synchronize()
+            assert close(ys[1], x[:64].float() @ w.float().t()) and close(ys[0][-700:], x[-700:].float() @ w.float().t())
+            assert not torch.isnan(ys[0]).any()
+    finally:
+        for exe in execs:
+            B.opara_exec_destroy(exe)
+        B.opara_dag_destroy(dag)
+        torch.cuda.empty_cache()
+
+
+@pytest.mark.gpu
 def test_convolution_past_the_reach():
     b, h, w, c, n = 1200, 40, 40, 848, 24
     x, wt, y = half(b, h, w, c), half(n, 3, 3, c, std=(9 * c) ** -0.5), torch.full((b, h, w, n), float("nan"), dtype=torch.float16, device="cuda")
