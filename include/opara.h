@@ -383,7 +383,7 @@ int opara_verify_dependencies(opara_dag *g, void *hip_stream, int32_t *n_violati
  * to that maximum, because every workgroup must be resident.  Items follow a topological
  * order, so the holder of the lowest unfinished item can always run.
  * The executor has its own kernel plan (opara_persistent_plan: one workgroup size, so
- * the 8-wavefront and quad-coalesced contractions run the 4-wavefront fragment-loading
+ * the contractions fed through LDS run the fragment-loading
  * form), and the serial prefix of the queue runs as ordinary kernel nodes ahead of the
  * persistent kernel (opara_persistent_prefix): results may differ from the other modes
  * in the last bits, and are identical from replay to replay.
@@ -471,7 +471,7 @@ int opara_persistent_reset(opara_exec *e, void *hip_stream, uint32_t spin_limit)
  * blocks come before its consumers' blocks, so the lowest unfinished block can always run:
  * the launch drains with whatever number of workgroups the device holds at a time, beside
  * other kernels too (no residency assumption).  And because a body is straight-line code
- * behind the wait, the kernel holds every 256-thread body, the quad-coalesced contractions
+ * behind the wait, the kernel holds every 256-thread body, the LDS-fed contractions
  * included (kernel plan: the one of OPARA_FUSED's group nodes).
  * workspace: device memory, caller-owned, 256-byte aligned, at least
  * opara_chained_workspace_bytes() bytes, exclusively this executor's until it is destroyed.

@@ -6,7 +6,7 @@
 // stored fp16 values of the stage before.
 //
 // What bounds it: three launches and two passes of the scores through memory, at these sizes
-// (12 heads x 128 x 64: 1.2 MB in all) hardly any arithmetic.  Sixteen rows per workgroup because
+// (12 heads x 128 x 64: 1.6 MB in all, half of it scores and probabilities) hardly any arithmetic.  Sixteen rows per workgroup because
 // a head has few rows (128: 96 workgroups, 512: 384); a row of up to kAttnMaxCols scores fits one
 // 16-byte chunk per lane of a wavefront.  The columns are dealt to the four wavefronts in tiles;
 // a wavefront stages its own tiles of K, and later of V, in its own ring and waits for its own

@@ -57,7 +57,8 @@ __device__ __forceinline__ void stg(P *p, const V &v) {
   } else if constexpr (sizeof(V) == 16) {
     // One 16-byte write-through store (what a relaxed agent-scope atomic store compiles to for
     // 8 bytes, `global_store_dwordx2 ... sc1`, in its four-dword form): the language has no
-    // 16-byte atomic, and two 8-byte ones reach memory as two partial-line writes.  The nop
+    // 16-byte atomic, and two 8-byte ones reach memory as two partial-line writes.  Like any plain
+    // store of the machine it takes element alignment.  The nop
     // covers the wait state a store of more than 8 bytes needs before its data registers
     // may be overwritten.
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -751,7 +752,7 @@ template <typename T, bool CS, typename AR>
 __device__ __forceinline__ void store4(const AR &a, T *dst, floatx4 v, int n) {
   typedef typename Vec16<T>::quad Q;
   typedef typename Run4<T>::type R;
-  const bool full = n + 3 < a.N && (!CS || ((uintptr_t)dst & (4 * sizeof(T) - 1)) == 0);   // coherent stores need alignment
+  const bool full = n + 3 < a.N && (!CS || ((uintptr_t)dst & (4 * sizeof(T) - 1)) == 0);   // atomic stores (8 bytes) need alignment
   if (full) {
     if constexpr (CS) stg<CS, Q>(dst, Q{(T)v[0], (T)v[1], (T)v[2], (T)v[3]});
     else *(R *)dst = R{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
@@ -1925,8 +1926,11 @@ extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f32(Persist
 // does.  No flags, no coherent accesses: kernel boundaries order the groups.  Three flavours
 // per element type, by the registers their bodies need: "stream" (at most 64: pooling,
 // row-wise, element-wise, concatenation, matrix-vector; eight wavefronts per SIMD stay
-// resident, which streaming wants), "light" (at most 128: those plus the fragment-loading
-// and 16 x 16-tile contractions; four per SIMD), "heavy" (all 256-thread bodies; two).
+// resident, which streaming wants), "light" (at most 128: those plus the register-staged, the
+// fragment-loading and the 16 x 16 and 32 x 32 LDS-fed contractions; four per SIMD), "heavy" (all
+// 256-thread bodies; two).  Every workgroup of a group has the workgroup memory of its largest
+// member: beside a 16 x 16 LDS-fed contraction (48 KB) three of them share a CU, beside a 32 x 32
+// one (64 KB) two, whatever the registers would allow.
 // ---------------------------------------------------------------------------------
 template <bool F16, int FLAVOR, bool TRACE>
 __device__ __forceinline__ void group_body() {
@@ -2041,7 +2045,7 @@ GROUPK(f32_heavy, 2, false, 2)
 // operator's predecessors (see ChainArgs).  Same hand-off as the persistent kernel (results
 // through device-coherent stores, completion counters and replicated flags, one cache
 // invalidate per workgroup), but no loop: a body is straight-line code behind the wait, so
-// nothing is hoisted across bodies, the quad-coalesced contractions can be held, and the
+// nothing is hoisted across bodies, the LDS-fed contractions can be held, and the
 // launch does not depend on all its workgroups being resident at once.
 // ---------------------------------------------------------------------------------
 template <bool F16, bool LIGHT>

@@ -25,9 +25,9 @@ inline uint32_t cdiv(int64_t a, int64_t b) { return (uint32_t)((a + b - 1) / b);
 // The contractions fed through workgroup memory, and what one workgroup of each costs, in
 // microseconds: a 128-byte step of K when the workgroup has a compute unit to itself
 // (`alone`) and when the launch keeps every CU busy (`busy`), and everything outside the K
-// walk (`fixed`).  `together`: how much longer the work takes inside a group kernel, which holds
-// two workgroups per CU where the body by itself would leave room for three (three 512 x 768 x
-// 768 products: 8.3 -> 7.5 us with the tiles this makes them take).  Fitted to isolated fp16 products, M x N x K = 49..346688 x 32..4096 x
+// walk (`fixed`).  `together`: how much longer the work takes beside other contractions of a wave;
+// fitted, like the rest (three 512 x 768 x 768 products: 8.3 -> 7.5 us with the tiles this makes
+// them take).  Fitted to isolated fp16 products, M x N x K = 49..346688 x 32..4096 x
 // 320..4096, within 15 %.  In fp32 a step cannot take less than its multiply-adds at the
 // matrix rate of a CU (0.6 TFLOP/s).
 struct TileKernel { int ids[2]; int bn, bm; double alone, busy, fixed, together; };   // ids: f32, f16
@@ -297,7 +297,8 @@ int plan_concat(const opara_op_desc &op, const void *const *in, KernelPlan *out)
 
 }  // namespace
 
-// Tile shapes of contractions that run together (the contractions of a wave, or one by itself).
+// Tile shapes of contractions that run together (the contractions of a wave, or one by itself,
+// also where that one shares its group kernel with operators of other types).
 // Small tiles finish one operator sooner (more CUs share it), large ones move
 // fewer bytes per multiply-add; what counts is the longer of the time the work takes on all
 // CUs together and the time the longest workgroup takes.  For every bound on the latter,
