@@ -214,7 +214,7 @@ int capture_fused(opara_dag *g, opara_exec **out) {
       for (int32_t v : wave)
         if (tile_choice_open(plan[v].kernel)) open[kernel_is_f16(plan[v].kernel)].push_back(&plan[v]);
       for (auto &o : open)
-        if (!o.empty()) choose_tiles(o.data(), (int)o.size());
+        if (!o.empty()) choose_tiles(o.data(), (int)o.size(), true);
     }
     // Operators of one element type share group kernels; waves of one run as ordinary kernel nodes.
     std::vector<int32_t> members;

@@ -73,6 +73,6 @@ std::vector<ConcatMerge> find_concat_merges(const opara_dag *g, const std::vecto
 bool tile_choice_open(int kernel_id);
 // The same contraction with an element-wise operator after it (KernelPlan::tail); -1: none.
 int tail_kernel(int kernel_id);
-void choose_tiles(KernelPlan *const *plans, int n);
+void choose_tiles(KernelPlan *const *plans, int n, bool grouped);
 
 }  // namespace opara

@@ -25,7 +25,7 @@ inline uint32_t cdiv(int64_t a, int64_t b) { return (uint32_t)((a + b - 1) / b);
 // The contractions fed through workgroup memory, and what one workgroup of each costs, in
 // microseconds: a 128-byte step of K when the workgroup has a compute unit to itself
 // (`alone`) and when the launch keeps every CU busy (`busy`), and everything outside the K
-// walk (`fixed`).  `together`: how much longer the work takes beside other contractions of a wave;
+// walk (`fixed`).  `together`: how much longer the work takes inside a group kernel;
 // fitted, like the rest (three 512 x 768 x 768 products: 8.3 -> 7.5 us with the tiles this makes
 // them take).  Fitted to isolated fp16 products, M x N x K = 49..346688 x 32..4096 x
 // 320..4096, within 15 %.  In fp32 a step cannot take less than its multiply-adds at the
@@ -170,7 +170,7 @@ int plan_igemm(const opara_op_desc &op, const void *const *in, int kind, KernelP
   }
   set(kTileKernels[0].ids[f16], kTileKernels[0].bn, kTileKernels[0].bm);
   KernelPlan *one = out;
-  choose_tiles(&one, 1);
+  choose_tiles(&one, 1, false);
   return OPARA_OK;
 }
 
@@ -297,15 +297,15 @@ int plan_concat(const opara_op_desc &op, const void *const *in, KernelPlan *out)
 
 }  // namespace
 
-// Tile shapes of contractions that run together (the contractions of a wave, or one by itself,
-// also where that one shares its group kernel with operators of other types).
+// Tile shapes of contractions that run together: those of a wave that becomes a group kernel
+// (`grouped`, also where there is only one beside operators of other types), or a launch of its own.
 // Small tiles finish one operator sooner (more CUs share it), large ones move
 // fewer bytes per multiply-add; what counts is the longer of the time the work takes on all
 // CUs together and the time the longest workgroup takes.  For every bound on the latter,
 // each operator takes its cheapest tile shape within it; the best bound wins.  The bounds are
 // visited in increasing order, and each only changes the one operator whose shape it admits
 // (trying every operator again under every bound took seconds for a wave of some thousand).
-void choose_tiles(KernelPlan *const *plans, int n) {
+void choose_tiles(KernelPlan *const *plans, int n, bool grouped) {
   struct Option { double longest, work; int op, shape; };
   std::vector<Option> options;
   for (int i = 0; i < n; ++i) {
@@ -320,8 +320,8 @@ void choose_tiles(KernelPlan *const *plans, int n) {
       o.op = i;
       o.shape = k;
       o.longest = steps * std::max(t.alone, least) + t.fixed;
-      o.work = tiles * (steps * std::max(t.busy, least) + t.fixed) / kCus * (n > 1 ? t.together : 1.0);
-      if (n == 1 && tiles > kCus && tiles < 4 * kCus)      // a single launch: whole rounds over the CUs
+      o.work = tiles * (steps * std::max(t.busy, least) + t.fixed) / kCus * (grouped ? t.together : 1.0);
+      if (!grouped && tiles > kCus && tiles < 4 * kCus)      // a single launch: whole rounds over the CUs
         o.work *= std::ceil(tiles / kCus) * kCus / tiles;
       options.push_back(o);
     }
