@@ -24,7 +24,7 @@ struct opara_exec {
   void *workspace = nullptr;
   int32_t persist_ops = 0, persist_items = 0, persist_workgroups = 0, persist_prefix = 0;
   opara::PersistArgs persist_args{};   // the persistent kernel's launch: arguments, element type, LDS
-  bool persist_f16 = false;
+  bool persist_f16 = false, persist_tiled = false;
   uint32_t persist_lds = 0;
   // chained executor (the loop-free form of the persistent one): shares the fields above
   bool chained = false, chain_light = false;
@@ -656,9 +656,11 @@ int build_persist_image(const opara_dag *g, int32_t n_workgroups, const char *wh
   // Workgroups the device holds at once: the launch size, and the tiles per work item of
   // operators that have more tiles than that.
   const bool f16 = kernel_is_f16(persist_kernel_id(g->plan_persist[g->order[prefix]].kernel));
+  const int tile = f16 ? K_igemm_f16_t128x64 : K_igemm_f32_t128x64;
+  const bool tiled = std::any_of(g->order.begin() + prefix, g->order.end(), [&](int32_t v) { return g->plan_persist[v].kernel == tile; });
   uint32_t wgs = 0;
   {
-    hipError_t err = persist_max_workgroups(f16, lds_bytes, &wgs);
+    hipError_t err = persist_max_workgroups(f16, tiled, lds_bytes, &wgs);
     if (err != hipSuccess) {
       set_error("%s: occupancy query failed: %s", who, hipGetErrorString(err));
       (void)hipGetLastError();
@@ -718,6 +720,7 @@ int build_persist_image(const opara_dag *g, int32_t n_workgroups, const char *wh
   img->wgs = wgs;
   img->lds_bytes = lds_bytes;
   img->f16 = f16;
+  img->tiled = tiled;
   return OPARA_OK;
 }
 
@@ -767,7 +770,7 @@ extern "C" int opara_capture_persistent(opara_dag *g, void *workspace, uint64_t 
       HIP_TRY(add_plan_node(e->graph, g->plan[g->order[q]], last ? &last : nullptr, last ? 1 : 0, &node));
       last = node;
     }
-    HIP_TRY(add_persist_node(e->graph, img.f16, pa, img.wgs, img.lds_bytes, last ? &last : nullptr, last ? 1 : 0, &node));
+    HIP_TRY(add_persist_node(e->graph, img.f16, img.tiled, pa, img.wgs, img.lds_bytes, last ? &last : nullptr, last ? 1 : 0, &node));
     HIP_TRY(hipGraphInstantiate(&e->exec, e->graph, nullptr, nullptr, 0));
     e->n_nodes = img.prefix + 1;
     e->n_edges = img.prefix;
@@ -775,6 +778,7 @@ extern "C" int opara_capture_persistent(opara_dag *g, void *workspace, uint64_t 
     e->persist_prefix = img.prefix;
     e->persist_args = pa;
     e->persist_f16 = img.f16;
+    e->persist_tiled = img.tiled;
     e->persist_lds = img.lds_bytes;
     e->persist_ops = n;
     e->persist_items = img.total;
@@ -820,7 +824,7 @@ extern "C" int opara_run_persistent_noalloc(opara_dag *g, void *hip_stream, uint
     // whatever the previous call (of this or another DAG) left in the array.
     HIP_TRY(hipMemcpyAsync(ws, img.host.data(), lay.bytes, hipMemcpyHostToDevice, st));
     for (int32_t q = 0; q < img.prefix; ++q) HIP_TRY(launch_plan(g->plan[g->order[q]], st));
-    HIP_TRY(launch_persist(img.f16, persist_args_at(img, n, ws), img.wgs, img.lds_bytes, st));
+    HIP_TRY(launch_persist(img.f16, img.tiled, persist_args_at(img, n, ws), img.wgs, img.lds_bytes, st));
     if (error_word) {
       PersistHeader h;
       HIP_TRY(hipMemcpyAsync(&h, ws, sizeof(h), hipMemcpyDeviceToHost, st));
@@ -1008,7 +1012,7 @@ extern "C" int opara_persistent_time_kernel(opara_exec *e, void *hip_stream, int
   HIP_TRY(hipEventRecord(t0, st));
   for (int32_t i = 0; i < launches; ++i) {
     if (e->chained) HIP_TRY(launch_chain(e->persist_f16, e->chain_light, e->chain_args, e->persist_lds, st));
-    else HIP_TRY(launch_persist(e->persist_f16, e->persist_args, (uint32_t)e->persist_workgroups, e->persist_lds, st));
+    else HIP_TRY(launch_persist(e->persist_f16, e->persist_tiled, e->persist_args, (uint32_t)e->persist_workgroups, e->persist_lds, st));
   }
   HIP_TRY(hipEventRecord(t1, st));
   HIP_TRY(hipEventSynchronize(t1));

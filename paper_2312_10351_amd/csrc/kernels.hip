@@ -1697,7 +1697,10 @@ template <typename A> __device__ __forceinline__ A load_uniform(const void *p) {
 // Loads inside the persistent kernel are plain: each work item starts with one cache
 // invalidate (acquire at device scope).  (Device-coherent loads instead cost 5-10 % more
 // latency: every operand re-read goes past the L2.)
-template <bool F16>
+// TILED: the kernel holds the 128 x 64 tile for heavy contractions as well.  Its scalar state makes the
+// compiler spill in the loop around every body, so that DAGs without such a contraction run without
+// it (us: BERT-like 1171 -> 1154, Inception-v3-like 458 -> 453, NASNet-like 157 -> 154).
+template <bool F16, bool TILED>
 __device__ __forceinline__ void persist_run(int kernel, const PersistOp *r, const Blk &b, unsigned char *lds) {
 #define PCASE(name, Args, call)                               \
   case K_##name: {                                            \
@@ -1706,7 +1709,6 @@ __device__ __forceinline__ void persist_run(int kernel, const PersistOp *r, cons
     call;                                                     \
   } break;
 #define PERSIST_BODIES(T, VE, tn)                                                                             \
-  PCASE(igemm_##tn##_t128x64, IgemmArgs, (igemm_tile_body<T, 128, 64, 2, 2, 2, kCohStore>(a, b, lds)))        \
   PCASE(igemm_##tn##_t64x64, IgemmArgs, (igemm_body<T, 64, 64, 2, 2, true, kCohStore>(a, b, lds)))            \
   PCASE(igemm_##tn##_direct4, IgemmArgs, (igemm_direct_body<T, 4, 2, kCohStore, 2, 2>(a, b, lds)))            \
   PCASE(igemm_##tn##_t64x64_scalar, IgemmArgs, (igemm_body<T, 64, 64, 2, 2, false, kCohStore>(a, b, lds)))    \
@@ -1714,12 +1716,26 @@ __device__ __forceinline__ void persist_run(int kernel, const PersistOp *r, cons
   if constexpr (F16) {
     switch (kernel) {
       PERSIST_BODIES(half_t, 8, f16)
-      default: break;
+      default:
+        if constexpr (TILED) {
+          switch (kernel) {
+            PCASE(igemm_f16_t128x64, IgemmArgs, (igemm_tile_body<half_t, 128, 64, 2, 2, 2, kCohStore>(a, b, lds)))
+            default: break;
+          }
+        }
+        break;
     }
   } else {
     switch (kernel) {
       PERSIST_BODIES(float, 4, f32)
-      default: break;
+      default:
+        if constexpr (TILED) {
+          switch (kernel) {
+            PCASE(igemm_f32_t128x64, IgemmArgs, (igemm_tile_body<float, 128, 64, 2, 2, 2, kCohStore>(a, b, lds)))
+            default: break;
+          }
+        }
+        break;
     }
   }
 #undef PERSIST_BODIES
@@ -1792,7 +1808,7 @@ __device__ __forceinline__ int persist_find(const int32_t *begin, int n, uint32_
 // one iteration straight into the next; the other lanes of its wavefront then reach the
 // barrier on their own, the wavefront arrives twice and the barrier count of the
 // workgroup no longer matches.
-template <bool F16>
+template <bool F16, bool TILED>
 __device__ __forceinline__ void persist_body(const PersistArgs &pa) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_lds[];
   unsigned char *lds = dyn_lds;                                  // kPersistBodyLds bytes for the bodies
@@ -1868,7 +1884,7 @@ __device__ __forceinline__ void persist_body(const PersistArgs &pa) {
       b.z = rest / hd.z;
       b.lin = b.y * hd.y + b.x;
       if (k > 0) __syncthreads();                                // the previous tile is done with workgroup memory
-      persist_run<F16>(hd.x, r, b, lds);
+      persist_run<F16, TILED>(hd.x, r, b, lds);
     }
     // While the stores drain: touch the next item's record so that its argument loads find
     // it in the scalar cache.  The values only feed a sink that is tested after the loop.
@@ -1915,8 +1931,10 @@ __device__ __forceinline__ void persist_body(const PersistArgs &pa) {
   }
 }
 
-extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f16(PersistArgs pa) { persist_body<true>(pa); }
-extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f32(PersistArgs pa) { persist_body<false>(pa); }
+extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f16(PersistArgs pa) { persist_body<true, false>(pa); }
+extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f32(PersistArgs pa) { persist_body<false, false>(pa); }
+extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f16_tiled(PersistArgs pa) { persist_body<true, true>(pa); }
+extern "C" __global__ void __launch_bounds__(256, 2) opara_k_persist_f32_tiled(PersistArgs pa) { persist_body<false, true>(pa); }
 
 // ---------------------------------------------------------------------------------
 // Group kernel (fused executor): one launch runs several mutually independent operators.
@@ -2424,28 +2442,34 @@ bool kernel_is_f16(int id) {
   }
 }
 
-hipError_t persist_max_workgroups(bool f16, uint32_t lds_bytes, uint32_t *n_workgroups) {
+namespace {
+typedef void (*PersistKernel)(PersistArgs);
+PersistKernel persist_func(bool f16, bool tiled) {
+  return f16 ? (tiled ? opara_k_persist_f16_tiled : opara_k_persist_f16) : (tiled ? opara_k_persist_f32_tiled : opara_k_persist_f32);
+}
+}  // namespace
+
+hipError_t persist_max_workgroups(bool f16, bool tiled, uint32_t lds_bytes, uint32_t *n_workgroups) {
   int dev = 0, cus = 0, per_cu = 0;
   hipError_t err = hipGetDevice(&dev);
   if (err != hipSuccess) return err;
   err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (err != hipSuccess) return err;
-  const void *func = f16 ? (const void *)opara_k_persist_f16 : (const void *)opara_k_persist_f32;
-  err = hipFuncSetAttribute(func, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPersistMaxLds);   // for every executor alike
+  err = hipFuncSetAttribute((const void *)persist_func(f16, tiled), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kPersistMaxLds);   // for every executor alike
   if (err != hipSuccess) return err;
-  err = f16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, opara_k_persist_f16, 256, lds_bytes)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, opara_k_persist_f32, 256, lds_bytes);
+  err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persist_func(f16, tiled), 256, lds_bytes);
   if (err != hipSuccess) return err;
   *n_workgroups = (uint32_t)(per_cu > 0 ? per_cu : 0) * (uint32_t)cus;
   return hipSuccess;
 }
 
-hipError_t add_persist_node(hipGraph_t graph, bool f16, const PersistArgs &a, uint32_t n_workgroups,
+hipError_t add_persist_node(hipGraph_t graph, bool f16, bool tiled, const PersistArgs &a, uint32_t n_workgroups,
                             uint32_t lds_bytes, const hipGraphNode_t *deps, size_t n_deps, hipGraphNode_t *node) {
   PersistArgs args = a;
   void *kparams[1] = {&args};
   hipKernelNodeParams np = {};
-  np.func = f16 ? (void *)opara_k_persist_f16 : (void *)opara_k_persist_f32;
+  np.func = (void *)persist_func(f16, tiled);
   np.gridDim = dim3(n_workgroups);
   np.blockDim = dim3(256);
   np.sharedMemBytes = lds_bytes;
@@ -2453,9 +2477,8 @@ hipError_t add_persist_node(hipGraph_t graph, bool f16, const PersistArgs &a, ui
   return hipGraphAddKernelNode(node, graph, deps, n_deps, &np);
 }
 
-hipError_t launch_persist(bool f16, const PersistArgs &a, uint32_t n_workgroups, uint32_t lds_bytes, hipStream_t s) {
-  if (f16) hipLaunchKernelGGL(opara_k_persist_f16, dim3(n_workgroups), dim3(256), lds_bytes, s, a);
-  else hipLaunchKernelGGL(opara_k_persist_f32, dim3(n_workgroups), dim3(256), lds_bytes, s, a);
+hipError_t launch_persist(bool f16, bool tiled, const PersistArgs &a, uint32_t n_workgroups, uint32_t lds_bytes, hipStream_t s) {
+  hipLaunchKernelGGL(persist_func(f16, tiled), dim3(n_workgroups), dim3(256), lds_bytes, s, a);
   return hipGetLastError();
 }
 

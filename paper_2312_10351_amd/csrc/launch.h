@@ -93,11 +93,12 @@ struct PersistArgs {
 int persist_kernel_id(int kernel_id);              // -1: not available
 bool kernel_is_f16(int kernel_id);
 // Workgroups of the persistent kernel the device holds at once (all must be resident).
-hipError_t persist_max_workgroups(bool f16, uint32_t lds_bytes, uint32_t *n_workgroups);
-hipError_t add_persist_node(hipGraph_t graph, bool f16, const PersistArgs &a, uint32_t n_workgroups,
+// tiled: the form of it that holds the 128 x 64 tile.
+hipError_t persist_max_workgroups(bool f16, bool tiled, uint32_t lds_bytes, uint32_t *n_workgroups);
+hipError_t add_persist_node(hipGraph_t graph, bool f16, bool tiled, const PersistArgs &a, uint32_t n_workgroups,
                             uint32_t lds_bytes, const hipGraphNode_t *deps, size_t n_deps, hipGraphNode_t *node);
 // The same kernel as an ordinary launch on `s` (for timing it apart from the graph it belongs to).
-hipError_t launch_persist(bool f16, const PersistArgs &a, uint32_t n_workgroups, uint32_t lds_bytes, hipStream_t s);
+hipError_t launch_persist(bool f16, bool tiled, const PersistArgs &a, uint32_t n_workgroups, uint32_t lds_bytes, hipStream_t s);
 
 // ---- Chained executor: the persistent executor without a work-item loop ----------------
 // One launch whose grid is the sum of all operators' grids in launch-queue order (each

@@ -14,7 +14,7 @@ struct PersistImage {
   int32_t prefix = 0;               // leading queue operators launched as ordinary kernels
   int32_t np_ops = 0, total = 0;    // operators inside the kernel, work items
   uint32_t wgs = 0, lds_bytes = 0;  // workgroups of the launch, dynamic LDS per workgroup
-  bool f16 = false;
+  bool f16 = false, tiled = false;  // tiled: some operator inside takes the 128 x 64 tile
 };
 }  // namespace opara
 
